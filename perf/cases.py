@@ -116,6 +116,14 @@ def _products(case):
     return [(case["M"], case["K"])]
 
 
+def _operands(case, gen, rows):
+    """M, K, X [N, K] and W [M, K] of each product of a case that multiplies, drawn in this order."""
+    dense = case["op"] == "dense"
+    for M, K in _products(case):
+        X = torch.randn((case["N"], K), generator=gen, device="cuda").half()
+        yield M, K, X, _weights(M, K, 0.0 if dense else case["sparsity"], "uniform" if dense else case["mask"], gen, rows)
+
+
 def prepare(case, seed):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     rows = np.random.default_rng(seed)
@@ -125,15 +133,13 @@ def prepare(case, seed):
         out = torch.zeros(room, dtype=torch.uint8, device="cuda")
         return {"case": case, "W": _weights(case["M"], case["K"], case["sparsity"], case["mask"], gen, rows), "out": out}
     N, calls, outs = case["N"], [], []
-    for M, K in _products(case):
-        X = torch.randn((N, K), generator=gen, device="cuda").half()
+    for M, K, X, W in _operands(case, gen, rows):
         C = torch.empty((N, M), dtype=torch.float16, device="cuda")
         fls.ensure_workspace(M, K, N)
         if case["op"] == "dense":
-            W = _weights(M, K, 0.0, "uniform", gen, rows)
             calls.append((fls.fls_dense_gemm, (W, X, C, M, K, N)))
         else:
-            blob, stats = _compress(_weights(M, K, case["sparsity"], case["mask"], gen, rows), case["version"])
+            blob, stats = _compress(W, case["version"])
             if case["op"] == "layer":
                 calls.append((fls.prepare_spmm(blob, X, C, M, K, N), ()))
             elif case["entry"] == "fls_spmm":
@@ -173,3 +179,17 @@ def tolerance(case):
     operands it is off by 2.1e-4 (2-norm) and by 4.9e-4 of the larger of a value and the root mean square; about four
     times that."""
     return "exact" if case["op"] == "compress" else {"rel": 8e-4, "max": 2e-3}
+
+
+def exact(case, seed):
+    """C in 64 bits from the same fp16 operands, a few thousand rows of W at a time."""
+    if case["op"] == "compress":
+        return None
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    outs = []
+    for M, K, X, W in _operands(case, gen, np.random.default_rng(seed)):
+        X, C = X.double(), torch.empty((case["N"], M), dtype=torch.float64, device="cuda")
+        for r in range(0, M, 4096):
+            C[:, r:r + 4096] = X @ W[r:r + 4096].double().T
+        outs.append(C)
+    return outs
