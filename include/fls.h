@@ -97,7 +97,8 @@ int fls_compress_bound(int64_t M, int64_t K, size_t* bytes_host);
  *   stats_host   out: may be NULL; filled on FLS_OK; on FLS_ECAPACITY bytes_total holds a size that is enough
  *                     (the exact size once the tiles are counted, the worst-case bound if out_capacity
  *                     did not even hold header and TileOffsets)
- * The result is a pure function of (W bits, M, K, order_policy).  Waits for its own kernels.
+ * The result is a pure function of (W bits, M, K, order_policy).  Waits for its own kernels.  On FLS_ECAPACITY
+ * the contents of out_dev are unspecified (nothing past out_capacity is written).
  * Uses the start of out_dev as scratch, so out_capacity must cover header and TileOffsets even
  * for an all-zero matrix.  Errors: FLS_EINVAL, FLS_EALIGN, FLS_ECAPACITY, FLS_EHIP.
  */

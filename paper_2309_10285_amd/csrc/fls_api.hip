@@ -193,11 +193,12 @@ static int compress_impl(const void* W_dev, int64_t M, int64_t K, void* out_dev,
   a.K = (uint32_t)K;
   a.policy = (uint32_t)order_policy;
   a.version = version;
+  a.capacity = out_capacity;
   {
     std::lock_guard<std::mutex> lk(g_mu);
     g_blobs.erase(out_dev);
   }
-  if (fls::launch_compress_index(a, s) != hipSuccess) return FLS_EHIP;
+  if (fls::launch_compress(a, s) != hipSuccess) return FLS_EHIP;
   unsigned char hdr[FLS_HEADER_BYTES];
   if (hipMemcpyAsync(hdr, out_dev, FLS_HEADER_BYTES, hipMemcpyDeviceToHost, s) != hipSuccess) return FLS_EHIP;
   if (hipStreamSynchronize(s) != hipSuccess) return FLS_EHIP;
@@ -208,8 +209,6 @@ static int compress_impl(const void* W_dev, int64_t M, int64_t K, void* out_dev,
     if (stats_host) *stats_host = st;
     return FLS_ECAPACITY;
   }
-  if (fls::launch_compress_emit(a, s) != hipSuccess) return FLS_EHIP;
-  if (hipStreamSynchronize(s) != hipSuccess) return FLS_EHIP;
   if (stats_host) *stats_host = st;
   {
     std::lock_guard<std::mutex> lk(g_mu);

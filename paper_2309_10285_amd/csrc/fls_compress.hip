@@ -1,166 +1,433 @@
 // fls_compress: dense masked W -> Tiled-CSL blob on the GPU (the paper's offline weight
-// reformatting step, Sec. 5; format Sec. 4.3.1-4.3.2; tile walk of Alg. 3).
+// reformatting step, Sec. 5; format Sec. 4.3.1-4.3.2; tile walk of Alg. 3), both format versions.
 //
-// Three kernels, all integer work on fp16 bit patterns (no value passes through a float op):
-//   count : one wave per tile counts the non-zero bit patterns and leaves the count in the
-//           tile's TileOffsets entry
-//   scan  : one workgroup turns the counts into padded run lengths and their exclusive prefix
-//           sums, fills the guard entries, and writes the header (nnz, longest run included)
-//   emit  : one wave per tile walks the tile in location order; per step every lane holds the 8
-//           halves of one (row, K-chunk) cell, a wave prefix sum of the per-lane counts gives each
-//           lane its slot in the run (ordered compaction)
+// All integer work on fp16 bit patterns (no value passes through a float op).  W is read from memory
+// once: a workgroup takes a chunk of 16 consecutive tiles, holds it in registers, counts it, learns
+// where its words start from the chunks before it while they are still at work (a scan by look-back over
+// published chunk sums), and writes the words.  Two kernels:
+//   emit   : everything but the index; leaves the chunk's running sum and its tiles' counts in the
+//            place of the chunk's own TileOffsets entries
+//   finish : turns those into TileOffsets, fills the guard entries and writes the header
+// Format version 1: an entry is a stored element, one 32-bit word (value, location), runs padded to a
+// multiple of four.  Format version 2, three bytes per entry: a tile's entries, in ascending location, go in
+// groups of four that take three words - two of values, one with the first entry's location in
+// 12 bits and the other three as 6-bit distances from the entry before.  An entry is a stored
+// element, a bridge (value 0) every 63 locations where the next stored element lies more than 63
+// behind the entry before it, or padding (value 0, distance 1) up to a multiple of four.
 #include "fls_device.h"
 #include "fls_launch.h"
 
 namespace fls {
 
-constexpr uint32_t kMagic = 0x31534C46u;  // "FLS1"
-constexpr uint32_t kPad = 4;
+constexpr uint32_t kMagic = 0x31534C46u;   // "FLS1"
+constexpr uint32_t kMagic2 = 0x32534C46u;  // "FLS2"
+constexpr uint32_t kPad = 4;               // words a run is padded to (version 1), entries per group (version 2)
+constexpr uint32_t kReach2 = 63;           // largest distance a 6-bit field holds
+
+constexpr int kChunkWaves = 8;
+constexpr int kTilesPerWave = 2;
+constexpr int kChunkTiles = kChunkWaves * kTilesPerWave;
+constexpr int kCells = kTileElems / 8 / 64;  // (row, K chunk) cells of a tile that a lane holds: 8 halves each
+// Entries that a wave's 8 KB of LDS stages at once (a word each, or a value and a location of 16 bits each);
+// a denser tile goes out in two rounds.
+constexpr uint32_t kStageEntries = 2048;
+
+// Where chunk q's state stands until the finish kernel runs: in words 16 q ... 16 q + 9 of TileOffsets (n_off
+// is a multiple of 16 and at least T + 4, so the last, partly empty chunk has room too).
+//   words 0, 1  running sum of words in bits 0 - 31, the chunk's stored elements in bits 32 - 48, kState* in bits 62 - 63
+//   words 2 - 9 entries of its 16 tiles, 16 bits each
+constexpr uint64_t kStateSum = 1ull << 62;     // the sum is the chunk's own
+constexpr uint64_t kStatePrefix = 2ull << 62;  // the sum is that of all chunks up to and including this one
+static_assert(kChunkTiles == 16, "the state of a chunk stands in the place of its 16 offsets");
+
+constexpr int kHeaderTicket = 7;   // header word: next chunk to be taken (0 again in a finished blob)
+constexpr int kHeaderGaveUp = 15;  // header word (upper half of total_words): 1 if a look-back gave up
 
 struct CompressParams {
   const uint16_t* W;
   unsigned char* out;
+  uint64_t capacity_words;  // words that fit behind TileOffsets
   uint32_t M, K, KT, T, n_off, policy;
 };
 
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
 __device__ __forceinline__ uint32_t* offs_of(const CompressParams& p) { return (uint32_t*)(p.out + 64); }
 __device__ __forceinline__ uint32_t* words_of(const CompressParams& p) { return (uint32_t*)(p.out + 64 + 4 * (size_t)p.n_off); }
+__device__ __forceinline__ uint64_t* state_of(const CompressParams& p, uint32_t q) { return (uint64_t*)(p.out + 64 + (size_t)q * 64); }
 
-__device__ __forceinline__ uint32_t nonzero_mask(const u32x4& v) {
-  uint32_t m = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    m |= ((v[i] & 0xffffu) != 0u ? 1u : 0u) << (2 * i);
-    m |= ((v[i] >> 16) != 0u ? 1u : 0u) << (2 * i + 1);
-  }
-  return m;
+template <int FMT>
+__device__ __forceinline__ uint32_t run_words(uint32_t entries) {
+  return FMT == 2 ? (entries + kPad - 1) / kPad * 3u : (entries + kPad - 1) / kPad * kPad;
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+// inclusive prefix sum over the 64 lanes
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+__device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
   return v;
 }
 
-// inclusive prefix sum over the 64 lanes
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t up = __shfl_up(v, d, 64);
-    if (lane >= d) v += up;
-  }
-  return v;
+// A tile as a wave holds it for the walk in location order (K chunk, then row, then position in the chunk): in
+// step s a lane has the cell (row 64 (s & 1) + lane, K chunk s >> 1), 8 consecutive locations.
+struct TileCells {
+  u32x4 v[kCells];
+  // Entries of the steps before this lane, three steps to a word, ten bits each: a step has at most 512 stored
+  // elements and 65 bridges.
+  uint32_t before[3], total[3];
+  uint32_t entries;       // of the tile, padding not counted
+  uint32_t last;          // (version 2) location of its last stored element
+};
+
+__device__ __forceinline__ uint32_t field10(const uint32_t (&w)[3], int s) { return (w[s / 3] >> (10 * (s % 3))) & 0x3ffu; }
+
+__device__ __forceinline__ uint32_t half_of(const u32x4& v, int e) { return (e & 1) ? v[e >> 1] >> 16 : v[e >> 1] & 0xffffu; }
+
+__device__ __forceinline__ uint32_t cell_location(int s, int lane) {
+  return (uint32_t)(s >> 1) * (kTileM * 8) + ((uint32_t)(s & 1) * 64 + (uint32_t)lane) * 8;
 }
 
-__global__ __launch_bounds__(256) void compress_count_kernel(CompressParams p) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= p.T) return;
-  const uint32_t band = t / p.KT, kt = t - band * p.KT;
-  // lane covers rows (lane >> 2) + 16*i, K chunk (lane & 3): 16 rows x 64 B per step
-  const uint16_t* src = p.W + ((size_t)band * kTileM + (lane >> 2)) * p.K + kt * kTileK + (lane & 3) * 8;
-  uint32_t cnt = 0;
+// stored elements of a cell: min(half, 1) summed, two halves at a time (an asm statement: of the same min in C++ the
+// compiler makes a compare and a select per half, and the counts came out wrong)
+__device__ __forceinline__ uint32_t cell_count(const u32x4& v) {
+  u16x2 n = {0, 0};
 #pragma unroll
-  for (int i = 0; i < kTileM / 16; ++i) {
-    const u32x4 v = *(const u32x4*)(src + (size_t)i * 16 * p.K);
-    cnt += __popc(nonzero_mask(v));
+  for (int i = 0; i < 4; ++i) {
+    u16x2 one;
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(one) : "v"(v[i]), "v"(0x00010001u));
+    n += one;
   }
-  cnt = wave_sum(cnt);
-  if (lane == 0) offs_of(p)[t] = cnt;
+  return (uint32_t)n[0] + (uint32_t)n[1];
 }
 
-__device__ __forceinline__ uint32_t padded(uint32_t cnt) { return (cnt + kPad - 1) / kPad * kPad; }
-
-// single workgroup of 1024 threads
-__global__ __launch_bounds__(1024) void compress_scan_kernel(CompressParams p) {
-  __shared__ unsigned long long part[1024];
-  __shared__ unsigned long long nnz_total;
-  __shared__ uint32_t longest;
-  uint32_t* offs = offs_of(p);
-  const uint32_t tid = threadIdx.x;
-  const uint32_t per = (p.T + 1023) / 1024;
-  const uint32_t a = tid * per < p.T ? tid * per : p.T, b = (tid + 1) * per < p.T ? (tid + 1) * per : p.T;
-  if (tid == 0) {
-    nnz_total = 0;
-    longest = 0;
-  }
-  __syncthreads();
-  unsigned long long s = 0, nnz = 0;
-  uint32_t mx = 0;
-  for (uint32_t i = a; i < b; ++i) {
-    const uint32_t cnt = offs[i], w = padded(cnt);
-    nnz += cnt;
-    s += w;
-    mx = w > mx ? w : mx;
-  }
-  part[tid] = s;
-  atomicAdd(&nnz_total, nnz);  // 1024 LDS atomics in all
-  atomicMax(&longest, mx);
-  __syncthreads();
-  // Hillis-Steele inclusive scan over the 1024 partial sums
-  for (uint32_t d = 1; d < 1024; d <<= 1) {
-    unsigned long long v = tid >= d ? part[tid - d] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
-  }
-  unsigned long long run = tid ? part[tid - 1] : 0;
-  const unsigned long long total = part[1023];
-  for (uint32_t i = a; i < b; ++i) {
-    const uint32_t w = padded(offs[i]);
-    offs[i] = (uint32_t)run;
-    run += w;
-  }
-  for (uint32_t i = p.T + tid; i < p.n_off; i += 1024) offs[i] = (uint32_t)total;
-  if (tid == 0) {
-    uint32_t* h = (uint32_t*)p.out;
-    h[0] = kMagic;
-    h[1] = 1u;
-    h[2] = kTileM;
-    h[3] = kTileK;
-    h[4] = kPad;
-    h[5] = p.policy;
-    h[6] = longest;
-    h[7] = 0u;
-    unsigned long long* q = (unsigned long long*)(p.out + 32);
-    q[0] = p.M;
-    q[1] = p.K;
-    q[2] = nnz_total;
-    q[3] = total;
-  }
+// index of the first / last stored element of a cell that has one
+__device__ __forceinline__ uint32_t cell_first(const u32x4& v) {
+  uint32_t f = 0;
+#pragma unroll
+  for (int e = 7; e >= 0; --e)
+    if (half_of(v, e)) f = e;
+  return f;
+}
+__device__ __forceinline__ uint32_t cell_last(const u32x4& v) {
+  uint32_t f = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    if (half_of(v, e)) f = e;
+  return f;
 }
 
-__global__ __launch_bounds__(256) void compress_emit_kernel(CompressParams p) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= p.T) return;
-  const uint32_t band = t / p.KT, kt = t - band * p.KT;
-  const uint32_t* offs = offs_of(p);
-  uint32_t* dst = words_of(p) + offs[t];
-  const uint32_t run_words = offs[t + 1] - offs[t];
-  uint32_t pos = 0;
-  // location order: K chunk, then row, then position in the chunk
-  for (uint32_t c = 0; c < kTileK / 8; ++c) {
-    for (uint32_t half = 0; half < kTileM / 64; ++half) {
-      const uint32_t row = half * 64 + lane;
-      const u32x4 v = *(const u32x4*)(p.W + ((size_t)band * kTileM + row) * p.K + kt * kTileK + c * 8);
-      const uint32_t mask = nonzero_mask(v);
-      const uint32_t cnt = __popc(mask);
-      const uint32_t incl = wave_inclusive_scan(cnt, lane);
-      uint32_t slot = pos + incl - cnt;
-      const uint32_t loc0 = c * (kTileM * 8) + row * 8;
+// Version 2: what stands before a lane's first stored element of step s.
+struct Before {
+  uint32_t prev;     // location of the stored element before it, 0 if there is none
+  uint32_t bridges;  // entries needed to reach it
+};
+// `any`: the lane's cell has a stored element; `counter`: location of the last one of the steps before, moved on
+__device__ __forceinline__ Before step_bridges(const u32x4& v, int s, bool any, uint32_t& counter, int lane) {
+  const uint32_t loc0 = cell_location(s, lane), last = loc0 + cell_last(v), first = loc0 + cell_first(v);
+  const uint64_t have = __builtin_amdgcn_ballot_w64(any);
+  const uint64_t below = have & ((1ull << lane) - 1ull);
+  const int from = below ? 63 - __builtin_clzll(below) : 0;
+  const uint32_t of_lane = (uint32_t)__builtin_amdgcn_ds_bpermute(from * 4, (int)last);
+  Before b;
+  b.prev = below ? of_lane : counter;
+  b.bridges = any && first > b.prev ? (first - b.prev - 1u) / kReach2 : 0u;
+  if (have) counter = (uint32_t)__builtin_amdgcn_readlane((int)last, 63 - __builtin_clzll(have));
+  return b;
+}
+
+// Counts the tile; returns its stored elements.
+template <int FMT>
+__device__ __forceinline__ uint32_t count_tile(TileCells& t, int lane) {
+  uint32_t packed[3] = {0u, 0u, 0u}, nz = 0, counter = 0;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (mask >> e & 1u) {
-          const uint32_t bits = (e & 1) ? (v[e >> 1] >> 16) : (v[e >> 1] & 0xffffu);
-          dst[slot++] = (bits << 16) | (loc0 + e);
-        }
+  for (int s = 0; s < kCells; ++s) {
+    uint32_t n = cell_count(t.v[s]);
+    if constexpr (FMT == 2) {
+      nz += n;
+      n += step_bridges(t.v[s], s, n != 0, counter, lane).bridges;
+    }
+    packed[s / 3] |= n << (10 * (s % 3));
+  }
+  t.last = counter;
+  t.entries = 0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const uint32_t incl = wave_inclusive_scan(packed[i]);
+    t.before[i] = incl - packed[i];
+    t.total[i] = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    t.entries += (t.total[i] & 0x3ffu) + ((t.total[i] >> 10) & 0x3ffu) + (t.total[i] >> 20);
+  }
+  if constexpr (FMT == 2) return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(nz), 63);
+  else return t.entries;
+}
+
+// A wave's LDS operations execute in order; this keeps the compiler from moving them.
+__device__ __forceinline__ void lds_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Puts entries [base, base + kStageEntries) of the tile into the wave's stage.  ALL: they are all the tile has.
+template <int FMT, bool ALL>
+__device__ __forceinline__ void stage_entries(TileCells& t, unsigned char* stage, uint32_t base, int lane) {
+  // what the count found out element by element, and the locations, are found out again here: kept, they would be a
+  // hundred registers a tile
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int s = 0; s < kCells; ++s) asm volatile("" : "+v"(t.v[s]));
+  uint32_t* words = (uint32_t*)stage;                       // version 1
+  uint16_t* values = (uint16_t*)stage;                      // version 2
+  uint16_t* locs = (uint16_t*)(stage + 2 * kStageEntries);
+  auto put = [&](uint32_t slot, uint32_t bits, uint32_t loc) {
+    if (ALL || slot < kStageEntries) {
+      if constexpr (FMT == 2) {
+        values[slot] = (uint16_t)bits;
+        locs[slot] = (uint16_t)loc;
+      } else {
+        words[slot] = (bits << 16) | loc;
       }
-      pos += __shfl(incl, 63, 64);
+    }
+  };
+  uint32_t pos = 0u - base, counter = 0;
+#pragma unroll
+  for (int s = 0; s < kCells; ++s) {
+    uint32_t slot = pos + field10(t.before, s);
+    const uint32_t loc0 = cell_location(s, lane);
+    if constexpr (FMT == 2) {
+      const bool any = (t.v[s][0] | t.v[s][1] | t.v[s][2] | t.v[s][3]) != 0u;
+      Before b = step_bridges(t.v[s], s, any, counter, lane);
+      for (; b.bridges > 0; --b.bridges) {
+        b.prev += kReach2;
+        put(slot++, 0u, b.prev);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t bits = half_of(t.v[s], e);
+      if (bits) put(slot++, bits, loc0 + e);
+    }
+    pos += field10(t.total, s);
+  }
+  // padding: version 1 words of value +0 one past the tile, version 2 entries of value 0 at distance 1
+  const uint32_t slot = t.entries + (uint32_t)lane;
+  if (lane < (int)kPad && slot < (t.entries + kPad - 1) / kPad * kPad)
+    put(slot - base, 0u, FMT == 2 ? t.last + 1u + (uint32_t)lane : (uint32_t)kTileElems);
+}
+
+// Copies the staged part of the run to the blob; dst = where the words of entry `base` go.
+template <int FMT>
+__device__ __forceinline__ void flush_stage(const TileCells& t, const unsigned char* stage, uint32_t base, uint32_t* dst, int lane) {
+  const uint32_t left = t.entries - base, n = left < kStageEntries ? left : kStageEntries;
+  const uint32_t groups = (n + kPad - 1) / kPad;
+  for (uint32_t g = (uint32_t)lane; g < groups; g += 64) {
+    if constexpr (FMT == 2) {
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      const u32x2 v = *(const u32x2*)(stage + g * 8), l = *(const u32x2*)(stage + 2 * kStageEntries + g * 8);
+      const uint32_t l0 = l[0] & 0xffffu, l1 = l[0] >> 16, l2 = l[1] & 0xffffu, l3 = l[1] >> 16;
+      dst[g * 3] = v[0];
+      dst[g * 3 + 1] = v[1];
+      dst[g * 3 + 2] = l0 | (l1 - l0) << 12 | (l2 - l1) << 18 | (l3 - l2) << 24;
+    } else {
+      ((u32x4*)dst)[g] = ((const u32x4*)stage)[g];
     }
   }
-  // padding words: value +0, location one past the tile
-  if (pos + lane < run_words) dst[pos + lane] = (uint32_t)kTileElems;
+}
+
+// Words of all chunks before chunk q.  Run by one whole wave; q's own sum is published.  Each look takes the
+// states of 64 chunks, nearest first, and ends at the nearest one that knows its prefix already.
+__device__ __forceinline__ uint32_t look_back(const CompressParams& p, uint32_t q, int lane) {
+  constexpr uint32_t kLookLimit = 1u << 22;
+  uint32_t sum = 0, looks = 0;
+  for (uint32_t top = q; top > 0;) {
+    uint64_t st = kStatePrefix;  // before the first chunk: nothing
+    if ((uint32_t)lane < top)
+      st = __hip_atomic_load(state_of(p, top - 1u - (uint32_t)lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t prefix = __builtin_amdgcn_ballot_w64((st & kStatePrefix) != 0);
+    const uint64_t missing = __builtin_amdgcn_ballot_w64((st >> 62) == 0);
+    const int end = prefix ? __builtin_ctzll(prefix) : 63;  // last lane that counts
+    if (missing & (~0ull >> (63 - end))) {
+      // chunks are taken in order, so every chunk before this one is being worked on and the wait ends; bounded all the same
+      if (++looks == kLookLimit) {
+        if (lane == 0) __hip_atomic_store((uint32_t*)p.out + kHeaderGaveUp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return sum;
+      }
+      __builtin_amdgcn_s_sleep(1);
+      continue;
+    }
+    const uint32_t part = lane <= end ? (uint32_t)st : 0u;
+    sum += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(part), 63);
+    if (prefix) break;
+    top = top > 64u ? top - 64u : 0u;
+  }
+  return sum;
+}
+
+// Bound by instructions, not by memory yet: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 178 us, 3.2 TB/s, where a
+// copy reaches 4.7; 12288 x 12288 at 90 % in version 2 153 us.  The same work as count, scan and emit kernels that
+// each read W (or its counts) again: 85 + 98 + 269 us and 466 + 66 + 173 us; the whole call 491 -> 218 us and 744 ->
+// 187 us.  Sixteen tiles to a chunk keep the look-back and the ticket rare (one of each per 128 KB of W); eight
+// waves with two tiles each leave room for two workgroups on a CU, one loading while the other writes.
+template <int FMT>
+__global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(CompressParams p) {
+  __shared__ __align__(16) unsigned char stages[kChunkWaves][kTileBytes];
+  __shared__ uint32_t entries_of[kChunkTiles];
+  __shared__ uint32_t stored_of[kChunkWaves];
+  __shared__ uint32_t ticket, chunk_base;
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Chunks are numbered in the order in which workgroups start, not by workgroup id: whatever the order in which
+  // the chip starts them, a workgroup only waits for others that run already.
+  if (threadIdx.x == 0) ticket = atomicAdd((uint32_t*)p.out + kHeaderTicket, 1u);
+  __syncthreads();
+  const uint32_t q = ticket;
+  unsigned char* stage = stages[wave];
+
+  // Loads: lane j takes row 16 i + (j >> 2), K chunk j & 3 - a quad reads the 64 contiguous bytes of a row of the tile.
+  TileCells t[kTilesPerWave];
+  uint32_t tile[kTilesPerWave];
+#pragma unroll
+  for (int a = 0; a < kTilesPerWave; ++a) {
+    tile[a] = q * kChunkTiles + wave * kTilesPerWave + a;
+    const uint32_t ta = tile[a] < p.T ? tile[a] : 0u;
+    const uint32_t band = ta / p.KT, kt = ta - band * p.KT;
+    const uint16_t* src = p.W + ((size_t)band * kTileM + (lane >> 2)) * p.K + kt * kTileK + (lane & 3) * 8;
+#pragma unroll
+    for (int i = 0; i < kCells; ++i)
+      t[a].v[i] = tile[a] < p.T ? __builtin_nontemporal_load((const u32x4*)(src + (size_t)i * 16 * p.K)) : u32x4{0u, 0u, 0u, 0u};
+  }
+  // ... and through LDS into the order of the walk.  Slot of cell (row, K chunk c): 128 c + (row ^ 4 c); any 16
+  // neighbouring lanes touch 16 different 16 B bank groups, both ways.
+  uint32_t stored = 0;
+#pragma unroll
+  for (int a = 0; a < kTilesPerWave; ++a) {
+    const uint32_t c = lane & 3;
+#pragma unroll
+    for (int i = 0; i < kCells; ++i) *(u32x4*)(stage + (c * kTileM + ((16u * i + (lane >> 2)) ^ (4u * c))) * 16) = t[a].v[i];
+    lds_order();
+#pragma unroll
+    for (int s = 0; s < kCells; ++s)
+      t[a].v[s] = *(const u32x4*)(stage + ((s >> 1) * kTileM + ((uint32_t)(s & 1) * 64 + ((uint32_t)lane ^ (4u * (s >> 1))))) * 16);
+    lds_order();
+    stored += count_tile<FMT>(t[a], lane);
+    if (lane == 0) entries_of[wave * kTilesPerWave + a] = t[a].entries;
+  }
+  if (lane == 0) stored_of[wave] = stored;
+  __syncthreads();
+
+  // the chunk's sum goes out first, its place is looked up after the first tile has been compacted
+  uint32_t words = 0, chunk_words = 0, nz = 0;
+  if (wave == 0) {
+    const uint32_t mine = lane < kChunkTiles ? entries_of[lane] : 0u;
+    words = run_words<FMT>(mine);
+    chunk_words = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(words), 63);
+    nz = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(lane < kChunkWaves ? stored_of[lane] : 0u), 63);
+    if (lane == 0)
+      __hip_atomic_store(state_of(p, q), (q == 0 ? kStatePrefix : kStateSum) | (uint64_t)nz << 32 | chunk_words, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t next = (uint32_t)__shfl_down((int)mine, 1, 64);
+    if (lane < kChunkTiles && (lane & 1) == 0) offs_of(p)[(size_t)q * kChunkTiles + 2 + lane / 2] = mine | next << 16;
+  }
+  if (t[0].entries <= kStageEntries) stage_entries<FMT, true>(t[0], stage, 0, lane);
+  if (wave == 0) {
+    const uint32_t before = look_back(p, q, lane);
+    if (lane == 0) {
+      if (q != 0)
+        __hip_atomic_store(state_of(p, q), kStatePrefix | (uint64_t)nz << 32 | (uint64_t)(before + chunk_words), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      chunk_base = before;
+    }
+  }
+  __syncthreads();
+
+  uint32_t begin = chunk_base;
+  for (uint32_t j = 0; j < wave * kTilesPerWave; ++j) begin += run_words<FMT>(entries_of[j]);
+#pragma unroll
+  for (int a = 0; a < kTilesPerWave; ++a) {
+    const uint32_t n = t[a].entries, end = begin + run_words<FMT>(n);
+    uint32_t* dst = words_of(p) + begin;
+    const bool fits = (uint64_t)begin + (end - begin) <= p.capacity_words;  // (a buffer that turns out too small gets the tiles that fit)
+    if (n <= kStageEntries) {
+      if (a > 0) stage_entries<FMT, true>(t[a], stage, 0, lane);
+      lds_order();
+      if (fits) flush_stage<FMT>(t[a], stage, 0, dst, lane);
+    } else {
+      for (uint32_t base = 0; base < n; base += kStageEntries) {
+        stage_entries<FMT, false>(t[a], stage, base, lane);
+        lds_order();
+        if (fits) flush_stage<FMT>(t[a], stage, base, dst + run_words<FMT>(base), lane);
+        lds_order();
+      }
+    }
+    lds_order();
+    begin = end;
+  }
+}
+
+// A thread per chunk: its state -> its TileOffsets (nothing of another chunk's is read).
+template <int FMT>
+__global__ __launch_bounds__(256) void compress_finish_kernel(CompressParams p) {
+  const uint32_t q = blockIdx.x * 256 + threadIdx.x, chunks = (p.T + kChunkTiles - 1) / kChunkTiles;
+  uint32_t* h = (uint32_t*)p.out;
+  uint64_t stored = 0;
+  uint32_t longest = 0;
+  if (q < chunks) {
+    u32x4* cell = (u32x4*)(offs_of(p) + (size_t)q * kChunkTiles);
+    u32x4 in[3], o[4];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) in[i] = cell[i];
+    const uint64_t st = (uint64_t)in[0][1] << 32 | in[0][0];
+    stored = (st >> 32) & 0x1ffffu;
+    uint32_t w[kChunkTiles], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kChunkTiles; ++j) {
+      const uint32_t pair = in[(2 + j / 2) / 4][(2 + j / 2) % 4];
+      w[j] = run_words<FMT>((j & 1) ? pair >> 16 : pair & 0xffffu);
+      sum += w[j];
+      longest = w[j] > longest ? w[j] : longest;
+    }
+    uint32_t run = (uint32_t)st - sum;
+#pragma unroll
+    for (int j = 0; j < kChunkTiles; ++j) {
+      o[j / 4][j % 4] = run;  // the tiles past the end of a last, partly empty chunk have no words: their entries are the total
+      run += w[j];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cell[i] = o[i];
+    if (q + 1 == chunks) {
+      for (uint32_t i = chunks * kChunkTiles; i < p.n_off; ++i) offs_of(p)[i] = run;
+      h[0] = FMT == 2 ? kMagic2 : kMagic;
+      h[1] = FMT;
+      h[2] = kTileM;
+      h[3] = kTileK;
+      h[4] = kPad;
+      h[5] = p.policy;
+      h[kHeaderTicket] = 0u;
+      unsigned long long* d = (unsigned long long*)(p.out + 32);
+      d[0] = p.M;
+      d[1] = p.K;
+      h[kHeaderTotalWords] = run;
+    }
+  }
+  stored = wave_sum64(stored);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    const uint32_t v = (uint32_t)__shfl_xor((int)longest, d, 64);
+    longest = v > longest ? v : longest;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd((unsigned long long*)(p.out + 48), (unsigned long long)stored);
+    atomicMax(h + kHeaderMaxTileWords, longest);
+  }
 }
 
 __global__ void fill_zero_kernel(u32x4* p, size_t n16) {
@@ -177,182 +444,19 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- format version 2
-//
-// Three bytes per entry (the index bytes that the footnote under the paper's Eq. 2 leaves out of
-// its model are what version 1 pays in full): a tile's entries, in ascending location, go in
-// groups of four that take three words - two of values, one with the first entry's location in
-// 12 bits and the other three as 6-bit distances from the entry before.  An entry is a stored
-// element, a bridge (value 0) every 63 locations where the next stored element lies more than 63
-// behind the entry before it, or padding (value 0, distance 1) up to a multiple of four.  Same
-// three kernels: count (entries per tile, bridges included; stored elements summed into the
-// header), scan, emit.
-
-constexpr uint32_t kMagic2 = 0x32534C46u;  // "FLS2"
-constexpr uint32_t kGroup = 4;              // entries per group of three words
-
-// inclusive running maximum over the 64 lanes
-__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t up = __shfl_up(v, d, 64);
-    if (lane >= d) v = up > v ? up : v;
-  }
-  return v;
+template <int FMT>
+static hipError_t launch_compress_fmt(const CompressParams& p, hipStream_t stream) {
+  const uint32_t chunks = (p.T + kChunkTiles - 1) / kChunkTiles;
+  // states and header start at zero
+  hipError_t e = launch_fill_zero(p.out, 64 + 4 * (size_t)p.n_off, stream);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((compress_emit_kernel<FMT>), dim3(chunks), dim3(kChunkWaves * 64), 0, stream, p);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL((compress_finish_kernel<FMT>), dim3((chunks + 255) / 256), dim3(256), 0, stream, p);
+  return hipGetLastError();
 }
 
-// One wave walks tile (band, kt) in location order, as compress_emit_kernel does: per step a lane
-// holds the 8 halves of one (row, K-chunk) cell, i.e. 8 consecutive locations.  Returns the number
-// of entries before padding; *stored = stored elements seen by this lane.  With EMIT the entries
-// (and the padding) are put together in `stage`, the tile's words in LDS, zeroed by the caller:
-// entry e is entry e & 3 of group e >> 2, whose three words different lanes fill, so values and
-// location fields are OR-ed in.
-constexpr uint32_t kReach2 = 63;  // largest distance a 6-bit field holds: a bridge entry every 63 empty locations
-template <bool EMIT>
-__device__ __forceinline__ uint32_t walk_tile_v2(const CompressParams& p, uint32_t band, uint32_t kt, int lane,
-                                                 uint32_t* stage, uint32_t* stored) {
-  auto put = [&](uint32_t e, uint32_t bits, uint32_t loc, uint32_t dist) {
-    const uint32_t g = e >> 2, k = e & 3u;
-    atomicOr(&stage[g * 3u + (k >> 1)], (k & 1u) ? bits << 16 : bits);
-    atomicOr(&stage[g * 3u + 2u], k == 0 ? loc : dist << (6u + 6u * k));  // the group's first location in full, then distances
-  };
-  uint32_t pos = 0;      // entries so far
-  uint32_t counter = 0;  // the location of the last entry of the steps done so far (0 before the first)
-  uint32_t nz = 0;
-  for (uint32_t c = 0; c < kTileK / 8; ++c) {
-    for (uint32_t half = 0; half < kTileM / 64; ++half) {
-      const uint32_t row = half * 64 + lane;
-      const u32x4 v = *(const u32x4*)(p.W + ((size_t)band * kTileM + row) * p.K + kt * kTileK + c * 8);
-      const uint32_t mask = nonzero_mask(v);
-      const uint32_t cnt = __popc(mask);
-      const uint32_t loc0 = c * (kTileM * 8) + row * 8;
-      // the entry this lane's first element follows: the last stored location in the lanes
-      // before it (0 stands for "none", which is also what the first element of a tile follows)
-      const uint32_t last = cnt ? loc0 + (31u - (uint32_t)__clz((int)mask)) : 0u;
-      const uint32_t run_max = wave_inclusive_max(last, lane);
-      uint32_t prev = __shfl_up(run_max, 1, 64);
-      if (lane == 0) prev = 0;
-      prev = prev > counter ? prev : counter;
-      const uint32_t first = loc0 + (uint32_t)__builtin_ctz(mask | 0x100u);
-      const uint32_t gap = first - prev;
-      const uint32_t bridges = (cnt && gap > 0u) ? (gap - 1u) / kReach2 : 0u;
-      const uint32_t entries = cnt + bridges;
-      const uint32_t incl = wave_inclusive_scan(entries, lane);
-      if (EMIT) {
-        uint32_t slot = pos + incl - entries, cur = prev;
-        for (uint32_t b = 0; b < bridges; ++b) {
-          cur += kReach2;
-          put(slot++, 0u, cur, kReach2);
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (mask >> e & 1u) {
-            const uint32_t bits = (e & 1) ? (v[e >> 1] >> 16) : (v[e >> 1] & 0xffffu);
-            put(slot++, bits, loc0 + e, loc0 + e - cur);
-            cur = loc0 + e;
-          }
-        }
-      }
-      pos += __shfl(incl, 63, 64);
-      const uint32_t step_max = __shfl(run_max, 63, 64);
-      counter = step_max > counter ? step_max : counter;
-      nz += cnt;
-    }
-  }
-  if (EMIT) {
-    // padding never starts a group, so only its distance (1) goes in
-    const uint32_t padded_entries = (pos + kGroup - 1) / kGroup * kGroup;
-    if (pos + lane < padded_entries) put(pos + lane, 0u, 0u, 1u);
-  }
-  *stored = nz;
-  return pos;
-}
-
-__global__ __launch_bounds__(256) void compress2_count_kernel(CompressParams p) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= p.T) return;
-  uint32_t nz;
-  const uint32_t entries = walk_tile_v2<false>(p, t / p.KT, t % p.KT, lane, nullptr, &nz);
-  nz = wave_sum(nz);
-  if (lane == 0) {
-    offs_of(p)[t] = entries;
-    atomicAdd((unsigned long long*)(p.out + 48), (unsigned long long)nz);  // the header's nnz (cleared before the launch)
-  }
-}
-
-__device__ __forceinline__ uint32_t words_v2(uint32_t entries) { return (entries + kGroup - 1) / kGroup * 3u; }
-
-// single workgroup of 1024 threads: entries per tile -> word offsets, guard entries, header
-__global__ __launch_bounds__(1024) void compress2_scan_kernel(CompressParams p) {
-  __shared__ unsigned long long part[1024];
-  __shared__ uint32_t longest;
-  uint32_t* offs = offs_of(p);
-  const uint32_t tid = threadIdx.x;
-  const uint32_t per = (p.T + 1023) / 1024;
-  const uint32_t a = tid * per < p.T ? tid * per : p.T, b = (tid + 1) * per < p.T ? (tid + 1) * per : p.T;
-  if (tid == 0) longest = 0;
-  __syncthreads();
-  unsigned long long s = 0;
-  uint32_t mx = 0;
-  for (uint32_t i = a; i < b; ++i) {
-    const uint32_t w = words_v2(offs[i]);
-    s += w;
-    mx = w > mx ? w : mx;
-  }
-  part[tid] = s;
-  atomicMax(&longest, mx);
-  __syncthreads();
-  for (uint32_t d = 1; d < 1024; d <<= 1) {
-    unsigned long long v = tid >= d ? part[tid - d] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
-  }
-  unsigned long long run = tid ? part[tid - 1] : 0;
-  const unsigned long long total = part[1023];
-  for (uint32_t i = a; i < b; ++i) {
-    const uint32_t w = words_v2(offs[i]);
-    offs[i] = (uint32_t)run;
-    run += w;
-  }
-  for (uint32_t i = p.T + tid; i < p.n_off; i += 1024) offs[i] = (uint32_t)total;
-  if (tid == 0) {
-    uint32_t* h = (uint32_t*)p.out;
-    h[0] = kMagic2;
-    h[1] = 2u;
-    h[2] = kTileM;
-    h[3] = kTileK;
-    h[4] = kGroup;
-    h[5] = 0u;
-    h[6] = longest;
-    h[7] = 0u;
-    unsigned long long* q = (unsigned long long*)(p.out + 32);
-    q[0] = p.M;
-    q[1] = p.K;  // q[2], the stored elements, was summed by the count kernel
-    q[3] = total;
-  }
-}
-
-// A wave per tile: the tile's words are put together in LDS (at most 1024 groups of 12 B) and copied out.
-__global__ __launch_bounds__(256) void compress2_emit_kernel(CompressParams p) {
-  __shared__ uint32_t stages[4][kTileM * kTileK / kGroup * 3];
-  const int lane = threadIdx.x & 63;
-  const uint32_t wave = threadIdx.x >> 6;
-  const uint32_t t = blockIdx.x * 4 + wave;
-  if (t >= p.T) return;
-  uint32_t* stage = stages[wave];
-  const uint32_t begin = offs_of(p)[t], nwords = offs_of(p)[t + 1] - begin;
-  for (uint32_t i = lane; i < nwords; i += 64) stage[i] = 0u;
-  __builtin_amdgcn_wave_barrier();  // (LDS executes a wave's operations in order; this keeps the compiler from moving them)
-  uint32_t nz;
-  walk_tile_v2<true>(p, t / p.KT, t % p.KT, lane, stage, &nz);
-  __builtin_amdgcn_wave_barrier();
-  uint32_t* dst = words_of(p) + begin;
-  for (uint32_t i = lane; i < nwords; i += 64) dst[i] = stage[i];
-}
-
-static CompressParams make_params(const CompressLaunch& a) {
+hipError_t launch_compress(const CompressLaunch& a, hipStream_t stream) {
   CompressParams p;
   p.W = a.W;
   p.out = a.out;
@@ -362,26 +466,8 @@ static CompressParams make_params(const CompressLaunch& a) {
   p.T = (a.M / kTileM) * p.KT;
   p.n_off = (p.T + 4 + 15) / 16 * 16;
   p.policy = a.policy;
-  return p;
-}
-
-hipError_t launch_compress_index(const CompressLaunch& a, hipStream_t stream) {
-  const CompressParams p = make_params(a);
-  hipError_t e = launch_fill_zero(a.out, 64, stream);
-  if (e != hipSuccess) return e;
-  if (a.version == 2) hipLaunchKernelGGL(compress2_count_kernel, dim3((p.T + 3) / 4), dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL(compress_count_kernel, dim3((p.T + 3) / 4), dim3(256), 0, stream, p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (a.version == 2) hipLaunchKernelGGL(compress2_scan_kernel, dim3(1), dim3(1024), 0, stream, p);
-  else hipLaunchKernelGGL(compress_scan_kernel, dim3(1), dim3(1024), 0, stream, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_compress_emit(const CompressLaunch& a, hipStream_t stream) {
-  const CompressParams p = make_params(a);
-  if (a.version == 2) hipLaunchKernelGGL(compress2_emit_kernel, dim3((p.T + 3) / 4), dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL(compress_emit_kernel, dim3((p.T + 3) / 4), dim3(256), 0, stream, p);
-  return hipGetLastError();
+  p.capacity_words = (a.capacity - (64 + 4 * (size_t)p.n_off)) / 4;
+  return a.version == 2 ? launch_compress_fmt<2>(p, stream) : launch_compress_fmt<1>(p, stream);
 }
 
 }  // namespace fls

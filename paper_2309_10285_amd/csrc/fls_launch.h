@@ -36,6 +36,7 @@ struct DenseLaunch {
 struct CompressLaunch {
   const uint16_t* W;
   unsigned char* out;  // blob
+  size_t capacity;     // bytes of `out`, at least header and TileOffsets: no word goes past it
   uint32_t M, K;
   uint32_t policy;
   uint32_t version;  // 1: 32-bit words (value, location); 2: groups of four entries in three words, three bytes per entry
@@ -163,10 +164,8 @@ hipError_t launch_spmm_wide(const SpmmLaunch& a, uint32_t n0, uint32_t groups, h
 // layout32: the partial results are in the 32x32 accumulator layout (sparse pass), else 16x16 (dense pass)
 hipError_t launch_wide_reduce(const WideParams& p, bool layout32, hipStream_t stream);
 hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream);
-// phase 1: per-tile counts, prefix sums, header (everything but the words)
-hipError_t launch_compress_index(const CompressLaunch& a, hipStream_t stream);
-// phase 2: the words
-hipError_t launch_compress_emit(const CompressLaunch& a, hipStream_t stream);
+// header, TileOffsets and every tile whose words fit the capacity
+hipError_t launch_compress(const CompressLaunch& a, hipStream_t stream);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 
 }  // namespace fls

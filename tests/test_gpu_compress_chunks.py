@@ -1,0 +1,61 @@
+"""The compressor works on chunks of 16 tiles and stages 2048 entries of a tile at a time: bit for bit against the oracle
+around both edges, in both formats, and within a buffer that is too small."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fls():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2309_10285_amd as f
+
+    f.lib()
+    return f
+
+
+def _dev(bits):
+    import torch
+
+    return torch.from_numpy(bits.view(np.float16)).cuda()
+
+
+def _weights(bands, kt, stored, seed):
+    """Tile j (band-major) holds exactly stored[j % len(stored)] elements at random places."""
+    g = np.random.Generator(np.random.Philox(seed))
+    W = np.zeros((bands, kt, 4096), dtype=np.uint16)
+    for j in range(bands * kt):
+        n = stored[j % len(stored)]
+        W[j // kt, j % kt, g.permutation(4096)[:n]] = g.integers(1, 65536, size=n, dtype=np.uint32).astype(np.uint16)
+    return np.ascontiguousarray(W.reshape(bands, kt, 128, 32).transpose(0, 2, 1, 3).reshape(bands * 128, kt * 32))
+
+
+@pytest.mark.parametrize("version", [1, 2])
+@pytest.mark.parametrize("bands,kt", [(1, 1), (1, 15), (2, 8), (1, 17), (3, 5), (67, 17), (5, 1025)])
+def test_chunk_edges(fls, oracle_mod, version, bands, kt):
+    W = _weights(bands, kt, [800, 0, 1, 2047, 2048, 2049, 4096, 5, 64], 11)
+    blob, st = (fls.fls_compress_v2 if version == 2 else fls.fls_compress)(_dev(W))
+    ref = (oracle_mod.ref_compress_v2 if version == 2 else oracle_mod.ref_compress)(W)
+    assert np.array_equal(blob.cpu().numpy(), ref)
+    assert st["nnz"] == int(np.count_nonzero(W))
+
+
+@pytest.mark.parametrize("version", [1, 2])
+def test_too_small_buffer_is_not_overrun(fls, version):
+    import torch
+
+    compress = fls.fls_compress_v2 if version == 2 else fls.fls_compress
+    W = _dev(_weights(3, 17, [700, 3000], 12))
+    size = compress(W)[1]["bytes_total"]
+    index = 64 + 4 * ((3 * 17 + 4 + 15) // 16 * 16)
+    for room in (size - 16, size // 2 // 16 * 16, index):
+        buf = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        with pytest.raises(fls.FlsError) as e:
+            compress(W, buf[:room])
+        assert e.value.code == fls.ECAPACITY
+        assert bool((buf[room:] == 0xA5).all())
+    assert compress(W, torch.empty(size, dtype=torch.uint8, device="cuda"))[1]["bytes_total"] == size
