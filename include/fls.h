@@ -35,7 +35,7 @@ extern "C" {
 #define FLS_TILE_M 128u /* rows of a Tiled-CSL tile                        (Sec. 4.3.1) */
 #define FLS_TILE_K 32u  /* columns (K extent) of a Tiled-CSL tile */
 #define FLS_PAD_WORDS 4u /* a tile's run is padded to a multiple of this many words */
-#define FLS_MAX_N 8192 /* the skinny case is N <= 256; wider N runs as passes of 64 columns (Sec. 6.2, non-skinny shapes) */
+#define FLS_MAX_N 8192 /* the skinny case is N <= 256; wider N runs in blocks of 64 - 256 columns (Sec. 6.2, non-skinny shapes) */
 #define FLS_FORMAT_VERSION 1u
 #define FLS_FORMAT_VERSION_2 2u /* four entries share a word of locations, 3 bytes per entry: fls_compress_v2 */
 #define FLS_HEADER_BYTES 64u
@@ -162,7 +162,7 @@ int fls_check_workspace(fls_stream_t stream);
 
 /*
  * C = W . X with W given as a Tiled-CSL blob (the SpMM of Alg. 1): streams the blob from HBM
- * (once per 64 columns for N > 32 - N = 8192 is 128 passes over W - else once), rebuilds each tile densely in LDS, multiplies
+ * (once per 64 columns for N > 32, per 128 or 256 in the block pass that most calls of more than 64 take, else once), rebuilds each tile densely in LDS, multiplies
  * with MFMA, fp32 accumulation.  Partial sums of different workgroups are added in a fixed order;
  * inside a workgroup the waves' sums are added in the order they finish unless the workgroup's
  * tiles lie in one row band (then in wave order), so two runs may differ in the last bit of an
@@ -181,9 +181,9 @@ int fls_check_workspace(fls_stream_t stream);
  * Only the 64-byte header is validated; TileOffsets and NonZeros are the caller's responsibility (a blob
  * from fls_compress is right by construction).  As a guard for blobs that were stored and read back, the
  * passes of up to 32 columns take no offset to lie beyond the header's word count, so a truncated or
- * damaged TileOffsets section gives wrong results, not loads outside NonZeros; the 64-column pass
+ * damaged TileOffsets section gives wrong results, not loads outside NonZeros; the block pass (N > 64) and the 64-column pass
  * (N > 32, and calls of 17 - 32 columns on long bands of sparse tiles, where sharing X between
- * bands makes it the faster one) trusts TileOffsets.
+ * bands makes it the faster one) trust TileOffsets.
  * Errors: FLS_EINVAL, FLS_EALIGN, FLS_EFORMAT, FLS_EWORKSPACE, FLS_EHIP.
  */
 int fls_spmm(const void* Wc_dev, const void* X_dev, void* C_dev, int64_t M, int64_t K, int64_t N,

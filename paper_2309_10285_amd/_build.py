@@ -5,11 +5,11 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libfls.so")
-SOURCES = ["fls_api.hip", "fls_spmm.hip", "fls_spmm_wide.hip", "fls_dense.hip", "fls_compress.hip"]
+SOURCES = ["fls_api.hip", "fls_spmm.hip", "fls_spmm_wide.hip", "fls_spmm_block.hip", "fls_dense.hip", "fls_compress.hip"]
 # measurement code (a plain streaming read: bench.py's empirical ceiling), a library of its own, not part of the C ABI
 PROBE_SOURCE = "fls_stream_probe.hip"
 PROBE_LIB = os.path.join(_HERE, "libfls_probe.so")
-HEADERS = ["fls_device.h", "fls_launch.h", "fls_tile.h", os.path.join("..", "..", "include", "fls.h")]
+HEADERS = ["fls_device.h", "fls_launch.h", "fls_mfma32.h", "fls_tile.h", os.path.join("..", "..", "include", "fls.h")]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-munsafe-fp-atomics",

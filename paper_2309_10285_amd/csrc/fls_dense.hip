@@ -168,13 +168,8 @@ __global__ __launch_bounds__(256) void dense_wide_kernel(WideParams p) {
   constexpr int NB = 4;
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // (group of four bands, K slice) pair and group of 64 columns of this workgroup: as in the sparse
-  // pass, the G workgroups that stream the same rows of W get ids 8 apart, which puts them on one
-  // XCD one after the other, so that all but the first find W in its L2
-  const uint32_t pairs = ((p.bands + 3u) / 4u) * p.S;
-  const uint32_t cg = (blockIdx.x >> 3) % p.G, pair = ((blockIdx.x >> 3) / p.G) * 8u + (blockIdx.x & 7u);
-  if (pair >= pairs) return;
-  const uint32_t group = pair / p.S, slice = pair - group * p.S;
+  uint32_t group, slice, cg;
+  if (!wide_unit((p.bands + 3u) / 4u, p.S, p.G, p.whole, group, slice, cg)) return;
   const uint32_t n0 = p.n0 + cg * 64u;
   const uint32_t band = group * 4 + wave;
   if (band >= p.bands) return;
@@ -292,7 +287,8 @@ static hipError_t launch_dense_wide(const DenseLaunch& a, uint32_t n0, uint32_t 
   p.bands = a.M / kTileM;
   p.S = wide_slices(p.bands, col_groups, p.KT, a.num_cus);
   const uint32_t groups = (p.bands + 3u) / 4u;
-  const uint32_t grid = (groups * p.S + 7u) / 8u * 8u * col_groups;
+  p.whole = whole_pairs(groups * p.S, col_groups, a.num_cus);
+  const uint32_t grid = wide_grid(groups * p.S, col_groups, p.whole);
   hipLaunchKernelGGL((dense_wide_kernel<kDenseWideRing>), dim3(grid), dim3(256), 0, stream, p);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && p.S > 1) e = launch_wide_reduce(p, false, stream);

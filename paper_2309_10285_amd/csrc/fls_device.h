@@ -55,6 +55,33 @@ struct OutParams {
   uint32_t T;       // tiles in total
 };
 
+// The unit of work of this workgroup when the grid is units rounded up to a multiple of eight.  Consecutive workgroup
+// ids go to the chip's eight XCDs in turn, so id 8 i + x takes the i-th unit of the x-th eighth: neighbouring units
+// run on one XCD, one after the other, and find in its L2 what they share.
+__device__ __forceinline__ bool xcd_unit(uint32_t units, uint32_t& unit) {
+  const uint32_t x = blockIdx.x & 7u;
+  unit = x * units / 8u + (blockIdx.x >> 3);
+  return unit < (x + 1u) * units / 8u;
+}
+
+// The 64-column passes: group of four bands, K slice and group of 64 columns of this workgroup.  The G workgroups that
+// stream the same words run on one XCD, one after the other, and all but the first find them in its L2.
+// `whole` (see whole_pairs of the launchers): (quad, slice) pair 8 i + x goes to XCD x with all its column groups.
+// Otherwise every XCD takes an eighth of all units, slice by slice.
+__device__ __forceinline__ bool wide_unit(uint32_t quads, uint32_t S, uint32_t G, bool whole, uint32_t& quad, uint32_t& slice, uint32_t& cg) {
+  const uint32_t pairs = quads * S, x = blockIdx.x & 7u;
+  uint32_t unit;
+  const bool mine = xcd_unit(pairs * G, unit);
+  if (whole) unit = blockIdx.x >> 3;
+  uint32_t pair = unit / G;
+  cg = unit - pair * G;
+  if (whole) pair = pair * 8u + x;
+  const uint32_t by = whole ? S : quads, major = pair / by, minor = pair - major * by;
+  quad = whole ? major : minor;
+  slice = whole ? minor : major;
+  return whole ? pair < pairs : mine;
+}
+
 // First tile of workgroup q's share when T tiles are cut over P workgroups.
 __device__ __forceinline__ uint32_t share_begin(uint32_t q, uint32_t T, uint32_t P) {
   return (uint32_t)((uint64_t)q * T / P);

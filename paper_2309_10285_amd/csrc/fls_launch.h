@@ -73,6 +73,44 @@ inline uint32_t wide_quad_slices(uint32_t bands, uint32_t col_groups, uint32_t K
   const uint32_t by_length = KT / (2u * body) > 0 ? KT / (2u * body) : 1u;
   return S < by_length ? S : by_length;
 }
+// How the 64-column passes spread their (group of four bands, K slice) pairs over the eight XCDs: whole pairs, in turn,
+// unless that leaves an XCD so many more workgroups than others that it takes a round more than an even cut of
+// all units.  7168 x 28672 at 80 %, N = 384: three slices, 42 pairs of six column groups, 36 workgroups on two XCDs of 32
+// CUs: 316 us, evenly cut 180; 12672 x 7840 at 82 %, N = 1085: 377 / 266; 5504 x 2752 at 64 %, N = 2735: 217 / 150.  Where both
+// take as many rounds whole pairs are up to 2 % faster (12288 x 12288 at 80 %, N = 128: 55.2 / 56.4 us; 27648 x 9216 at 70 %,
+// N = 32: 58.1 / 59.2).
+inline bool whole_pairs(uint32_t pairs, uint32_t G, int cus) {
+  const uint64_t per_xcd = cus >= 8 ? (uint64_t)cus / 8u : 1u;
+  const uint64_t whole = (uint64_t)((pairs + 7u) / 8u) * G, even = ((uint64_t)pairs * G + 7u) / 8u;
+  return (whole + per_xcd - 1u) / per_xcd == (even + per_xcd - 1u) / per_xcd;
+}
+// Workgroups of such a launch.
+inline uint32_t wide_grid(uint32_t pairs, uint32_t G, bool whole) {
+  return whole ? (pairs + 7u) / 8u * 8u * G : (pairs * G + 7u) / 8u * 8u;
+}
+// The block pass: a workgroup takes 4 / share row bands x 128 * share columns x a K slice of whole bodies of three tiles.
+inline uint32_t block_band_groups(uint32_t bands, uint32_t share) { return (bands * share + 3u) / 4u; }
+inline uint32_t block_col_groups(uint32_t cols, uint32_t share) { return (cols + 128u * share - 1u) / (128u * share); }
+// Slices per (group of bands, column group): as many as fill the CUs, none shorter than twelve tiles.  A workgroup leaves
+// eight partial results of 128 x 64, and 4 * kMaxWorkgroups of them have room.
+inline uint32_t block_slices(uint32_t units, uint32_t KT, int cus) {
+  const uint32_t most = cus < (int)(kMaxWorkgroups / 2) ? (uint32_t)cus : kMaxWorkgroups / 2;
+  const uint32_t S = units < most ? most / units : 1u, by_length = KT / 12u > 0 ? KT / 12u : 1u;
+  return S < by_length ? S : by_length;
+}
+// Which pass a call of more than 64 columns takes: 0 the 64-column pass, else the block pass's share.
+// The passes differ in three ways that pull apart: what a tile step costs (extraction and fragment reads are
+// shared by 64, 128 or 256 columns), how evenly their units fill the CUs (a ragged last round, columns that only pad), and
+// how many partial sums they leave when K is sliced (a CU of the block pass holds twice as many).  So the rule is an
+// estimate of each, in us, with measured constants: a step of one workgroup takes 0.30 + 0.071 R us (64
+// columns x 4 bands), 0.72 + 0.036 R (128 x 4) and 0.70 + 0.026 R (256 x 2) for R staged rounds with the whole chip at
+// work, and less where part of it idles, since the matrix cores' clock is set by power; partial sums are written and read back at
+// 5.5 TB/s; the block pass clears and stores twice as much, 1.5 us.  On 48 products of 1024 x 1760 ... 32000 x 7584 and 7168 x
+// 28672 at 60 - 90 %, both formats, N = 80 ... 4096, the pass it picks is on average 2 % slower than the best of the three.  Some of what was measured (us, 64-column / share 1 / share 2):
+// 12288 x 12288 at 80 %, N = 128 60 / 59 / 70, 256 111 / 88 / 83, 384 190 / 122 / 139, 1000 379 / 280 / 254, 4096 1234 /
+// 942 / 872; 7168 x 28672 at 80 %, N = 384 180 / 149 / 174; 28672 x 7168 at 90 %, N = 256 94 / 108 / 104.
+uint32_t spmm_pass_share(uint32_t max_tile_words, uint32_t round_words, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus);
+constexpr uint32_t kBlockRounds1 = 6, kBlockRounds2 = 10;  // rounds of a tile that the variants with share 1 / 2 stage
 // fp32 values of the split-K partial sums: [workgroup][column blocks][128 x 16] for the passes of
 // up to 32 columns, [band][slice][4][128 x 16] for the 64-column pass
 inline size_t parts_floats(uint32_t N) {
@@ -151,6 +189,7 @@ struct WideParams {
   _Float16* C;
   float* parts;           // [band][slice][column block][row block][lane] float4, used when S > 1
   uint32_t M, K, N, n0, KT, bands, S;
+  bool whole;  // whole_pairs: how workgroups spread over the XCDs (64-column passes)
   uint32_t G;  // groups of 64 columns in the launch, from column n0 on (sparse pass; 1 in the dense pass)
   uint32_t cb; // 32-column blocks of a group that are multiplied and hold sums (sparse pass: 2, or 1 for a call of at most 32 columns)
 };
@@ -160,6 +199,8 @@ hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream);
 // `groups` groups of 64 columns of the sparse 64-column pass from column n0 on, in one launch
 hipError_t launch_xpack(const _Float16* X, _Float16* xpack, uint32_t K, uint32_t N, hipStream_t stream);
 hipError_t launch_spmm_wide(const SpmmLaunch& a, uint32_t n0, uint32_t groups, hipStream_t stream);
+// all columns from n0 on with the block pass
+hipError_t launch_spmm_block(const SpmmLaunch& a, uint32_t n0, uint32_t share, hipStream_t stream);
 // C = sum over the S slices of parts, in slice order (the second kernel of a 64-column pass with S > 1);
 // layout32: the partial results are in the 32x32 accumulator layout (sparse pass), else 16x16 (dense pass)
 hipError_t launch_wide_reduce(const WideParams& p, bool layout32, hipStream_t stream);

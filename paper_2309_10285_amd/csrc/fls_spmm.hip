@@ -16,7 +16,7 @@
 //              zeros where their words went, dense ones by clearing all 8 KB
 // Split-K: the tile sequence (band-major) is cut evenly over all waves of the grid; partial
 // bands are summed in LDS inside a workgroup and through fp32 slots in HBM between workgroups.
-// More than 32 columns: fls_spmm_wide.hip.
+// More than 32 columns: fls_spmm_wide.hip and, from 65 on, fls_spmm_block.hip.
 #include <atomic>
 #include <type_traits>
 
@@ -443,6 +443,9 @@ hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream) {
   // rounds no longer fit its registers): a matrix with denser tiles - less than 40 % sparse
   // somewhere - takes 32-column passes throughout.
   const bool wide_ok = a.max_tile_words <= 10 * round_words;
+  // ... and beyond 64 columns it or the block pass takes all columns of the call, whichever the estimate prefers
+  const uint32_t share =
+      wide_ok && a.N > kSpmmGroupCols ? spmm_pass_share(a.max_tile_words, round_words, a.version, a.M / kTileM, a.K / kTileK, a.N, a.num_cus) : 0u;
   for (uint32_t n0 = 0; n0 < a.N;) {
     p.out.n0 = n0;
     const uint32_t left = a.N - n0;
@@ -458,6 +461,9 @@ hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream) {
       p.X = a.X;
       e = v2 ? launch_r<2, 8, 2>(R, p, grid, stream) : launch_r<2, 8, 1>(R, p, grid, stream);
       n0 += 32;
+    } else if (share > 0) {
+      e = launch_spmm_block(a, n0, share, stream);
+      n0 = a.N;
     } else {
       // All the groups of 64 columns in one launch, a last one that is partly empty included: the workgroups of a
       // further group find the words in their XCD's L2, where a narrower pass of its own for the rest would stream

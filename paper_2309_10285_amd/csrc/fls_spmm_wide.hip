@@ -27,6 +27,7 @@
 
 #include "fls_device.h"
 #include "fls_launch.h"
+#include "fls_mfma32.h"
 #include "fls_tile.h"
 
 // Latency-breakdown builds (see fls_spmm.hip): 2 no MFMA, 4 no extract, 8 no re-zeroing, 16 no LDS
@@ -67,59 +68,6 @@ __global__ __launch_bounds__(256) void xpack_kernel(const _Float16* X, _Float16*
   }
 }
 
-// Compile-time loop: f(integral_constant<int, I>) for I in [B, E).
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-// acc += a . b with the accumulator kept where it is (sixteen AGPRs): as an asm statement, so that
-// the instruction keeps its place between the memory operations around it.
-//
-// The 64-column pass multiplies with v_mfma_f32_32x32x16_f16 rather than 16x16x32: half as many
-// instructions for the same work, each leaving eight issue slots in its shadow.  Operand layouts
-// of the 32x32x16 shape, lane l = 32 h + c:
-//   A: row c of the 32-row block, the 8 k of chunk h of the 16-k step;  B: column c, the same 8 k;
-//   C/D: column c, rows 8 q + 4 h + (0..3) in registers 4 q .. 4 q + 3, q = 0..3.
-// A and B hold the same thing in the same lanes, so either operand can be the W block.  The pass
-// computes the transposed product, X block (A) times W block (B): the chip's clock under this
-// kernel is set by power, the matrix cores draw less when the operand that is mostly zeros is B,
-// and the call is 3 % faster for it (measured; with X all zeros instead of random values the same
-// instruction stream runs 15 - 18 % faster still, with W's values all equal 2 %).  An accumulator block
-// is therefore 32 columns of X (its rows) by 32 rows of W (its columns).
-typedef float float16v __attribute__((ext_vector_type(16)));
-__device__ __forceinline__ void mfma_in_place(float16v& acc, const half8& a, const half8& b) {
-  asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-constexpr int kRowBlocks32 = kTileM / 32;  // 32-row blocks of a tile
-constexpr int kColBlocks32 = 2;            // 32-column blocks of a group of 64 columns
-constexpr int kSteps16 = kTileK / 16;      // 16-k steps of a tile
-
-// Converts a wave's 128 x 64 accumulators (32x32 layout, transposed: see above) to fp16 and stores them
-// to column-major C: register 4 q + r of block (rb, cb) is row 32 rb + c of the band, column
-// 32 cb + 8 q + 4 h + r of the group - 64 contiguous bytes of C per store and half wave.
-template <int CB>
-__device__ __forceinline__ void store_band32(_Float16* C, uint32_t M, uint32_t N, uint32_t n0,
-                                             const float16v (&acc)[kRowBlocks32][CB], uint32_t band, int lane) {
-  const uint32_t c = lane & 31, h = lane >> 5;
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t n = n0 + cb * 32 + q * 8 + h * 4 + r;
-        if (n < N) {
-#pragma unroll
-          for (int rb = 0; rb < kRowBlocks32; ++rb)
-            C[(size_t)n * M + band * kTileM + rb * 32 + c] = (_Float16)acc[rb][cb][4 * q + r];
-        }
-      }
-}
-
 // LDS of a workgroup: two X chunks (a chunk = the NS K tiles of a loop body x 64 columns, 4 KB per
 // tile), then the four waves' tiles.  The chunks come first so that the two lie 2^k apart and a
 // body switches between them by flipping one address bit.
@@ -147,13 +95,9 @@ __global__ __launch_bounds__(kWideWaves * 64) void spmm_wide_kernel(WideParams p
   // The workgroup: four row bands (one per wave) x one K slice, which all four waves walk together,
   // x one group of 64 columns.  A call of more than 64 columns is one launch over all its column
   // groups (with G groups the chip is filled by G times fewer K slices, so G times fewer partial
-  // sums per column go through memory than with a launch per group).  The G workgroups that stream
-  // the same words get workgroup ids 8 apart: consecutive ids go to the chip's eight XCDs in turn,
-  // so those G land on one XCD, one after the other, and all but the first find the words in its L2.
-  const uint32_t pairs = ((p.bands + 3u) / 4u) * p.S;  // (group of bands, slice) pairs
-  const uint32_t cg = (blockIdx.x >> 3) % p.G, pair = ((blockIdx.x >> 3) / p.G) * 8u + (blockIdx.x & 7u);
-  if (pair >= pairs) return;  // the grid is rounded up to a multiple of eight pairs
-  const uint32_t quad = pair / p.S, slice = pair - quad * p.S;
+  // sums per column go through memory than with a launch per group).
+  uint32_t quad, slice, cg;
+  if (!wide_unit((p.bands + 3u) / 4u, p.S, p.G, p.whole, quad, slice, cg)) return;
   const uint32_t n0 = p.n0 + cg * 64u;
   const uint32_t band = quad * 4 + wave;
   const bool active = band < p.bands;  // a wave past the last band loads no words but shares the X work
@@ -572,7 +516,8 @@ static hipError_t launch_wide_variant(WideParams p, int cus, hipStream_t stream)
   }
   const uint32_t quads = (p.bands + 3u) / 4u;
   p.S = wide_quad_slices(p.bands, p.G, p.KT, cus, NS);
-  const uint32_t grid = (quads * p.S + 7u) / 8u * 8u * p.G;  // (group of bands, slice) pairs rounded up to eight, x column groups
+  p.whole = whole_pairs(quads * p.S, p.G, cus);
+  const uint32_t grid = wide_grid(quads * p.S, p.G, p.whole);
   p.cb = CB;
   hipLaunchKernelGGL((spmm_wide_kernel<R, NS, FMT, CB>), dim3(grid), dim3(kWideWaves * 64), kLds, stream, p);
   hipError_t e = hipGetLastError();
