@@ -272,10 +272,10 @@ __device__ __forceinline__ uint32_t look_back(const CompressParams& p, uint32_t 
   return sum;
 }
 
-// Bound by instructions, not by memory yet: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 178 us, 3.2 TB/s, where a
-// copy reaches 4.7; 12288 x 12288 at 90 % in version 2 153 us.  The same work as count, scan and emit kernels that
-// each read W (or its counts) again: 85 + 98 + 269 us and 466 + 66 + 173 us; the whole call 491 -> 218 us and 744 ->
-// 187 us.  Sixteen tiles to a chunk keep the look-back and the ticket rare (one of each per 128 KB of W); eight
+// Near its memory bound in version 1: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 139 us, 4.1 TB/s, where a
+// copy reaches 5.1; version 2 is bound by instructions (12288 x 12288 at 90 % 144 us, 2.4 TB/s).  The same work as count, scan and emit kernels that
+// each read W (or its counts) again: 85 + 98 + 269 us and 466 + 66 + 173 us; the whole call 491 -> 168 us and 744 ->
+// 162 us.  Sixteen tiles to a chunk keep the look-back and the ticket rare (one of each per 128 KB of W); eight
 // waves with two tiles each leave room for two workgroups on a CU, one loading while the other writes.
 template <int FMT>
 __global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(CompressParams p) {
@@ -293,18 +293,26 @@ __global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(Comp
   unsigned char* stage = stages[wave];
 
   // Loads: lane j takes row 16 i + (j >> 2), K chunk j & 3 - a quad reads the 64 contiguous bytes of a row of the tile.
+  // The wave's tiles are neighbours in K, two to a 128 B line of W (but at a band's end): the two halves of a line are
+  // asked for one after the other, and the line stays in the caches in between.  (A tile's loads after the other's, and as
+  // non-temporal ones, fetched lines twice: 28672 x 7168 at 80 % 217 us a call against 168, 12288 x 12288 at 90 % in
+  // version 2 187 against 162.)
   TileCells t[kTilesPerWave];
-  uint32_t tile[kTilesPerWave];
+  const uint16_t* src[kTilesPerWave];
+  bool live[kTilesPerWave];
 #pragma unroll
   for (int a = 0; a < kTilesPerWave; ++a) {
-    tile[a] = q * kChunkTiles + wave * kTilesPerWave + a;
-    const uint32_t ta = tile[a] < p.T ? tile[a] : 0u;
+    const uint32_t tile = q * kChunkTiles + wave * kTilesPerWave + a;
+    live[a] = tile < p.T;
+    const uint32_t ta = live[a] ? tile : 0u;
     const uint32_t band = ta / p.KT, kt = ta - band * p.KT;
-    const uint16_t* src = p.W + ((size_t)band * kTileM + (lane >> 2)) * p.K + kt * kTileK + (lane & 3) * 8;
-#pragma unroll
-    for (int i = 0; i < kCells; ++i)
-      t[a].v[i] = tile[a] < p.T ? __builtin_nontemporal_load((const u32x4*)(src + (size_t)i * 16 * p.K)) : u32x4{0u, 0u, 0u, 0u};
+    src[a] = p.W + ((size_t)band * kTileM + (lane >> 2)) * p.K + kt * kTileK + (lane & 3) * 8;
   }
+#pragma unroll
+  for (int i = 0; i < kCells; ++i)
+#pragma unroll
+    for (int a = 0; a < kTilesPerWave; ++a)
+      t[a].v[i] = live[a] ? *(const u32x4*)(src[a] + (size_t)i * 16 * p.K) : u32x4{0u, 0u, 0u, 0u};
   // ... and through LDS into the order of the walk.  Slot of cell (row, K chunk c): 128 c + (row ^ 4 c); any 16
   // neighbouring lanes touch 16 different 16 B bank groups, both ways.
   uint32_t stored = 0;
