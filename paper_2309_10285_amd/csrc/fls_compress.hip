@@ -31,6 +31,10 @@ constexpr int kCells = kTileElems / 8 / 64;  // (row, K chunk) cells of a tile t
 // Entries that a wave's 8 KB of LDS stages at once (a word each, or a value and a location of 16 bits each);
 // a denser tile goes out in two rounds.
 constexpr uint32_t kStageEntries = 2048;
+// ... behind them a slot that nothing reads, for the elements that are not stored (version 2: one behind the values, one
+// behind the locations)
+constexpr uint32_t kStageBytes = kTileBytes + 32;
+constexpr uint32_t kStageLocs = 2 * kStageEntries + 16;
 
 // Where chunk q's state stands until the finish kernel runs: in words 16 q ... 16 q + 9 of TileOffsets (n_off
 // is a multiple of 16 and at least T + 4, so the last, partly empty chunk has room too).
@@ -187,15 +191,16 @@ __device__ __forceinline__ void stage_entries(TileCells& t, unsigned char* stage
   for (int s = 0; s < kCells; ++s) asm volatile("" : "+v"(t.v[s]));
   uint32_t* words = (uint32_t*)stage;                       // version 1
   uint16_t* values = (uint16_t*)stage;                      // version 2
-  uint16_t* locs = (uint16_t*)(stage + 2 * kStageEntries);
-  auto put = [&](uint32_t slot, uint32_t bits, uint32_t loc) {
-    if (ALL || slot < kStageEntries) {
-      if constexpr (FMT == 2) {
-        values[slot] = (uint16_t)bits;
-        locs[slot] = (uint16_t)loc;
-      } else {
-        words[slot] = (bits << 16) | loc;
-      }
+  uint16_t* locs = (uint16_t*)(stage + kStageLocs);
+  // Every lane stores every element, those that are zero to the slot that nothing reads: a branch around each store
+  // costs more than the store (28672 x 7168 at 80 %: 168 us a call with branches, 166 without; 12288 x 12288 at 90 % in version 2: 162 and 161).
+  auto put = [&](bool stored, uint32_t slot, uint32_t bits, uint32_t loc) {
+    const uint32_t at = stored && (ALL || slot < kStageEntries) ? slot : kStageEntries;
+    if constexpr (FMT == 2) {
+      values[at] = (uint16_t)bits;
+      locs[at] = (uint16_t)loc;
+    } else {
+      words[at] = (bits << 16) | loc;
     }
   };
   uint32_t pos = 0u - base, counter = 0;
@@ -208,20 +213,21 @@ __device__ __forceinline__ void stage_entries(TileCells& t, unsigned char* stage
       Before b = step_bridges(t.v[s], s, any, counter, lane);
       for (; b.bridges > 0; --b.bridges) {
         b.prev += kReach2;
-        put(slot++, 0u, b.prev);
+        put(true, slot++, 0u, b.prev);
       }
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const uint32_t bits = half_of(t.v[s], e);
-      if (bits) put(slot++, bits, loc0 + e);
+      put(bits != 0u, slot, bits, loc0 + e);
+      slot += bits != 0u ? 1u : 0u;
     }
     pos += field10(t.total, s);
   }
   // padding: version 1 words of value +0 one past the tile, version 2 entries of value 0 at distance 1
   const uint32_t slot = t.entries + (uint32_t)lane;
   if (lane < (int)kPad && slot < (t.entries + kPad - 1) / kPad * kPad)
-    put(slot - base, 0u, FMT == 2 ? t.last + 1u + (uint32_t)lane : (uint32_t)kTileElems);
+    put(true, slot - base, 0u, FMT == 2 ? t.last + 1u + (uint32_t)lane : (uint32_t)kTileElems);
 }
 
 // Copies the staged part of the run to the blob; dst = where the words of entry `base` go.
@@ -232,7 +238,7 @@ __device__ __forceinline__ void flush_stage(const TileCells& t, const unsigned c
   for (uint32_t g = (uint32_t)lane; g < groups; g += 64) {
     if constexpr (FMT == 2) {
       typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-      const u32x2 v = *(const u32x2*)(stage + g * 8), l = *(const u32x2*)(stage + 2 * kStageEntries + g * 8);
+      const u32x2 v = *(const u32x2*)(stage + g * 8), l = *(const u32x2*)(stage + kStageLocs + g * 8);
       const uint32_t l0 = l[0] & 0xffffu, l1 = l[0] >> 16, l2 = l[1] & 0xffffu, l3 = l[1] >> 16;
       dst[g * 3] = v[0];
       dst[g * 3 + 1] = v[1];
@@ -279,7 +285,7 @@ __device__ __forceinline__ uint32_t look_back(const CompressParams& p, uint32_t 
 // waves with two tiles each leave room for two workgroups on a CU, one loading while the other writes.
 template <int FMT>
 __global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(CompressParams p) {
-  __shared__ __align__(16) unsigned char stages[kChunkWaves][kTileBytes];
+  __shared__ __align__(16) unsigned char stages[kChunkWaves][kStageBytes];
   __shared__ uint32_t entries_of[kChunkTiles];
   __shared__ uint32_t stored_of[kChunkWaves];
   __shared__ uint32_t ticket, chunk_base;
