@@ -80,6 +80,8 @@ def lib():
         L.fls_forget.restype = None
         L.fls_dense_gemm.argtypes = [vp, vp, vp, i64, i64, i64, vp]
         L.fls_dense_gemm.restype = ci
+        L.fls_internal_spmm_plan.argtypes = [ctypes.c_uint32] * 5 + [ci, ci, ctypes.POINTER(ctypes.c_uint32)]
+        L.fls_internal_spmm_plan.restype = None
         L.fls_strerror.argtypes = [ci]
         L.fls_strerror.restype = ctypes.c_char_p
         _lib = L
@@ -274,6 +276,15 @@ def prepare_dense_gemm(W, X, C, M, K, N):
             _check(rc, "fls_dense_gemm")
 
     return call
+
+
+def spmm_plan(stats, N, cus=256, entry="fls_spmm"):
+    """What a product with that blob and N columns runs on a GPU of that many CUs, from the library's own rule: a dict of pass
+    ("narrow", "wide": the 64-column pass, "block"), share, rounds and slices.  Needs no GPU."""
+    out = (ctypes.c_uint32 * 4)()
+    lib().fls_internal_spmm_plan(stats["max_tile_words"], stats["format_version"], stats["M"], stats["K"], N, cus,
+                                 int(entry != "fls_spmm_noalloc"), out)
+    return dict(zip(("pass", "share", "rounds", "slices"), (("narrow", "wide", "block")[out[0]], *out[1:])))
 
 
 def fls_check_workspace():

@@ -445,6 +445,15 @@ int fls_dense_gemm(const void* W_dev, const void* X_dev, void* C_dev, int64_t M,
   return fls::launch_dense(a, (hipStream_t)stream) == hipSuccess ? FLS_OK : FLS_EHIP;
 }
 
+void fls_internal_spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t M, uint32_t K, uint32_t N, int cus, int wide32,
+                            uint32_t* out) {
+  const fls::SpmmPlan plan = fls::spmm_plan(max_tile_words, version, M / FLS_TILE_M, K / FLS_TILE_K, N, cus, wide32 != 0);
+  out[0] = (uint32_t)plan.pass;
+  out[1] = plan.share;
+  out[2] = plan.rounds;
+  out[3] = plan.slices;
+}
+
 const char* fls_strerror(int code) {
   switch (code) {
     case FLS_OK: return "ok";

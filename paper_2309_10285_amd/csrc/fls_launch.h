@@ -66,6 +66,7 @@ inline uint32_t wide_slices(uint32_t bands, uint32_t col_groups, uint32_t KT, in
 // group and slice.  Slices per (group of four bands, column group): as many as fill the CUs, none
 // shorter than two bodies.  With S > 1, groups of bands x column groups x S <= CUs <= kMaxWorkgroups,
 // so at most 4 * kMaxWorkgroups partial results exist (what parts_floats provides).
+inline uint32_t wide_body(uint32_t rounds) { return rounds <= 4u ? 8u : 4u; }  // by the rounds of a tile that the variant stages
 inline uint32_t wide_quad_slices(uint32_t bands, uint32_t col_groups, uint32_t KT, int cus, uint32_t body) {
   if (cus > (int)kMaxWorkgroups) cus = (int)kMaxWorkgroups;
   const uint64_t units = (uint64_t)((bands + 3) / 4) * col_groups;
@@ -109,8 +110,15 @@ inline uint32_t block_slices(uint32_t units, uint32_t KT, int cus) {
 // 28672 at 60 - 90 %, both formats, N = 80 ... 4096, the pass it picks is on average 2 % slower than the best of the three.  Some of what was measured (us, 64-column / share 1 / share 2):
 // 12288 x 12288 at 80 %, N = 128 60 / 59 / 70, 256 111 / 88 / 83, 384 190 / 122 / 139, 1000 379 / 280 / 254, 4096 1234 /
 // 942 / 872; 7168 x 28672 at 80 %, N = 384 180 / 149 / 174; 28672 x 7168 at 90 %, N = 256 94 / 108 / 104.
-uint32_t spmm_pass_share(uint32_t max_tile_words, uint32_t round_words, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus);
+uint32_t spmm_pass_share(uint32_t need, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus);
 constexpr uint32_t kBlockRounds1 = 6, kBlockRounds2 = 10;  // rounds of a tile that the variants with share 1 / 2 stage
+// Variants by the rounds of 256 entries that they stage of a tile: the smallest that holds the densest tile, which needs
+// `need` (the largest where none does: the kernels have a slow path for that).
+inline uint32_t wide_rounds(uint32_t need) { return need <= 2u ? 2u : need <= 4u ? need : need <= 6u ? 6u : need <= 8u ? 8u : 10u; }
+inline uint32_t block_rounds(uint32_t share, uint32_t need) {
+  if (share == 1u) return need <= 2u ? 2u : need <= 4u ? need : kBlockRounds1;
+  return need <= 2u ? 2u : need <= 8u ? (need + 1u) / 2u * 2u : kBlockRounds2;  // two waves stage a tile, every other round each
+}
 // fp32 values of the split-K partial sums: [workgroup][column blocks][128 x 16] for the passes of
 // up to 32 columns, [band][slice][4][128 x 16] for the 64-column pass
 inline size_t parts_floats(uint32_t N) {
@@ -141,7 +149,7 @@ inline bool wide32_pays(uint32_t max_tile_words, uint32_t round_words, uint32_t 
   if (KT >= 384u) return true;
   if (KT < 288u || max_tile_words <= 2u * round_words) return false;
   // the longest K slice at most a tenth above the mean (bodies of 8 tiles up to four rounds, of 4 beyond: as the pass picks them)
-  const uint32_t body = max_tile_words <= 4u * round_words ? 8u : 4u;
+  const uint32_t body = wide_body((max_tile_words + round_words - 1u) / round_words);
   const uint32_t bodies = KT / body, S = wide_quad_slices(bands, 1u, KT, cus, body);
   return (uint64_t)((bodies + S - 1u) / S) * S * 10u <= (uint64_t)bodies * 11u;
 }
@@ -194,13 +202,21 @@ struct WideParams {
   uint32_t cb; // 32-column blocks of a group that are multiplied and hold sums (sparse pass: 2, or 1 for a call of at most 32 columns)
 };
 
+// What a call of the sparse product runs.
+enum class SpmmPass : uint32_t { kNarrow, kWide, kBlock };  // passes of up to 32 columns; all columns in the 64-column pass; ... in the block pass
+struct SpmmPlan {
+  SpmmPass pass;
+  uint32_t share;   // block pass: 1 or 2, else 0
+  uint32_t rounds;  // rounds of a tile that the variant stages
+  uint32_t slices;  // K slices (block and 64-column pass), else 0
+};
+SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus, bool wide32);
 hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream);
 // X -> xpack (fragment order, all N columns): the dense 64-column passes read it
-// `groups` groups of 64 columns of the sparse 64-column pass from column n0 on, in one launch
 hipError_t launch_xpack(const _Float16* X, _Float16* xpack, uint32_t K, uint32_t N, hipStream_t stream);
-hipError_t launch_spmm_wide(const SpmmLaunch& a, uint32_t n0, uint32_t groups, hipStream_t stream);
-// all columns from n0 on with the block pass
-hipError_t launch_spmm_block(const SpmmLaunch& a, uint32_t n0, uint32_t share, hipStream_t stream);
+// all columns in the sparse 64-column pass, in the block pass
+hipError_t launch_spmm_wide(const SpmmLaunch& a, const SpmmPlan& plan, hipStream_t stream);
+hipError_t launch_spmm_block(const SpmmLaunch& a, const SpmmPlan& plan, hipStream_t stream);
 // C = sum over the S slices of parts, in slice order (the second kernel of a 64-column pass with S > 1);
 // layout32: the partial results are in the 32x32 accumulator layout (sparse pass), else 16x16 (dense pass)
 hipError_t launch_wide_reduce(const WideParams& p, bool layout32, hipStream_t stream);
@@ -210,3 +226,9 @@ hipError_t launch_compress(const CompressLaunch& a, hipStream_t stream);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 
 }  // namespace fls
+
+// What fls_spmm (wide32 = 1) or fls_spmm_noalloc (wide32 = 0) runs for a blob of that longest tile and version on a GPU of
+// that many CUs: out = pass, share, rounds, slices of SpmmPlan.  Host arithmetic only; for tests and the benchmark's
+// label, not part of the C ABI.
+extern "C" void fls_internal_spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t M, uint32_t K, uint32_t N, int cus, int wide32,
+                                       uint32_t* out);

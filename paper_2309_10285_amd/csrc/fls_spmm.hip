@@ -416,7 +416,30 @@ static hipError_t launch_r(int R, const SpmmParams& p, int grid, hipStream_t str
   }
 }
 
+SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus, bool wide32) {
+  const uint32_t round_words = version == 2u ? kRoundWords2 : 256u, need = (max_tile_words + round_words - 1u) / round_words;
+  const uint32_t groups = (N + kSpmmGroupCols - 1u) / kSpmmGroupCols;
+  // The 64-column pass stages at most ten rounds of a tile (it has no slow path for more; twelve
+  // rounds no longer fit its registers): a matrix with denser tiles - less than 40 % sparse
+  // somewhere - takes 32-column passes throughout.
+  if (N > kGroupCols ? need <= 10u : N > 16u && wide32 && wide32_pays(max_tile_words, round_words, KT, version, bands, cus)) {
+    // ... and beyond 64 columns it or the block pass takes all columns of the call, whichever the estimate prefers
+    const uint32_t share = N > kSpmmGroupCols ? spmm_pass_share(need, version, bands, KT, N, cus) : 0u;
+    if (share > 0)
+      return {SpmmPass::kBlock, share, block_rounds(share, need), block_slices(block_band_groups(bands, share) * block_col_groups(N, share), KT, cus)};
+    const uint32_t rounds = wide_rounds(need);
+    return {SpmmPass::kWide, 0u, rounds, wide_quad_slices(bands, groups, KT, cus, wide_body(rounds))};
+  }
+  return {SpmmPass::kNarrow, 0u, need <= 8u ? wide_rounds(need) : 8u, 0u};
+}
+
 hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream) {
+  const SpmmPlan plan = spmm_plan(a.max_tile_words, a.version, a.M / kTileM, a.K / kTileK, a.N, a.num_cus, a.wide32);
+  if (plan.pass == SpmmPass::kBlock) return launch_spmm_block(a, plan, stream);
+  // All the groups of 64 columns in one launch, a last one that is partly empty included: the workgroups of a
+  // further group find the words in their XCD's L2, where a narrower pass of its own for the rest would stream
+  // W from HBM once more (12288 x 12288 at 90 %: N = 80 in 42.5 us against 54.8, N = 96 in 42.2 against 59.7).
+  if (plan.pass == SpmmPass::kWide) return launch_spmm_wide(a, plan, stream);
   SpmmParams p;
   p.offs = a.offs;
   p.words = a.words;
@@ -430,48 +453,13 @@ hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream) {
   p.out.N = a.N;
   p.out.KT = a.K / kTileK;
   const int grid = pick_grid(a.M / kTileM, a.K / kTileK, a.num_cus);
-  // rounds of 256 words staged per tile: the smallest variant that holds the densest tile
-  // (a denser tile is still handled, through a slow path)
   const bool v2 = a.version == 2;
-  const uint32_t round_words = v2 ? kRoundWords2 : 256u;
-  int R = 8;
-  if (a.max_tile_words <= 2 * round_words) R = 2;
-  else if (a.max_tile_words <= 3 * round_words) R = 3;
-  else if (a.max_tile_words <= 4 * round_words) R = 4;
-  else if (a.max_tile_words <= 6 * round_words) R = 6;
-  // The 64-column pass stages at most ten rounds of a tile (it has no slow path for more; twelve
-  // rounds no longer fit its registers): a matrix with denser tiles - less than 40 % sparse
-  // somewhere - takes 32-column passes throughout.
-  const bool wide_ok = a.max_tile_words <= 10 * round_words;
-  // ... and beyond 64 columns it or the block pass takes all columns of the call, whichever the estimate prefers
-  const uint32_t share =
-      wide_ok && a.N > kSpmmGroupCols ? spmm_pass_share(a.max_tile_words, round_words, a.version, a.M / kTileM, a.K / kTileK, a.N, a.num_cus) : 0u;
-  for (uint32_t n0 = 0; n0 < a.N;) {
+  const int R = (int)plan.rounds;
+  for (uint32_t n0 = 0; n0 < a.N; n0 += a.N - n0 <= 16 ? 16 : kGroupCols) {
     p.out.n0 = n0;
-    const uint32_t left = a.N - n0;
     hipError_t e;
-    if (left <= 16) {
-      p.X = a.X;
-      e = v2 ? launch_r<1, 8, 2>(R, p, grid, stream) : launch_r<1, 8, 1>(R, p, grid, stream);
-      n0 += 16;
-    } else if (left <= 32 && a.wide32 && wide32_pays(a.max_tile_words, round_words, a.K / kTileK, a.version, a.M / kTileM, a.num_cus)) {
-      e = launch_spmm_wide(a, n0, 1, stream);  // multiplies its first 32-column block only
-      n0 += 32;
-    } else if (left <= 32 || !wide_ok) {
-      p.X = a.X;
-      e = v2 ? launch_r<2, 8, 2>(R, p, grid, stream) : launch_r<2, 8, 1>(R, p, grid, stream);
-      n0 += 32;
-    } else if (share > 0) {
-      e = launch_spmm_block(a, n0, share, stream);
-      n0 = a.N;
-    } else {
-      // All the groups of 64 columns in one launch, a last one that is partly empty included: the workgroups of a
-      // further group find the words in their XCD's L2, where a narrower pass of its own for the rest would stream
-      // W from HBM once more (12288 x 12288 at 90 %: N = 80 in 42.5 us against 54.8, N = 96 in 42.2 against 59.7).
-      const uint32_t groups = (left + kSpmmGroupCols - 1u) / kSpmmGroupCols;
-      e = launch_spmm_wide(a, n0, groups, stream);
-      n0 += groups * kSpmmGroupCols;
-    }
+    if (a.N - n0 <= 16) e = v2 ? launch_r<1, 8, 2>(R, p, grid, stream) : launch_r<1, 8, 1>(R, p, grid, stream);
+    else e = v2 ? launch_r<2, 8, 2>(R, p, grid, stream) : launch_r<2, 8, 1>(R, p, grid, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

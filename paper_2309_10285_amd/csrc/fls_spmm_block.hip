@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kBlockWaves * 64) __attribute__((amdgpu_waves_per_e
 }
 
 template <int SHARE, int RW, int FMT>
-static hipError_t launch_block_variant(WideParams p, int cus, hipStream_t stream) {
+static hipError_t launch_block_variant(const WideParams& p, hipStream_t stream) {
   static std::atomic<bool> attr_done{false};  // per kernel variant; setting the attribute twice from two threads is harmless
   constexpr int kLds = block_lds_bytes<SHARE>();
   if (!attr_done.load(std::memory_order_acquire)) {
@@ -347,7 +347,6 @@ static hipError_t launch_block_variant(WideParams p, int cus, hipStream_t stream
     attr_done.store(true, std::memory_order_release);
   }
   const uint32_t bgroups = block_band_groups(p.bands, SHARE), cgroups = block_col_groups(p.N - p.n0, SHARE);
-  p.S = block_slices(bgroups * cgroups, p.KT, cus);
   const uint32_t grid = (bgroups * p.S * cgroups + 7u) / 8u * 8u;
   hipLaunchKernelGGL((spmm_block_kernel<SHARE, RW, FMT>), dim3(grid), dim3(kBlockWaves * 64), kLds, stream, p);
   hipError_t e = hipGetLastError();
@@ -356,26 +355,26 @@ static hipError_t launch_block_variant(WideParams p, int cus, hipStream_t stream
 }
 
 template <int FMT>
-static hipError_t launch_block_fmt(const WideParams& p, uint32_t share, uint32_t rounds, int cus, hipStream_t stream) {
+static hipError_t launch_block_fmt(const WideParams& p, uint32_t share, uint32_t rounds, hipStream_t stream) {
   if (share == 1u) {
-    if (rounds <= 2) return launch_block_variant<1, 2, FMT>(p, cus, stream);
-    if (rounds <= 3) return launch_block_variant<1, 3, FMT>(p, cus, stream);
-    if (rounds <= 4) return launch_block_variant<1, 4, FMT>(p, cus, stream);
-    return launch_block_variant<1, 6, FMT>(p, cus, stream);
+    switch (rounds) {
+      case 2: return launch_block_variant<1, 2, FMT>(p, stream);
+      case 3: return launch_block_variant<1, 3, FMT>(p, stream);
+      case 4: return launch_block_variant<1, 4, FMT>(p, stream);
+      default: return launch_block_variant<1, 6, FMT>(p, stream);
+    }
   }
-  if (rounds <= 2) return launch_block_variant<2, 1, FMT>(p, cus, stream);
-  if (rounds <= 4) return launch_block_variant<2, 2, FMT>(p, cus, stream);
-  if (rounds <= 6) return launch_block_variant<2, 3, FMT>(p, cus, stream);
-  if (rounds <= 8) return launch_block_variant<2, 4, FMT>(p, cus, stream);
-  return launch_block_variant<2, 5, FMT>(p, cus, stream);
+  switch (rounds) {
+    case 2: return launch_block_variant<2, 1, FMT>(p, stream);
+    case 4: return launch_block_variant<2, 2, FMT>(p, stream);
+    case 6: return launch_block_variant<2, 3, FMT>(p, stream);
+    case 8: return launch_block_variant<2, 4, FMT>(p, stream);
+    default: return launch_block_variant<2, 5, FMT>(p, stream);
+  }
 }
 
-uint32_t spmm_pass_share(uint32_t max_tile_words, uint32_t round_words, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N,
-                         int cus) {
-  uint32_t R = 10;  // rounds that the 64-column pass stages
-  for (uint32_t r : {8u, 6u, 4u, 3u, 2u})
-    if (max_tile_words <= r * round_words) R = r;
-  const uint32_t body = R <= 4u ? 8u : 4u;
+uint32_t spmm_pass_share(uint32_t need, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus) {
+  const uint32_t R = wide_rounds(need), body = wide_body(R);  // of the 64-column pass
   const float slower = version == 2u ? 1.04f : 1.0f;  // of version 2's extraction
   auto estimate = [&](float step, uint32_t units, uint32_t S, uint32_t tiles, float start) {
     const uint32_t wgs = units * S, rounds = (wgs + (uint32_t)cus - 1u) / (uint32_t)cus;
@@ -399,8 +398,7 @@ uint32_t spmm_pass_share(uint32_t max_tile_words, uint32_t round_words, uint32_t
   return pick;
 }
 
-// All columns from n0 on.  share: 1 (at most kBlockRounds1 rounds a tile) or 2 (at most kBlockRounds2).
-hipError_t launch_spmm_block(const SpmmLaunch& a, uint32_t n0, uint32_t share, hipStream_t stream) {
+hipError_t launch_spmm_block(const SpmmLaunch& a, const SpmmPlan& plan, hipStream_t stream) {
   WideParams p;
   p.offs = a.offs;
   p.words = a.words;
@@ -412,16 +410,13 @@ hipError_t launch_spmm_block(const SpmmLaunch& a, uint32_t n0, uint32_t share, h
   p.M = a.M;
   p.K = a.K;
   p.N = a.N;
-  p.n0 = n0;
+  p.n0 = 0;
   p.KT = a.K / kTileK;
   p.bands = a.M / kTileM;
-  p.S = 1;
-  p.G = (a.N - n0 + 63u) / 64u;
+  p.S = plan.slices;
+  p.G = (a.N + 63u) / 64u;
   p.cb = 2;
-  const uint32_t round = a.version == 2 ? kRoundWords2 : 256u;
-  const uint32_t rounds = (a.max_tile_words + round - 1u) / round;
-  return a.version == 2 ? launch_block_fmt<2>(p, share, rounds, a.num_cus, stream)
-                        : launch_block_fmt<1>(p, share, rounds, a.num_cus, stream);
+  return a.version == 2 ? launch_block_fmt<2>(p, plan.share, plan.rounds, stream) : launch_block_fmt<1>(p, plan.share, plan.rounds, stream);
 }
 
 }  // namespace fls

@@ -505,8 +505,9 @@ __global__ __launch_bounds__(256) void wide_reduce_kernel(WideParams p) {
   }
 }
 
-template <int R, int NS, int FMT, int CB = 2>
+template <int R, int FMT, int CB>
 static hipError_t launch_wide_variant(WideParams p, int cus, hipStream_t stream) {
+  constexpr int NS = R <= 4 ? 8 : 4;  // wide_body: the ring is eight tiles deep while the registers allow
   static std::atomic<bool> attr_done{false};  // per kernel variant; setting the attribute twice from two threads is harmless
   constexpr int kLds = wide_lds_bytes<NS>();
   if (!attr_done.load(std::memory_order_acquire)) {
@@ -515,7 +516,6 @@ static hipError_t launch_wide_variant(WideParams p, int cus, hipStream_t stream)
     attr_done.store(true, std::memory_order_release);
   }
   const uint32_t quads = (p.bands + 3u) / 4u;
-  p.S = wide_quad_slices(p.bands, p.G, p.KT, cus, NS);
   p.whole = whole_pairs(quads * p.S, p.G, cus);
   const uint32_t grid = wide_grid(quads * p.S, p.G, p.whole);
   p.cb = CB;
@@ -523,6 +523,20 @@ static hipError_t launch_wide_variant(WideParams p, int cus, hipStream_t stream)
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && p.S > 1) e = launch_wide_reduce(p, true, stream);
   return e;
+}
+
+// Variants by rounds staged per tile (256 words in version 1, 64 groups = 192 words in version 2).
+template <int FMT, int CB>
+static hipError_t launch_wide_rounds(uint32_t rounds, const WideParams& p, int cus, hipStream_t stream) {
+  switch (rounds) {
+    case 2: return launch_wide_variant<2, FMT, CB>(p, cus, stream);
+    case 3: return launch_wide_variant<3, FMT, CB>(p, cus, stream);
+    case 4: return launch_wide_variant<4, FMT, CB>(p, cus, stream);
+    // (wide32_pays asks for no more in version 2 with one column block)
+    case 6: return launch_wide_variant<6, FMT, FMT == 2 ? 2 : CB>(p, cus, stream);
+    case 8: return launch_wide_variant<8, FMT, FMT == 2 ? 2 : CB>(p, cus, stream);
+    default: return launch_wide_variant<10, FMT, FMT == 2 ? 2 : CB>(p, cus, stream);
+  }
 }
 
 // X (all N columns of the call) into fragment order, once per call of the dense 64-column pass.
@@ -539,8 +553,8 @@ hipError_t launch_wide_reduce(const WideParams& p, bool layout32, hipStream_t st
   return hipGetLastError();
 }
 
-// `groups` groups of 64 columns starting at column n0, in one launch (the last group may reach past N).
-hipError_t launch_spmm_wide(const SpmmLaunch& a, uint32_t n0, uint32_t groups, hipStream_t stream) {
+// All groups of 64 columns in one launch (the last group may reach past N).
+hipError_t launch_spmm_wide(const SpmmLaunch& a, const SpmmPlan& plan, hipStream_t stream) {
   WideParams p;
   p.offs = a.offs;
   p.words = a.words;
@@ -552,46 +566,15 @@ hipError_t launch_spmm_wide(const SpmmLaunch& a, uint32_t n0, uint32_t groups, h
   p.M = a.M;
   p.K = a.K;
   p.N = a.N;
-  p.n0 = n0;
-  p.G = groups;
+  p.n0 = 0;
+  p.G = (a.N + kSpmmGroupCols - 1u) / kSpmmGroupCols;
   p.KT = a.K / kTileK;
   p.bands = a.M / kTileM;
-  p.S = 1;
-  // Variants by rounds staged per tile (256 words in version 1, 64 groups = 192 words in version 2); the ring is
-  // 8 tiles deep while the registers allow.
-  // At most 32 columns in all: only the first 32-column block is multiplied (the variants that wide32_pays can
-  // ask for; anything else - a header that is out of date - falls through to the two-block variants, which are right
-  // for any N).
-  if (groups == 1 && a.N - n0 <= 32u) {
-    const uint32_t round = a.version == 2 ? kRoundWords2 : 256u;
-    if (a.version == 2) {
-      if (a.max_tile_words <= 2 * round) return launch_wide_variant<2, 8, 2, 1>(p, a.num_cus, stream);
-      if (a.max_tile_words <= 3 * round) return launch_wide_variant<3, 8, 2, 1>(p, a.num_cus, stream);
-      if (a.max_tile_words <= 4 * round) return launch_wide_variant<4, 8, 2, 1>(p, a.num_cus, stream);
-    } else {
-      if (a.max_tile_words <= 2 * round) return launch_wide_variant<2, 8, 1, 1>(p, a.num_cus, stream);
-      if (a.max_tile_words <= 3 * round) return launch_wide_variant<3, 8, 1, 1>(p, a.num_cus, stream);
-      if (a.max_tile_words <= 4 * round) return launch_wide_variant<4, 8, 1, 1>(p, a.num_cus, stream);
-      if (a.max_tile_words <= 6 * round) return launch_wide_variant<6, 4, 1, 1>(p, a.num_cus, stream);
-      if (a.max_tile_words <= 8 * round) return launch_wide_variant<8, 4, 1, 1>(p, a.num_cus, stream);
-      if (a.max_tile_words <= 10 * round) return launch_wide_variant<10, 4, 1, 1>(p, a.num_cus, stream);
-    }
-  }
-  if (a.version == 2) {
-    const uint32_t round = kRoundWords2;
-    if (a.max_tile_words <= 2 * round) return launch_wide_variant<2, 8, 2>(p, a.num_cus, stream);
-    if (a.max_tile_words <= 3 * round) return launch_wide_variant<3, 8, 2>(p, a.num_cus, stream);
-    if (a.max_tile_words <= 4 * round) return launch_wide_variant<4, 8, 2>(p, a.num_cus, stream);
-    if (a.max_tile_words <= 6 * round) return launch_wide_variant<6, 4, 2>(p, a.num_cus, stream);
-    if (a.max_tile_words <= 8 * round) return launch_wide_variant<8, 4, 2>(p, a.num_cus, stream);
-    return launch_wide_variant<10, 4, 2>(p, a.num_cus, stream);
-  }
-  if (a.max_tile_words <= 2 * 256) return launch_wide_variant<2, 8, 1>(p, a.num_cus, stream);
-  if (a.max_tile_words <= 3 * 256) return launch_wide_variant<3, 8, 1>(p, a.num_cus, stream);
-  if (a.max_tile_words <= 4 * 256) return launch_wide_variant<4, 8, 1>(p, a.num_cus, stream);
-  if (a.max_tile_words <= 6 * 256) return launch_wide_variant<6, 4, 1>(p, a.num_cus, stream);
-  if (a.max_tile_words <= 8 * 256) return launch_wide_variant<8, 4, 1>(p, a.num_cus, stream);
-  return launch_wide_variant<10, 4, 1>(p, a.num_cus, stream);
+  p.S = plan.slices;
+  // at most 32 columns in all: only the first 32-column block is multiplied
+  if (a.N <= kGroupCols)
+    return a.version == 2 ? launch_wide_rounds<2, 1>(plan.rounds, p, a.num_cus, stream) : launch_wide_rounds<1, 1>(plan.rounds, p, a.num_cus, stream);
+  return a.version == 2 ? launch_wide_rounds<2, 2>(plan.rounds, p, a.num_cus, stream) : launch_wide_rounds<1, 2>(plan.rounds, p, a.num_cus, stream);
 }
 
 }  // namespace fls

@@ -107,7 +107,7 @@ def sweep_w32():
 
 
 # one point per kernel path of the sweep: 96 bands cut between all workgroups with the hand-over through
-# memory (N = 8, N = 32 at 60 %), the 64-column pass with K slices (N = 64), two such passes (N = 128), the
+# memory (N = 8, N = 32 at 60 %), the 64-column pass with K slices (N = 64), the block pass (N = 128, N = 256), the
 # row-skewed mask at 50 %, whose densest tiles need the ten-round register ring of the 64-column pass, and
 # 32 columns at 90 %, which take the 64-column pass with one column block
 SWEEP_POINTS = [("uniform", 0.8, 8), ("uniform", 0.6, 32), ("uniform", 0.9, 64), ("uniform", 0.7, 128),

@@ -1,0 +1,76 @@
+"""Which pass and variant a product takes: the library's rule, asked on the host."""
+import itertools
+import random
+
+import pytest
+
+import test_gpu_block_pass
+
+ROUND_WORDS = {1: 256, 2: 192}
+
+
+@pytest.fixture(scope="module")
+def plan():
+    import os
+
+    import paper_2309_10285_amd as fls
+    from paper_2309_10285_amd import _build
+
+    if not os.path.exists(fls.LIB_PATH):
+        _build.build()
+
+    def ask(rounds, version, M, K, N, cus=256, entry="fls_spmm"):
+        p = fls.spmm_plan({"max_tile_words": rounds * ROUND_WORDS[version], "format_version": version, "M": M, "K": K}, N, cus, entry)
+        return p["pass"], p["share"], p["rounds"], p["slices"]
+
+    return ask
+
+
+def test_the_block_pass_cases_reach_every_variant(plan):
+    """The cases of the GPU test, asked with the rounds that tiles of their sparsity need, and all variants among them."""
+    need = {0.9: 2, 0.85: 3, 0.8: 4, 0.7: 6, 0.6: 7, 0.55: 8, 0.5: 9}
+    seen = set()
+    for M, K, N, sparsity, version, want in test_gpu_block_pass.ROWS:
+        p = plan(need[sparsity], version, M, K, N)
+        assert (*p[:3], p[3] > 1) == want, (M, K, N)
+        if p[0] == "block":
+            seen.add((p[1], p[2], version))
+    assert seen == {(share, r, v) for v in (1, 2) for share, rounds in ((1, (2, 3, 4, 6)), (2, (2, 4, 6, 8, 10))) for r in rounds}
+
+
+@pytest.mark.parametrize("version", [1, 2])
+def test_columns_and_density_decide(plan, version):
+    M, K = 12288, 8192  # bands of 256 K tiles: too short for the 64-column pass at up to 32 columns
+    for N in (1, 16, 17, 32):
+        assert plan(4, version, M, K, N)[0] == "narrow"
+    for N in (33, 64):
+        assert plan(4, version, M, K, N)[0] == "wide"
+    assert plan(4, version, M, K, 4096)[0] == "block"
+    for N in (33, 64, 65, 4096):  # denser tiles than any of the wider passes stages
+        assert plan(11, version, M, K, N) == ("narrow", 0, 8, 0)
+    long_band = (2, version, 12288, 49152)
+    assert plan(*long_band, 32)[0] == "wide" and plan(*long_band, 16)[0] == "narrow"
+    assert plan(*long_band, 32, entry="fls_spmm_noalloc")[0] == "narrow"
+    for rounds, staged in ((1, 2), (2, 2), (3, 3), (4, 4), (5, 6), (6, 6), (7, 8), (8, 8), (9, 10), (10, 10)):
+        assert plan(rounds, version, M, K, 64)[2] == staged
+
+
+def _shapes(count):
+    rng = random.Random(7)
+    for _ in range(count):
+        M, K = int(128 * 500 ** rng.random()) // 128 * 128, int(32 * 2000 ** rng.random()) // 32 * 32
+        N = min(int(33 * 248 ** rng.random()), (2**30 - 1) // max(M, K))
+        if N > 32 and M * K < 2**32:
+            yield M, K, N
+
+
+@pytest.mark.parametrize("cus", [8, 64, 256, 304])
+def test_partial_sums_fit_their_area(plan, cus):
+    """A sliced product leaves slices x bands x groups of 64 columns partial results of 32 KB; the area holds 2048."""
+    for (M, K, N), rounds, version in itertools.product(_shapes(400), (2, 4, 6, 10), (1, 2)):
+        kind, share, staged, slices = plan(rounds, version, M, K, N, cus)
+        assert slices >= 1 and staged >= rounds
+        if slices > 1:
+            groups = -(-N // 64)
+            units = -(-M // 512) * groups if kind == "wide" else -(-M * share // 512) * -(-N // (128 * share))
+            assert units * slices <= min(cus, 512) and M // 128 * groups * slices <= 2048
