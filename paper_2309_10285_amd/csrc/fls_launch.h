@@ -100,16 +100,20 @@ inline uint32_t block_slices(uint32_t units, uint32_t KT, int cus) {
   return S < by_length ? S : by_length;
 }
 // Which pass a call of more than 64 columns takes: 0 the 64-column pass, else the block pass's share.
-// The passes differ in three ways that pull apart: what a tile step costs (extraction and fragment reads are
-// shared by 64, 128 or 256 columns), how evenly their units fill the CUs (a ragged last round, columns that only pad), and
-// how many partial sums they leave when K is sliced (a CU of the block pass holds twice as many).  So the rule is an
-// estimate of each, in us, with measured constants: a step of one workgroup takes 0.30 + 0.071 R us (64
-// columns x 4 bands), 0.72 + 0.036 R (128 x 4) and 0.70 + 0.026 R (256 x 2) for R staged rounds with the whole chip at
-// work, and less where part of it idles, since the matrix cores' clock is set by power; partial sums are written and read back at
-// 5.5 TB/s; the block pass clears and stores twice as much, 1.5 us.  On 48 products of 1024 x 1760 ... 32000 x 7584 and 7168 x
-// 28672 at 60 - 90 %, both formats, N = 80 ... 4096, the pass it picks is on average 2 % slower than the best of the three.  Some of what was measured (us, 64-column / share 1 / share 2):
-// 12288 x 12288 at 80 %, N = 128 60 / 59 / 70, 256 111 / 88 / 83, 384 190 / 122 / 139, 1000 379 / 280 / 254, 4096 1234 /
-// 942 / 872; 7168 x 28672 at 80 %, N = 384 180 / 149 / 174; 28672 x 7168 at 90 %, N = 256 94 / 108 / 104.
+// The passes differ in what a tile step costs (extraction and fragment reads are shared by 64, 128 or 256 columns), in
+// how evenly their units fill the CUs (a ragged last round, columns that only pad), in how many partial sums they leave when K is
+// sliced (a CU of the block pass holds twice as many), in what a workgroup's start and end cost (the block pass clears three
+// buffers and stores twice the sums), and in the K tiles that fill no body, which the 64-column pass takes one by one.  These
+// pull apart, so the rule is an estimate of each pass in us, with constants fitted to 1200 products drawn over the sizes that the calls take:
+//   a step of one workgroup 0.29 + 0.075 R (64 columns x 4 bands), 0.75 + 0.035 R (128 x 4), 0.65 + 0.022 R (256 x 2) for R staged
+//   rounds of a tile, 0.90 + 0.28 R for a tile outside the bodies; down to 0.7 of that where the chip idles (the matrix cores' clock is set by power);
+//   a round of workgroups 3 (64-column pass, if it has a body at all) or 4; a call 4, in the block pass 7; partial sums
+//   1 and their bytes out and back at 7 TB/s; and what is level to 3 % goes to the 64-column pass.
+// On 400 other products (M 128 ... 49152, K 32 ... 49152, N 65 ... 4096, 50 - 90 %, both formats) its pick takes 1.007 times the best of the three,
+// 1.27 at most; without the starts and the tiles outside the bodies in the estimate 1.029 and 1.89 (12288 x 480 at 80 %, N = 4096: 139 us
+// instead of 67).  Some of what was measured (us, 64-column / share 1 / share 2): 12288 x 12288 at 80 %, N = 128 57.8 / 60.5 / 68.2, 256 111 / 89 /
+// 84, 384 189 / 127 / 143, 1000 384 / 285 / 259, 4096 1328 / 975 / 914; 7168 x 28672 at 80 %, N = 384 176 / 151 / 174; 28672 x 7168 at 90 %,
+// N = 256 87 / 104 / 102; 12288 x 32 at 90 %, N = 4096 30 / 38 / 38, 12288 x 224 69 / 51 / 50.
 uint32_t spmm_pass_share(uint32_t need, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus);
 constexpr uint32_t kBlockRounds1 = 6, kBlockRounds2 = 10;  // rounds of a tile that the variants with share 1 / 2 stage
 // Variants by the rounds of 256 entries that they stage of a tile: the smallest that holds the densest tile, which needs

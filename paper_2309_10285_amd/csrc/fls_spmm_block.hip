@@ -373,23 +373,33 @@ static hipError_t launch_block_fmt(const WideParams& p, uint32_t share, uint32_t
   }
 }
 
+// Measurement builds (pass_times.py): 0, 1 or 2 takes that pass for every call of more than 64 columns.
+#ifndef FLS_PASS
+#define FLS_PASS -1
+#endif
+
 uint32_t spmm_pass_share(uint32_t need, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus) {
+  if (FLS_PASS >= 0) return (uint32_t)FLS_PASS;
   const uint32_t R = wide_rounds(need), body = wide_body(R);  // of the 64-column pass
-  const float slower = version == 2u ? 1.04f : 1.0f;  // of version 2's extraction
-  auto estimate = [&](float step, uint32_t units, uint32_t S, uint32_t tiles, float start) {
+  const float slower = version == 2u ? 1.08f : 1.0f;  // of version 2's extraction
+  // `round`: what a round of workgroups costs beside its steps; `rest`: tiles outside the pipelined loop
+  auto estimate = [&](float start, uint32_t units, uint32_t S, float round, float steps, float rest) {
     const uint32_t wgs = units * S, rounds = (wgs + (uint32_t)cus - 1u) / (uint32_t)cus;
     const float fill = (float)wgs / ((float)rounds * (float)cus);
-    float us = start + (float)rounds * (float)tiles * step * slower * (0.4f + 0.6f * fill);
-    if (S > 1u) us += 2.0f + (float)bands * (float)((N + 63u) / 64u) * (float)S * (2.0f * 32768.0f / 5.5e6f);
+    float us = start + (float)rounds * (round + (steps * slower + rest) * (0.7f + 0.3f * fill));
+    if (S > 1u) us += 1.0f + (float)bands * (float)((N + 63u) / 64u) * (float)S * (2.0f * 32768.0f / 7.0e6f);
     return us;
   };
-  const uint32_t groups = (N + 63u) / 64u, S0 = wide_quad_slices(bands, groups, KT, cus, body);
-  float best = estimate(0.30f + 0.071f * (float)R, (bands + 3u) / 4u * groups, S0, (KT / body + S0 - 1u) / S0 * body, 0.0f);
+  // the 64-column pass: whole bodies, and in the last slice tile by tile what is left of K
+  const uint32_t groups = (N + 63u) / 64u, S0 = wide_quad_slices(bands, groups, KT, cus, body), bodies = (KT / body + S0 - 1u) / S0;
+  float best = 0.97f * estimate(4.0f, (bands + 3u) / 4u * groups, S0, bodies > 0u ? 3.0f : 0.0f, (float)(bodies * body) * (0.29f + 0.075f * (float)R),
+                                (float)(KT % body) * (0.90f + 0.28f * (float)R));
   uint32_t pick = 0;
   for (uint32_t share = 1; share <= 2; ++share) {
     if (share == 1u && R > kBlockRounds1) continue;
     const uint32_t units = block_band_groups(bands, share) * block_col_groups(N, share), S = block_slices(units, KT, cus);
-    const float us = estimate(share == 1u ? 0.72f + 0.036f * (float)R : 0.70f + 0.026f * (float)R, units, S, ((KT + 2u) / 3u + S - 1u) / S * 3u, 1.5f);
+    const float us = estimate(4.0f + 3.0f, units, S, 4.0f,
+                              (float)(((KT + 2u) / 3u + S - 1u) / S * 3u) * (share == 1u ? 0.75f + 0.035f * (float)R : 0.65f + 0.022f * (float)R), 0.0f);
     if (us < best) {
       best = us;
       pick = share;

@@ -50,18 +50,23 @@ PREBUILT_MASKS = (0, 1 | 2 | 4 | 8 | 16)
 
 
 def build_variant(mask, folder):
-    """libfls_ablate<mask>.so in `folder`: the two kernel sources compiled with -DFLS_ABLATE=<mask>, linked with
-    the library's other objects (built by _build.build(); built here if missing)."""
+    """libfls_ablate<mask>.so in `folder`: the two kernel sources compiled with -DFLS_ABLATE=<mask>."""
+    return build_with(f"ablate{mask}", f"-DFLS_ABLATE={mask}", ABLATED_SOURCES, folder)
+
+
+def build_with(name, define, sources, folder):
+    """libfls_<name>.so in `folder`: `sources` compiled with `define`, linked with the library's other objects (built by
+    _build.build(); built here if missing)."""
     os.makedirs(folder, exist_ok=True)
-    lib = os.path.join(folder, f"libfls_ablate{mask}.so")
-    others = [os.path.join(_build.CSRC, s.replace(".hip", ".o")) for s in _build.SOURCES if s not in ABLATED_SOURCES]
+    lib = os.path.join(folder, f"libfls_{name}.so")
+    others = [os.path.join(_build.CSRC, s.replace(".hip", ".o")) for s in _build.SOURCES if s not in sources]
     if not all(os.path.exists(o) for o in others):
         _build.build()
     objs, procs = [], []
-    for src in ABLATED_SOURCES:
-        obj = os.path.join(folder, f"a{mask}_{src.replace('.hip', '.o')}")
+    for src in sources:
+        obj = os.path.join(folder, f"{name}_{src.replace('.hip', '.o')}")
         objs.append(obj)
-        cmd = ["hipcc", *_build.HIPCC_FLAGS, f"-DFLS_ABLATE={mask}", "-c", os.path.join(_build.CSRC, src), "-o", obj]
+        cmd = ["hipcc", *_build.HIPCC_FLAGS, define, "-c", os.path.join(_build.CSRC, src), "-o", obj]
         procs.append(subprocess.Popen(cmd, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE, text=True))
     for p in procs:
         _, err = p.communicate()

@@ -67,9 +67,9 @@ ROWS = [
     (22912, 544, 513, 0.8, 2, ("block", 1, 4, False)),
     (22912, 416, 513, 0.7, 1, ("block", 1, 6, False)),
     (22912, 416, 513, 0.7, 2, ("block", 1, 6, False)),
-    # ... K slices of unequal length, a column group with one column more than half
-    (3968, 3040, 65, 0.7, 1, ("block", 1, 6, True)),
-    (3968, 3040, 65, 0.7, 2, ("block", 1, 6, True)),
+    # ... K slices of unequal length
+    (1152, 9952, 456, 0.7, 1, ("block", 1, 6, True)),
+    (2304, 5600, 470, 0.7, 2, ("block", 1, 6, True)),
     # 256 columns x two bands: one band on its own in dozens of K slices
     (128, 19840, 197, 0.9, 1, ("block", 2, 2, True)),
     (128, 18784, 201, 0.9, 2, ("block", 2, 2, True)),
@@ -83,13 +83,13 @@ ROWS = [
     (640, 3040, 384, 0.6, 2, ("block", 2, 8, True)),
     (5760, 736, 257, 0.5, 1, ("block", 2, 10, False)),
     (1664, 3040, 129, 0.5, 2, ("block", 2, 10, True)),
-    # shapes like these that the rule gives to one pass or the other
-    (3968, 544, 257, 0.7, 1, ("block", 2, 6, False)),
-    (3968, 544, 512, 0.7, 2, ("block", 2, 6, False)),
+    # shapes like these that the rule gives to the 64-column pass, whose K tiles fill no whole number of bodies
+    (3968, 544, 257, 0.7, 1, ("wide", 0, 6, True)),
+    (3968, 544, 512, 0.7, 2, ("wide", 0, 6, True)),
     (3968, 544, 512, 0.9, 1, ("wide", 0, 2, False)),
-    (15232, 544, 125, 0.7, 1, ("block", 1, 6, False)),
+    (15232, 544, 125, 0.7, 1, ("wide", 0, 6, True)),
     (15232, 544, 125, 0.8, 2, ("wide", 0, 4, False)),
-    (7296, 1696, 125, 0.7, 1, ("block", 1, 6, True)),
+    (7296, 1696, 125, 0.7, 1, ("wide", 0, 6, True)),
 ]
 
 
@@ -105,7 +105,7 @@ def test_edges(fls, M, K, N, sparsity, version, plan):
 
 
 @pytest.mark.parametrize("M,K,N,sparsity,version,plan", [r for r in ROWS if r[:3] in (
-    (22912, 416, 513), (3968, 3040, 65), (8064, 608, 129), (640, 3040, 384), (640, 3040, 385), (1664, 3040, 129))])
+    (22912, 416, 513), (1152, 9952, 456), (8064, 608, 129), (640, 3040, 384), (640, 3040, 385), (1664, 3040, 129))])
 def test_denser_blob_behind_the_librarys_back(fls, M, K, N, sparsity, version, plan):
     """The variant is picked for the sparse blob that the library remembers; the denser one that stands there by the
     time of the call does not fit its stages and takes the block pass's plain loop."""
@@ -127,10 +127,11 @@ def test_denser_blob_behind_the_librarys_back(fls, M, K, N, sparsity, version, p
 
 
 @pytest.mark.parametrize("M,K,N,plan", [
-    (3968, 544, 300, ("block", 2, 6, False)),
+    (3968, 544, 300, ("wide", 0, 6, True)),
+    (8064, 608, 300, ("block", 2, 6, False)),
     (896, 3040, 641, ("block", 2, 6, True)),
     (22912, 416, 513, ("block", 1, 6, False)),
-    (3968, 3040, 97, ("block", 1, 6, True)),
+    (1152, 9952, 456, ("block", 1, 6, True)),
 ])
 def test_inf_and_nan_stay_in_their_slice(fls, M, K, N, plan):
     """An Inf of X at the first k behind a slice or behind the last K tile must not meet the zero tiles that fill a body

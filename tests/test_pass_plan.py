@@ -55,6 +55,24 @@ def test_columns_and_density_decide(plan, version):
         assert plan(rounds, version, M, K, 64)[2] == staged
 
 
+@pytest.mark.parametrize("rounds,version,M,K,N,share", [
+    # K tiles that fill no body of the 64-column pass (us there / in the block pass with share 1 / 2)
+    (4, 1, 12288, 480, 4096, 2),    # 139 / 70 / 67
+    (7, 1, 12288, 224, 4096, 2),    # 100 / - / 57
+    (4, 1, 46720, 672, 149, 2),     # 48 / 28 / 25
+    (5, 1, 39808, 192, 266, 1),     # 26 / 19 / 27
+    # so little work that the start of a block pass costs more than it saves
+    (2, 1, 12288, 32, 4096, 0),     # 30 / 38 / 38
+    (4, 1, 4096, 160, 1000, 0),     # 12.6 / 15.9 / 14.9
+    (7, 1, 2176, 384, 1768, 0),     # 17.0 / - / 19.6
+    (7, 2, 1280, 1056, 1475, 0),    # 28.9 / - / 32.8
+    # level: the pass with fewer partial sums
+    (4, 1, 12288, 12288, 128, 0),   # 57.9 / 60.5 / 70.8
+])
+def test_the_rule_takes_the_pass_that_measured_faster(plan, rounds, version, M, K, N, share):
+    assert plan(rounds, version, M, K, N)[1] == share
+
+
 def _shapes(count):
     rng = random.Random(7)
     for _ in range(count):
