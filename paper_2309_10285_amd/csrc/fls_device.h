@@ -67,19 +67,23 @@ __device__ __forceinline__ bool xcd_unit(uint32_t units, uint32_t& unit) {
 // The 64-column passes: group of four bands, K slice and group of 64 columns of this workgroup.  The G workgroups that
 // stream the same words run on one XCD, one after the other, and all but the first find them in its L2.
 // `whole` (see whole_pairs of the launchers): (quad, slice) pair 8 i + x goes to XCD x with all its column groups.
-// Otherwise every XCD takes an eighth of all units, slice by slice.
+// Otherwise every XCD takes an eighth of all units, slice by slice.  (Two branches, not one formula with selects: that cost 1 - 2 % of
+// calls of 5 - 10 us and half a percent of longer ones.)
 __device__ __forceinline__ bool wide_unit(uint32_t quads, uint32_t S, uint32_t G, bool whole, uint32_t& quad, uint32_t& slice, uint32_t& cg) {
-  const uint32_t pairs = quads * S, x = blockIdx.x & 7u;
+  if (whole) {
+    const uint32_t i = blockIdx.x >> 3, pair = i / G * 8u + (blockIdx.x & 7u);
+    cg = i % G;
+    quad = pair / S;
+    slice = pair - quad * S;
+    return pair < quads * S;
+  }
   uint32_t unit;
-  const bool mine = xcd_unit(pairs * G, unit);
-  if (whole) unit = blockIdx.x >> 3;
-  uint32_t pair = unit / G;
+  if (!xcd_unit(quads * S * G, unit)) return false;
+  const uint32_t pair = unit / G;
   cg = unit - pair * G;
-  if (whole) pair = pair * 8u + x;
-  const uint32_t by = whole ? S : quads, major = pair / by, minor = pair - major * by;
-  quad = whole ? major : minor;
-  slice = whole ? minor : major;
-  return whole ? pair < pairs : mine;
+  slice = pair / quads;
+  quad = pair - slice * quads;
+  return true;
 }
 
 // First tile of workgroup q's share when T tiles are cut over P workgroups.

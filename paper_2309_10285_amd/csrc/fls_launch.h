@@ -77,7 +77,8 @@ inline uint32_t wide_quad_slices(uint32_t bands, uint32_t col_groups, uint32_t K
 // How the 64-column passes spread their (group of four bands, K slice) pairs over the eight XCDs: whole pairs, in turn,
 // unless that leaves an XCD so many more workgroups than others that it takes a round more than an even cut of
 // all units.  7168 x 28672 at 80 %, N = 384: three slices, 42 pairs of six column groups, 36 workgroups on two XCDs of 32
-// CUs: 316 us, evenly cut 180; 12672 x 7840 at 82 %, N = 1085: 377 / 266; 5504 x 2752 at 64 %, N = 2735: 217 / 150.  Where both
+// CUs: 316 us, evenly cut 180; 12672 x 7840 at 82 %, N = 1085: 377 / 266; 5504 x 2752 at 64 %, N = 2735: 217 / 150.  The dense
+// pass, 7168 x 28672, N = 384: 896 / 516, and level (1 % either way) on 170 shapes of which most keep whole pairs.  Where both
 // take as many rounds whole pairs are up to 2 % faster (12288 x 12288 at 80 %, N = 128: 55.2 / 56.4 us; 27648 x 9216 at 70 %,
 // N = 32: 58.1 / 59.2).
 inline bool whole_pairs(uint32_t pairs, uint32_t G, int cus) {
