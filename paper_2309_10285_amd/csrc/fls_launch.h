@@ -105,17 +105,18 @@ inline uint32_t block_slices(uint32_t units, uint32_t KT, int cus) {
 // how evenly their units fill the CUs (a ragged last round, columns that only pad), in how many partial sums they leave when K is
 // sliced (a CU of the block pass holds twice as many), in what a workgroup's start and end cost (the block pass clears three
 // buffers and stores twice the sums), and in the K tiles that fill no body, which the 64-column pass takes one by one.  These
-// pull apart, so the rule is an estimate of each pass in us, with constants fitted to 1200 products drawn over the sizes that the calls take:
-//   a step of one workgroup 0.29 + 0.075 R (64 columns x 4 bands), 0.75 + 0.035 R (128 x 4), 0.65 + 0.022 R (256 x 2) for R staged
+// pull apart, so the rule is an estimate of each pass in us, with constants fitted to 2600 products over the sizes that the calls take:
+//   a step of one workgroup 0.24 + 0.08 R (64 columns x 4 bands), 0.68 + 0.047 R (128 x 4), 0.675 + 0.017 R (256 x 2) for R staged
 //   rounds of a tile, 0.90 + 0.28 R for a tile outside the bodies; down to 0.7 of that where the chip idles (the matrix cores' clock is set by power);
 //   a round of workgroups 3 (64-column pass, if it has a body at all) or 4; a call 4, in the block pass 7; partial sums
 //   1 and their bytes out and back at 7 TB/s; and what is level to 3 % goes to the 64-column pass.
-// On 400 other products (M 128 ... 49152, K 32 ... 49152, N 65 ... 4096, 50 - 90 %, both formats) its pick takes 1.007 times the best of the three,
-// 1.27 at most; without the starts and the tiles outside the bodies in the estimate 1.029 and 1.89 (12288 x 480 at 80 %, N = 4096: 139 us
-// instead of 67).  Some of what was measured (us, 64-column / share 1 / share 2): 12288 x 12288 at 80 %, N = 128 57.8 / 60.5 / 68.2, 256 111 / 89 /
-// 84, 384 189 / 127 / 143, 1000 384 / 285 / 259, 4096 1328 / 975 / 914; 7168 x 28672 at 80 %, N = 384 176 / 151 / 174; 28672 x 7168 at 90 %,
-// N = 256 87 / 104 / 102; 12288 x 32 at 90 %, N = 4096 30 / 38 / 38, 12288 x 224 69 / 51 / 50.
-uint32_t spmm_pass_share(uint32_t need, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus);
+// On 400 other products (M 128 ... 49152, K 32 ... 49152, N 65 ... 4096, 50 - 90 %, both formats) its pick takes 1.009 times the best of the three,
+// 1.24 at most, and 0.865 times the 64-column pass; on four of them it is more than 2 % slower than that pass.  Some of what was measured
+// (us, 64-column / share 1 / share 2): 12288 x 12288 at 80 %, N = 128 57.8 / 60.5 / 68.2, 256 111 / 89 /
+// 84, 384 189 / 127 / 143, 1000 384 / 285 / 259, 4096 1328 / 975 / 914; at 90 %, N = 256 78 / 79 / 78, 512 133 / 145 / 140, 1024 272 / 249 / 242, 2048
+// 437 / 530 / 498; 7168 x 28672 at 80 %, N = 384 176 / 151 / 174; 12288 x 480 at 80 %, N = 4096 139 / 70 / 67; 12288 x 32 at 90 %, N = 4096
+// 30 / 38 / 38.
+uint32_t spmm_pass_share(uint32_t need, uint32_t bands, uint32_t KT, uint32_t N, int cus);
 constexpr uint32_t kBlockRounds1 = 6, kBlockRounds2 = 10;  // rounds of a tile that the variants with share 1 / 2 stage
 // Variants by the rounds of 256 entries that they stage of a tile: the smallest that holds the densest tile, which needs
 // `need` (the largest where none does: the kernels have a slow path for that).

@@ -424,7 +424,7 @@ SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, ui
   // somewhere - takes 32-column passes throughout.
   if (N > kGroupCols ? need <= 10u : N > 16u && wide32 && wide32_pays(max_tile_words, round_words, KT, version, bands, cus)) {
     // ... and beyond 64 columns it or the block pass takes all columns of the call, whichever the estimate prefers
-    const uint32_t share = N > kSpmmGroupCols ? spmm_pass_share(need, version, bands, KT, N, cus) : 0u;
+    const uint32_t share = N > kSpmmGroupCols ? spmm_pass_share(need, bands, KT, N, cus) : 0u;
     if (share > 0)
       return {SpmmPass::kBlock, share, block_rounds(share, need), block_slices(block_band_groups(bands, share) * block_col_groups(N, share), KT, cus)};
     const uint32_t rounds = wide_rounds(need);

@@ -378,28 +378,27 @@ static hipError_t launch_block_fmt(const WideParams& p, uint32_t share, uint32_t
 #define FLS_PASS -1
 #endif
 
-uint32_t spmm_pass_share(uint32_t need, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus) {
+uint32_t spmm_pass_share(uint32_t need, uint32_t bands, uint32_t KT, uint32_t N, int cus) {
   if (FLS_PASS >= 0) return (uint32_t)FLS_PASS;
   const uint32_t R = wide_rounds(need), body = wide_body(R);  // of the 64-column pass
-  const float slower = version == 2u ? 1.08f : 1.0f;  // of version 2's extraction
-  // `round`: what a round of workgroups costs beside its steps; `rest`: tiles outside the pipelined loop
-  auto estimate = [&](float start, uint32_t units, uint32_t S, float round, float steps, float rest) {
+  // `round`: what a round of workgroups costs beside its steps
+  auto estimate = [&](float start, uint32_t units, uint32_t S, float round, float steps) {
     const uint32_t wgs = units * S, rounds = (wgs + (uint32_t)cus - 1u) / (uint32_t)cus;
     const float fill = (float)wgs / ((float)rounds * (float)cus);
-    float us = start + (float)rounds * (round + (steps * slower + rest) * (0.7f + 0.3f * fill));
+    float us = start + (float)rounds * (round + steps * (0.7f + 0.3f * fill));
     if (S > 1u) us += 1.0f + (float)bands * (float)((N + 63u) / 64u) * (float)S * (2.0f * 32768.0f / 7.0e6f);
     return us;
   };
   // the 64-column pass: whole bodies, and in the last slice tile by tile what is left of K
   const uint32_t groups = (N + 63u) / 64u, S0 = wide_quad_slices(bands, groups, KT, cus, body), bodies = (KT / body + S0 - 1u) / S0;
-  float best = 0.97f * estimate(4.0f, (bands + 3u) / 4u * groups, S0, bodies > 0u ? 3.0f : 0.0f, (float)(bodies * body) * (0.29f + 0.075f * (float)R),
-                                (float)(KT % body) * (0.90f + 0.28f * (float)R));
+  float best = 0.97f * estimate(4.0f, (bands + 3u) / 4u * groups, S0, bodies > 0u ? 3.0f : 0.0f,
+                                (float)(bodies * body) * (0.24f + 0.08f * (float)R) + (float)(KT % body) * (0.90f + 0.28f * (float)R));
   uint32_t pick = 0;
   for (uint32_t share = 1; share <= 2; ++share) {
-    if (share == 1u && R > kBlockRounds1) continue;
+    if (share == 1u && need > kBlockRounds1) continue;
     const uint32_t units = block_band_groups(bands, share) * block_col_groups(N, share), S = block_slices(units, KT, cus);
-    const float us = estimate(4.0f + 3.0f, units, S, 4.0f,
-                              (float)(((KT + 2u) / 3u + S - 1u) / S * 3u) * (share == 1u ? 0.75f + 0.035f * (float)R : 0.65f + 0.022f * (float)R), 0.0f);
+    const float r = (float)block_rounds(share, need), step = share == 1u ? 0.68f + 0.047f * r : 0.675f + 0.017f * r;
+    const float us = estimate(4.0f + 3.0f, units, S, 4.0f, (float)(((KT + 2u) / 3u + S - 1u) / S * 3u) * step);
     if (us < best) {
       best = us;
       pick = share;

@@ -31,6 +31,7 @@ def products():
     out = [(7168, 28672, 0.8, 1, n) for n in (80, 128, 192, 256, 384, 1000, 4096)]
     out += [(12288, 12288, 0.8, 1, n) for n in (80, 128, 192, 256, 384, 512, 1000, 4096)]
     out += [(12288, 12288, 0.7, 2, n) for n in (128, 256, 384, 1000, 4096)]
+    out += [(m, m, 0.9, 1, n) for m in (9216, 12288) for n in (128, 256, 512, 1024, 2048, 4096)]
     out += [(12288, 12288, 0.6, 1, n) for n in (128, 256, 512, 2048)]
     out += [(28672, 7168, 0.9, 1, n) for n in (128, 256, 512, 1000, 4096)]
     return out + [(4096, 4096, 0.6, 1, n) for n in (80, 128, 256, 384, 512, 1000, 4096)]

@@ -2,8 +2,8 @@
 Each case says which variant it is there for, and the library's own rule is asked whether it runs that one.  C against the
 product in 64 bits of the same fp16 operands.
 
-Tolerance: products of fp16 values are exact in fp32; a sum of K <= 19840 of them in fp32 is off by at most K * 2^-24 of the
-sum of their magnitudes (about 1.2e-3 of it, and far less in effect), fp16 rounding adds 2^-11 of the value: 2e-3 of the
+Tolerance: products of fp16 values are exact in fp32; a sum of K <= 11200 of them in fp32 is off by at most K * 2^-24 of the
+sum of their magnitudes (about 7e-4 of it, and far less in effect), fp16 rounding adds 2^-11 of the value: 2e-3 of the
 largest value covers both, as in the other parity tests.
 """
 import numpy as np
@@ -59,8 +59,8 @@ def _plan(fls, stats, N):
 # M, K, N, sparsity, version, and the pass with its share, the rounds of a tile that the variant stages and whether K is sliced
 ROWS = [
     # 128 columns x four bands, an incomplete group of bands, K tiles that are no multiple of three, a ragged last column group
-    (35968, 1312, 350, 0.9, 1, ("block", 1, 2, False)),
-    (35072, 1312, 361, 0.9, 2, ("block", 1, 2, False)),
+    (35968, 160, 257, 0.9, 1, ("block", 1, 2, False)),
+    (33664, 160, 271, 0.9, 2, ("block", 1, 2, False)),
     (5376, 800, 1477, 0.85, 1, ("block", 1, 3, False)),
     (5376, 800, 1533, 0.85, 2, ("block", 1, 3, False)),
     (22912, 544, 513, 0.8, 1, ("block", 1, 4, False)),
@@ -68,11 +68,11 @@ ROWS = [
     (22912, 416, 513, 0.7, 1, ("block", 1, 6, False)),
     (22912, 416, 513, 0.7, 2, ("block", 1, 6, False)),
     # ... K slices of unequal length
-    (1152, 9952, 456, 0.7, 1, ("block", 1, 6, True)),
-    (2304, 5600, 470, 0.7, 2, ("block", 1, 6, True)),
-    # 256 columns x two bands: one band on its own in dozens of K slices
-    (128, 19840, 197, 0.9, 1, ("block", 2, 2, True)),
-    (128, 18784, 201, 0.9, 2, ("block", 2, 2, True)),
+    (5504, 8672, 277, 0.8, 1, ("block", 1, 4, True)),
+    (12160, 3680, 331, 0.8, 2, ("block", 1, 4, True)),
+    # 256 columns x two bands: one band on its own in dozens of K slices; few K tiles
+    (128, 11200, 137, 0.9, 1, ("block", 2, 2, True)),
+    (21632, 160, 732, 0.9, 2, ("block", 2, 2, False)),
     # ... an odd number of bands, a last column group with one column, or half empty
     (16768, 544, 449, 0.8, 1, ("block", 2, 4, False)),
     (640, 3040, 897, 0.8, 2, ("block", 2, 4, True)),
@@ -105,7 +105,7 @@ def test_edges(fls, M, K, N, sparsity, version, plan):
 
 
 @pytest.mark.parametrize("M,K,N,sparsity,version,plan", [r for r in ROWS if r[:3] in (
-    (22912, 416, 513), (1152, 9952, 456), (8064, 608, 129), (640, 3040, 384), (640, 3040, 385), (1664, 3040, 129))])
+    (22912, 416, 513), (5504, 8672, 277), (8064, 608, 129), (640, 3040, 384), (640, 3040, 385), (1664, 3040, 129))])
 def test_denser_blob_behind_the_librarys_back(fls, M, K, N, sparsity, version, plan):
     """The variant is picked for the sparse blob that the library remembers; the denser one that stands there by the
     time of the call does not fit its stages and takes the block pass's plain loop."""
@@ -126,19 +126,19 @@ def test_denser_blob_behind_the_librarys_back(fls, M, K, N, sparsity, version, p
     assert np.abs(C - ref).max() / np.abs(ref).max() <= TOL
 
 
-@pytest.mark.parametrize("M,K,N,plan", [
-    (3968, 544, 300, ("wide", 0, 6, True)),
-    (8064, 608, 300, ("block", 2, 6, False)),
-    (896, 3040, 641, ("block", 2, 6, True)),
-    (22912, 416, 513, ("block", 1, 6, False)),
-    (1152, 9952, 456, ("block", 1, 6, True)),
+@pytest.mark.parametrize("M,K,N,sparsity,plan", [
+    (3968, 544, 300, 0.7, ("wide", 0, 6, True)),
+    (8064, 608, 300, 0.7, ("block", 2, 6, False)),
+    (896, 3040, 641, 0.7, ("block", 2, 6, True)),
+    (22912, 416, 513, 0.7, ("block", 1, 6, False)),
+    (5504, 8672, 277, 0.82, ("block", 1, 4, True)),
 ])
-def test_inf_and_nan_stay_in_their_slice(fls, M, K, N, plan):
+def test_inf_and_nan_stay_in_their_slice(fls, M, K, N, sparsity, plan):
     """An Inf of X at the first k behind a slice or behind the last K tile must not meet the zero tiles that fill a body
     up: against stored weights everywhere it gives Inf, never NaN."""
     W = wl.dense_bits(wl.gen_weights_f32(M, K, 91))
     g = np.random.Generator(np.random.Philox(92))
-    W[g.random((M, K)) < 0.7] = 0
+    W[g.random((M, K)) < sparsity] = 0
     X = wl.gen_x(N, K, 93)
     for i, k in enumerate(range(0, K, 32)):  # one Inf per K tile, in a column of its own
         W[:, k] = 0x2400

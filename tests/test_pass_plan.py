@@ -66,6 +66,11 @@ def test_columns_and_density_decide(plan, version):
     (4, 1, 4096, 160, 1000, 0),     # 12.6 / 15.9 / 14.9
     (7, 1, 2176, 384, 1768, 0),     # 17.0 / - / 19.6
     (7, 2, 1280, 1056, 1475, 0),    # 28.9 / - / 32.8
+    # sparse tiles, which cost the 64-column pass least
+    (2, 1, 12288, 12288, 512, 0),   # 133 / 145 / 140
+    (2, 1, 12288, 12288, 2048, 0),  # 437 / 530 / 498
+    (2, 1, 9216, 9216, 4096, 0),    # 537 / 607 / 582
+    (2, 1, 12288, 12288, 1024, 2),  # 272 / 249 / 242
     # level: the pass with fewer partial sums
     (4, 1, 12288, 12288, 128, 0),   # 57.9 / 60.5 / 70.8
 ])
