@@ -101,8 +101,10 @@ __device__ __forceinline__ uint32_t cell_location(int s, int lane) {
   return (uint32_t)(s >> 1) * (kTileM * 8) + ((uint32_t)(s & 1) * 64 + (uint32_t)lane) * 8;
 }
 
-// stored elements of a cell: min(half, 1) summed, two halves at a time (an asm statement: of the same min in C++ the
-// compiler makes a compare and a select per half, and the counts came out wrong)
+// Stored elements of a cell: min(half, 1) summed, two halves at a time.  An asm statement: of the same min in C++ the
+// compiler makes a compare and a select per half and a merge.  (And __builtin_bit_cast(u16x2, v[i]), the obvious way to write it, counts
+// v[0] four times: given an element of a vector clang reads the vector's first one, whatever i, in host code and without optimisation too
+// - clang 22 of ROCm 7.2.  A scalar copy of the element casts right; nothing here casts an element of a vector.)
 __device__ __forceinline__ uint32_t cell_count(const u32x4& v) {
   u16x2 n = {0, 0};
 #pragma unroll
@@ -193,7 +195,8 @@ __device__ __forceinline__ void stage_entries(TileCells& t, unsigned char* stage
   uint16_t* values = (uint16_t*)stage;                      // version 2
   uint16_t* locs = (uint16_t*)(stage + kStageLocs);
   // Every lane stores every element, those that are zero to the slot that nothing reads: a branch around each store
-  // costs more than the store (28672 x 7168 at 80 %: 168 us a call with branches, 166 without; 12288 x 12288 at 90 % in version 2: 162 and 161).
+  // costs more than the store (28672 x 7168 at 80 %: 169.1 us a call with branches, 164.6 without; 12288 x 12288 at 90 % in version 2, where most
+  // branches are those of the bridges: 162.7 and 162.1; repeats differ by half a percent).
   auto put = [&](bool stored, uint32_t slot, uint32_t bits, uint32_t loc) {
     const uint32_t at = stored && (ALL || slot < kStageEntries) ? slot : kStageEntries;
     if constexpr (FMT == 2) {
@@ -278,9 +281,10 @@ __device__ __forceinline__ uint32_t look_back(const CompressParams& p, uint32_t 
   return sum;
 }
 
-// Near its memory bound in version 1: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 139 us, 4.1 TB/s, where a
-// copy reaches 5.1; version 2 is bound by instructions (12288 x 12288 at 90 % 144 us, 2.4 TB/s).  The same work as count, scan and emit kernels that
-// each read W (or its counts) again: 85 + 98 + 269 us and 466 + 66 + 173 us; the whole call 491 -> 168 us and 744 ->
+// Near its memory bound in version 1: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 133 us, 4.3 TB/s, where a
+// copy reaches 5.1; version 2 is bound by instructions (12288 x 12288 at 90 % 130 us, 2.7 TB/s; the vector ALUs issue in 72 % of the cycles, in
+// version 1 in 45 %; LDS is busy in 26 and 24 %).  The same work as count, scan and emit kernels that
+// each read W (or its counts) again: 85 + 98 + 269 us and 466 + 66 + 173 us; the whole call 491 -> 165 us and 744 ->
 // 162 us.  Sixteen tiles to a chunk keep the look-back and the ticket rare (one of each per 128 KB of W); eight
 // waves with two tiles each leave room for two workgroups on a CU, one loading while the other writes.
 template <int FMT>
