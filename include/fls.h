@@ -162,7 +162,7 @@ int fls_check_workspace(fls_stream_t stream);
 
 /*
  * C = W . X with W given as a Tiled-CSL blob (the SpMM of Alg. 1): streams the blob from HBM
- * (once per 64 columns for N > 32, per 128 or 256 in the block pass that most calls of more than 64 take, else once), rebuilds each tile densely in LDS, multiplies
+ * (once per 64 columns for N > 32, per 128 or 256 in the block pass that many calls of more than 64 take, else once), rebuilds each tile densely in LDS, multiplies
  * with MFMA, fp32 accumulation.  Partial sums of different workgroups are added in a fixed order;
  * inside a workgroup the waves' sums are added in the order they finish unless the workgroup's
  * tiles lie in one row band (then in wave order), so two runs may differ in the last bit of an
