@@ -28,13 +28,9 @@ constexpr int kChunkWaves = 8;
 constexpr int kTilesPerWave = 2;
 constexpr int kChunkTiles = kChunkWaves * kTilesPerWave;
 constexpr int kCells = kTileElems / 8 / 64;  // (row, K chunk) cells of a tile that a lane holds: 8 halves each
-// Entries that a wave's 8 KB of LDS stages at once (a word each, or a value and a location of 16 bits each);
-// a denser tile goes out in two rounds.
+// Entries that a wave's 8 KB of LDS stages at once, a word (value, location) each in either version; a denser tile goes
+// out in two rounds.
 constexpr uint32_t kStageEntries = 2048;
-// ... behind them a slot that nothing reads, for the elements that are not stored (version 2: one behind the values, one
-// behind the locations)
-constexpr uint32_t kStageBytes = kTileBytes + 32;
-constexpr uint32_t kStageLocs = 2 * kStageEntries + 16;
 
 // Where chunk q's state stands until the finish kernel runs: in words 16 q ... 16 q + 9 of TileOffsets (n_off
 // is a multiple of 16 and at least T + 4, so the last, partly empty chunk has room too).
@@ -53,8 +49,6 @@ struct CompressParams {
   uint64_t capacity_words;  // words that fit behind TileOffsets
   uint32_t M, K, KT, T, n_off, policy;
 };
-
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t* offs_of(const CompressParams& p) { return (uint32_t*)(p.out + 64); }
 __device__ __forceinline__ uint32_t* words_of(const CompressParams& p) { return (uint32_t*)(p.out + 64 + 4 * (size_t)p.n_off); }
@@ -82,99 +76,67 @@ __device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
   return v;
 }
 
-// A tile as a wave holds it for the walk in location order (K chunk, then row, then position in the chunk): in
-// step s a lane has the cell (row 64 (s & 1) + lane, K chunk s >> 1), 8 consecutive locations.
+// A tile as a wave holds it for the walk in location order: a lane has 64 consecutive locations, from 64 * lane on (eight
+// rows of one K chunk: eight cells of eight halves).  One prefix sum over the lanes then places every entry, a lane's masks of
+// stored elements give its first and last one, and a gap that takes bridges only ever lies before a lane's first element.
 struct TileCells {
   u32x4 v[kCells];
-  // Entries of the steps before this lane, three steps to a word, ten bits each: a step has at most 512 stored
-  // elements and 65 bridges.
-  uint32_t before[3], total[3];
-  uint32_t entries;       // of the tile, padding not counted
-  uint32_t last;          // (version 2) location of its last stored element
+  uint32_t before;   // entries of the lanes before this one
+  uint32_t bridges;  // (version 2) entries needed to reach the lane's first stored element,
+  uint32_t prev;     // ... from this location: that of the stored element before it, 0 if there is none
+  uint32_t entries;  // of the tile, padding not counted
+  uint32_t last;     // (version 2) location of its last stored element
 };
 
-__device__ __forceinline__ uint32_t field10(const uint32_t (&w)[3], int s) { return (w[s / 3] >> (10 * (s % 3))) & 0x3ffu; }
-
-__device__ __forceinline__ uint32_t half_of(const u32x4& v, int e) { return (e & 1) ? v[e >> 1] >> 16 : v[e >> 1] & 0xffffu; }
-
-__device__ __forceinline__ uint32_t cell_location(int s, int lane) {
-  return (uint32_t)(s >> 1) * (kTileM * 8) + ((uint32_t)(s & 1) * 64 + (uint32_t)lane) * 8;
-}
-
-// Stored elements of a cell: min(half, 1) summed, two halves at a time.  An asm statement: of the same min in C++ the
-// compiler makes a compare and a select per half and a merge.  (And __builtin_bit_cast(u16x2, v[i]), the obvious way to write it, counts
-// v[0] four times: given an element of a vector clang reads the vector's first one, whatever i, in host code and without optimisation too
-// - clang 22 of ROCm 7.2.  A scalar copy of the element casts right; nothing here casts an element of a vector.)
-__device__ __forceinline__ uint32_t cell_count(const u32x4& v) {
-  u16x2 n = {0, 0};
+// Bit e of the lowest eight: element e of the cell is stored.  min(half, 1) of two halves at a time as an asm statement: of the
+// same min in C++ the compiler makes a compare and a select per half and a merge.  (And __builtin_bit_cast(u16x2, v[i]), the obvious way to
+// write it, counts v[0] four times: given an element of a vector clang reads the vector's first one, whatever i, in host code and
+// without optimisation too - clang 22 of ROCm 7.2.  A scalar copy of the element casts right; nothing here casts an element of a vector.)
+__device__ __forceinline__ uint32_t cell_mask(const u32x4& v) {
+  uint32_t m = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    u16x2 one;
+    uint32_t one;
     asm("v_pk_min_u16 %0, %1, %2" : "=v"(one) : "v"(v[i]), "v"(0x00010001u));
-    n += one;
+    m |= one << (2 * i);  // even halves in bits 0, 2, 4, 6, odd ones in bits 16, 18, 20, 22
   }
-  return (uint32_t)n[0] + (uint32_t)n[1];
+  return m | m >> 15;
 }
 
-// index of the first / last stored element of a cell that has one
-__device__ __forceinline__ uint32_t cell_first(const u32x4& v) {
-  uint32_t f = 0;
+// Masks of a lane's stored elements: bit 8 i + e of the two words together is element e of cell i.
+__device__ __forceinline__ void tile_masks(const TileCells& t, uint32_t& lo, uint32_t& hi) {
+  uint32_t w[2];
 #pragma unroll
-  for (int e = 7; e >= 0; --e)
-    if (half_of(v, e)) f = e;
-  return f;
-}
-__device__ __forceinline__ uint32_t cell_last(const u32x4& v) {
-  uint32_t f = 0;
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    if (half_of(v, e)) f = e;
-  return f;
+  for (int h = 0; h < 2; ++h) {
+    // byte 0 of the second operand, then byte 0 of the first; then the two pairs
+    const uint32_t a = __builtin_amdgcn_perm(cell_mask(t.v[4 * h + 1]), cell_mask(t.v[4 * h]), 0x0c0c0400u);
+    const uint32_t b = __builtin_amdgcn_perm(cell_mask(t.v[4 * h + 3]), cell_mask(t.v[4 * h + 2]), 0x04000c0cu);
+    w[h] = a | b;
+  }
+  lo = w[0];
+  hi = w[1];
 }
 
-// Version 2: what stands before a lane's first stored element of step s.
-struct Before {
-  uint32_t prev;     // location of the stored element before it, 0 if there is none
-  uint32_t bridges;  // entries needed to reach it
-};
-// `any`: the lane's cell has a stored element; `counter`: location of the last one of the steps before, moved on
-__device__ __forceinline__ Before step_bridges(const u32x4& v, int s, bool any, uint32_t& counter, int lane) {
-  const uint32_t loc0 = cell_location(s, lane), last = loc0 + cell_last(v), first = loc0 + cell_first(v);
-  const uint64_t have = __builtin_amdgcn_ballot_w64(any);
-  const uint64_t below = have & ((1ull << lane) - 1ull);
-  const int from = below ? 63 - __builtin_clzll(below) : 0;
-  const uint32_t of_lane = (uint32_t)__builtin_amdgcn_ds_bpermute(from * 4, (int)last);
-  Before b;
-  b.prev = below ? of_lane : counter;
-  b.bridges = any && first > b.prev ? (first - b.prev - 1u) / kReach2 : 0u;
-  if (have) counter = (uint32_t)__builtin_amdgcn_readlane((int)last, 63 - __builtin_clzll(have));
-  return b;
-}
-
-// Counts the tile; returns its stored elements.
+// Counts a lane's entries of the tile; `stored` = its stored elements.
 template <int FMT>
-__device__ __forceinline__ uint32_t count_tile(TileCells& t, int lane) {
-  uint32_t packed[3] = {0u, 0u, 0u}, nz = 0, counter = 0;
-#pragma unroll
-  for (int s = 0; s < kCells; ++s) {
-    uint32_t n = cell_count(t.v[s]);
-    if constexpr (FMT == 2) {
-      nz += n;
-      n += step_bridges(t.v[s], s, n != 0, counter, lane).bridges;
-    }
-    packed[s / 3] |= n << (10 * (s % 3));
+__device__ __forceinline__ uint32_t count_lane(TileCells& t, uint32_t& stored, int lane) {
+  uint32_t lo, hi;
+  tile_masks(t, lo, hi);
+  stored = (uint32_t)__popc(lo) + (uint32_t)__popc(hi);
+  t.bridges = t.prev = t.last = 0;
+  if constexpr (FMT == 2) {
+    const bool any = (lo | hi) != 0u;
+    const uint32_t loc0 = 64u * (uint32_t)lane;
+    const uint32_t first = loc0 + (lo ? (uint32_t)__builtin_ctz(lo) : 32u + (uint32_t)__builtin_ctz(hi | 0x80000000u));
+    const uint32_t last = loc0 + (hi ? 63u - (uint32_t)__builtin_clz(hi) : 31u - (uint32_t)__builtin_clz(lo | 1u));
+    const uint64_t have = __builtin_amdgcn_ballot_w64(any);
+    const uint64_t below = have & ((1ull << lane) - 1ull);
+    const uint32_t of_lane = (uint32_t)__builtin_amdgcn_ds_bpermute((below ? 63 - __builtin_clzll(below) : 0) * 4, (int)last);
+    t.prev = below ? of_lane : 0u;
+    t.bridges = any && first > t.prev ? (first - t.prev - 1u) / kReach2 : 0u;
+    if (have) t.last = (uint32_t)__builtin_amdgcn_readlane((int)last, 63 - __builtin_clzll(have));
   }
-  t.last = counter;
-  t.entries = 0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const uint32_t incl = wave_inclusive_scan(packed[i]);
-    t.before[i] = incl - packed[i];
-    t.total[i] = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-    t.entries += (t.total[i] & 0x3ffu) + ((t.total[i] >> 10) & 0x3ffu) + (t.total[i] >> 20);
-  }
-  if constexpr (FMT == 2) return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(nz), 63);
-  else return t.entries;
+  return stored + t.bridges;
 }
 
 // A wave's LDS operations execute in order; this keeps the compiler from moving them.
@@ -183,54 +145,70 @@ __device__ __forceinline__ void lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Puts entries [base, base + kStageEntries) of the tile into the wave's stage.  ALL: they are all the tile has.
+// Puts entries [base, base + kStageEntries) of the tile into the wave's stage.  ALL: they are all the tile has.  Per element a
+// compare that switches off the lanes whose element is zero, the step to the lane's next word, and the store, as an asm
+// statement: the compiler puts a branch around such a store, which costs more than the store, and keeps the words of a tile
+// for the rounds of a dense one.
 template <int FMT, bool ALL>
 __device__ __forceinline__ void stage_entries(TileCells& t, unsigned char* stage, uint32_t base, int lane) {
-  // what the count found out element by element, and the locations, are found out again here: kept, they would be a
-  // hundred registers a tile
-  asm volatile("" : "+v"(lane));
-#pragma unroll
-  for (int s = 0; s < kCells; ++s) asm volatile("" : "+v"(t.v[s]));
-  uint32_t* words = (uint32_t*)stage;                       // version 1
-  uint16_t* values = (uint16_t*)stage;                      // version 2
-  uint16_t* locs = (uint16_t*)(stage + kStageLocs);
-  // Every lane stores every element, those that are zero to the slot that nothing reads: a branch around each store
-  // costs more than the store (28672 x 7168 at 80 %: 169.1 us a call with branches, 164.6 without; 12288 x 12288 at 90 % in version 2, where most
-  // branches are those of the bridges: 162.7 and 162.1; repeats differ by half a percent).
-  auto put = [&](bool stored, uint32_t slot, uint32_t bits, uint32_t loc) {
-    const uint32_t at = stored && (ALL || slot < kStageEntries) ? slot : kStageEntries;
-    if constexpr (FMT == 2) {
-      values[at] = (uint16_t)bits;
-      locs[at] = (uint16_t)loc;
-    } else {
-      words[at] = (bits << 16) | loc;
+  uint32_t* words = (uint32_t*)stage;
+  uint32_t slot = t.before - base;
+  if constexpr (FMT == 2)
+    for (uint32_t b = t.bridges, loc = t.prev; b > 0; --b, ++slot) {
+      loc += kReach2;
+      if (ALL || slot < kStageEntries) words[slot] = loc;
     }
-  };
-  uint32_t pos = 0u - base, counter = 0;
+  const uint32_t stage_at = (uint32_t)(uintptr_t)stage;  // LDS addresses are the low 32 bits
+  uint32_t at = slot * 4u - 4u, loc = 64u * (uint32_t)lane, word, to;
+  if (ALL) at += stage_at;
+  const uint64_t all = __builtin_amdgcn_read_exec();
 #pragma unroll
-  for (int s = 0; s < kCells; ++s) {
-    uint32_t slot = pos + field10(t.before, s);
-    const uint32_t loc0 = cell_location(s, lane);
-    if constexpr (FMT == 2) {
-      const bool any = (t.v[s][0] | t.v[s][1] | t.v[s][2] | t.v[s][3]) != 0u;
-      Before b = step_bridges(t.v[s], s, any, counter, lane);
-      for (; b.bridges > 0; --b.bridges) {
-        b.prev += kReach2;
-        put(true, slot++, 0u, b.prev);
-      }
-    }
+  for (int s = 0; s < kCells; ++s)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t bits = half_of(t.v[s], e);
-      put(bits != 0u, slot, bits, loc0 + e);
-      slot += bits != 0u ? 1u : 0u;
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (ALL)
+        asm volatile(
+            "v_lshl_or_b32 %2, %3, 16, %1\n\t"
+            "v_add_u32 %1, 1, %1\n\t"
+            "v_cmpx_ne_u16 vcc, 0, %3\n\t"
+            "v_add_u32 %0, 4, %0\n\t"
+            "ds_write_b32 %0, %2\n\t"
+            "s_mov_b64 exec, %4\n\t"
+            "v_and_or_b32 %2, %3, %5, %1\n\t"
+            "v_add_u32 %1, 1, %1\n\t"
+            "v_cmpx_lt_u32 vcc, %6, %3\n\t"
+            "v_add_u32 %0, 4, %0\n\t"
+            "ds_write_b32 %0, %2\n\t"
+            "s_mov_b64 exec, %4"
+            : "+&v"(at), "+&v"(loc), "=&v"(word)
+            : "v"(t.v[s][i]), "s"(all), "s"(0xffff0000u), "s"(0xffffu)
+            : "vcc", "memory");
+      else
+        asm volatile(
+            "v_lshl_or_b32 %2, %4, 16, %1\n\t"
+            "v_add_u32 %1, 1, %1\n\t"
+            "v_cmpx_ne_u16 vcc, 0, %4\n\t"
+            "v_add_u32 %0, 4, %0\n\t"
+            "v_cmpx_gt_u32 vcc, %8, %0\n\t"
+            "v_add_u32 %3, %9, %0\n\t"
+            "ds_write_b32 %3, %2\n\t"
+            "s_mov_b64 exec, %5\n\t"
+            "v_and_or_b32 %2, %4, %6, %1\n\t"
+            "v_add_u32 %1, 1, %1\n\t"
+            "v_cmpx_lt_u32 vcc, %7, %4\n\t"
+            "v_add_u32 %0, 4, %0\n\t"
+            "v_cmpx_gt_u32 vcc, %8, %0\n\t"
+            "v_add_u32 %3, %9, %0\n\t"
+            "ds_write_b32 %3, %2\n\t"
+            "s_mov_b64 exec, %5"
+            : "+&v"(at), "+&v"(loc), "=&v"(word), "=&v"(to)
+            : "v"(t.v[s][i]), "s"(all), "s"(0xffff0000u), "s"(0xffffu), "s"(kStageEntries * 4u), "s"(stage_at)
+            : "vcc", "memory");
     }
-    pos += field10(t.total, s);
-  }
   // padding: version 1 words of value +0 one past the tile, version 2 entries of value 0 at distance 1
-  const uint32_t slot = t.entries + (uint32_t)lane;
-  if (lane < (int)kPad && slot < (t.entries + kPad - 1) / kPad * kPad)
-    put(true, slot - base, 0u, FMT == 2 ? t.last + 1u + (uint32_t)lane : (uint32_t)kTileElems);
+  slot = t.entries + (uint32_t)lane;
+  if (lane < (int)kPad && slot < (t.entries + kPad - 1) / kPad * kPad && (ALL || slot - base < kStageEntries))
+    words[slot - base] = FMT == 2 ? t.last + 1u + (uint32_t)lane : (uint32_t)kTileElems;
 }
 
 // Copies the staged part of the run to the blob; dst = where the words of entry `base` go.
@@ -240,11 +218,10 @@ __device__ __forceinline__ void flush_stage(const TileCells& t, const unsigned c
   const uint32_t groups = (n + kPad - 1) / kPad;
   for (uint32_t g = (uint32_t)lane; g < groups; g += 64) {
     if constexpr (FMT == 2) {
-      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-      const u32x2 v = *(const u32x2*)(stage + g * 8), l = *(const u32x2*)(stage + kStageLocs + g * 8);
-      const uint32_t l0 = l[0] & 0xffffu, l1 = l[0] >> 16, l2 = l[1] & 0xffffu, l3 = l[1] >> 16;
-      dst[g * 3] = v[0];
-      dst[g * 3 + 1] = v[1];
+      const u32x4 w = ((const u32x4*)stage)[g];
+      const uint32_t l0 = w[0] & 0xffffu, l1 = w[1] & 0xffffu, l2 = w[2] & 0xffffu, l3 = w[3] & 0xffffu;
+      dst[g * 3] = w[0] >> 16 | (w[1] & 0xffff0000u);
+      dst[g * 3 + 1] = w[2] >> 16 | (w[3] & 0xffff0000u);
       dst[g * 3 + 2] = l0 | (l1 - l0) << 12 | (l2 - l1) << 18 | (l3 - l2) << 24;
     } else {
       ((u32x4*)dst)[g] = ((const u32x4*)stage)[g];
@@ -281,15 +258,15 @@ __device__ __forceinline__ uint32_t look_back(const CompressParams& p, uint32_t 
   return sum;
 }
 
-// Near its memory bound in version 1: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 133 us, 4.3 TB/s, where a
-// copy reaches 5.1; version 2 is bound by instructions (12288 x 12288 at 90 % 130 us, 2.7 TB/s; the vector ALUs issue in 72 % of the cycles, in
-// version 1 in 45 %; LDS is busy in 26 and 24 %).  The same work as count, scan and emit kernels that
-// each read W (or its counts) again: 85 + 98 + 269 us and 466 + 66 + 173 us; the whole call 491 -> 165 us and 744 ->
-// 162 us.  Sixteen tiles to a chunk keep the look-back and the ticket rare (one of each per 128 KB of W); eight
-// waves with two tiles each leave room for two workgroups on a CU, one loading while the other writes.
+// Bound by memory, at 0.85 of a copy's rate: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 123 us, 12288 x 12288 at 90 % in version 2
+// (302 in, 45 out) 85 us.  The walk of a lane over 64 consecutive locations takes a third of the vector instructions that one over eight
+// cells strewn over the tile took, with a prefix sum, a search for the element before and a loop for bridges per cell: the whole call 165.7 ->
+// 157.1 us in version 1 and 162.5 -> 118.1 us in version 2, whose vector ALUs were 72 % busy (1509 instructions a tile).  The same work as count, scan
+// and emit kernels that each read W (or its counts) again: 491 and 744 us a call.  Sixteen tiles to a chunk keep the look-back and the ticket rare (one of
+// each per 128 KB of W); eight waves with two tiles each leave room for two workgroups on a CU, one loading while the other writes.
 template <int FMT>
 __global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(CompressParams p) {
-  __shared__ __align__(16) unsigned char stages[kChunkWaves][kStageBytes];
+  __shared__ __align__(16) unsigned char stages[kChunkWaves][kTileBytes];
   __shared__ uint32_t entries_of[kChunkTiles];
   __shared__ uint32_t stored_of[kChunkWaves];
   __shared__ uint32_t ticket, chunk_base;
@@ -299,47 +276,62 @@ __global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(Comp
   // the chip starts them, a workgroup only waits for others that run already.
   if (threadIdx.x == 0) ticket = atomicAdd((uint32_t*)p.out + kHeaderTicket, 1u);
   __syncthreads();
-  const uint32_t q = ticket;
+  const uint32_t q = __builtin_amdgcn_readfirstlane(ticket);
   unsigned char* stage = stages[wave];
 
   // Loads: lane j takes row 16 i + (j >> 2), K chunk j & 3 - a quad reads the 64 contiguous bytes of a row of the tile.
   // The wave's tiles are neighbours in K, two to a 128 B line of W (but at a band's end): the two halves of a line are
-  // asked for one after the other, and the line stays in the caches in between.  (A tile's loads after the other's, and as
-  // non-temporal ones, fetched lines twice: 28672 x 7168 at 80 % 217 us a call against 168, 12288 x 12288 at 90 % in
-  // version 2 187 against 162.)
+  // asked for one after the other, in an order that the compiler is kept from changing, and the line stays in the caches in between.  (All
+  // loads of a tile before the other's: 160.5 us against 157.1 for 28672 x 7168 at 80 %, 124.4 against 118.1 for 12288 x 12288 at 90 % in
+  // version 2; as non-temporal ones, which fetch lines twice, a third slower.)
   TileCells t[kTilesPerWave];
-  const uint16_t* src[kTilesPerWave];
-  bool live[kTilesPerWave];
+  // (A tile past the last one has an empty descriptor: its loads return 0.)
+  __amdgpu_buffer_rsrc_t src[kTilesPerWave];
+  uint32_t at[kTilesPerWave];
 #pragma unroll
   for (int a = 0; a < kTilesPerWave; ++a) {
-    const uint32_t tile = q * kChunkTiles + wave * kTilesPerWave + a;
-    live[a] = tile < p.T;
-    const uint32_t ta = live[a] ? tile : 0u;
-    const uint32_t band = ta / p.KT, kt = ta - band * p.KT;
-    src[a] = p.W + ((size_t)band * kTileM + (lane >> 2)) * p.K + kt * kTileK + (lane & 3) * 8;
+    const uint32_t tile = q * kChunkTiles + wave * kTilesPerWave + a, live = tile < p.T ? tile : 0u;
+    const uint32_t band = live / p.KT, kt = live - band * p.KT;
+    src[a] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.W + (size_t)band * kTileM * p.K), 0,
+                                               tile < p.T ? (int)(kTileM * 2u * p.K) : 0, kBufferFlags);
+    at[a] = ((lane >> 2) * p.K + kt * kTileK + (lane & 3) * 8) * 2u;
   }
 #pragma unroll
-  for (int i = 0; i < kCells; ++i)
+  for (int i = 0; i < kCells; ++i) {
 #pragma unroll
-    for (int a = 0; a < kTilesPerWave; ++a)
-      t[a].v[i] = live[a] ? *(const u32x4*)(src[a] + (size_t)i * 16 * p.K) : u32x4{0u, 0u, 0u, 0u};
-  // ... and through LDS into the order of the walk.  Slot of cell (row, K chunk c): 128 c + (row ^ 4 c); any 16
-  // neighbouring lanes touch 16 different 16 B bank groups, both ways.
-  uint32_t stored = 0;
+    for (int a = 0; a < kTilesPerWave; ++a) t[a].v[i] = __builtin_amdgcn_raw_buffer_load_b128(src[a], at[a], i * 32u * p.K, 0);
+    __builtin_amdgcn_sched_barrier(0);  // in this order
+  }
+  // ... and through LDS into the order of the walk.  Cell (row, K chunk c), row bits b6 ... b0, is in slot
+  // ((c, b6 b5, b2), c ^ b4 b3, b1 b0 ^ b6 b5): any 16 neighbouring lanes touch 16 different 16 B bank groups, both ways.
+  uint32_t entries[kTilesPerWave], stored[kTilesPerWave];
+  const uint32_t c = lane & 3, r = lane >> 2, h = (lane >> 2) & 3;  // store: K chunk, row in its 16; read: b6 b5 of the lane's rows
+  const uint32_t put_at = ((c * 8 + ((r >> 2) & 1)) * 16 + (c ^ (r >> 3)) * 4 + (r & 3)) * 16;
+  const uint32_t get_at = (((lane >> 4) * 8 + h * 2) * 16 + ((lane >> 4) ^ (lane & 3)) * 4) * 16;
 #pragma unroll
   for (int a = 0; a < kTilesPerWave; ++a) {
-    const uint32_t c = lane & 3;
 #pragma unroll
-    for (int i = 0; i < kCells; ++i) *(u32x4*)(stage + (c * kTileM + ((16u * i + (lane >> 2)) ^ (4u * c))) * 16) = t[a].v[i];
+    for (int i = 0; i < kCells; ++i) *(u32x4*)(stage + ((put_at ^ ((i & 1) * 128u + (i >> 1) * 16u)) + (i >> 1) * 512u)) = t[a].v[i];
     lds_order();
 #pragma unroll
-    for (int s = 0; s < kCells; ++s)
-      t[a].v[s] = *(const u32x4*)(stage + ((s >> 1) * kTileM + ((uint32_t)(s & 1) * 64 + ((uint32_t)lane ^ (4u * (s >> 1))))) * 16);
+    for (int i = 0; i < kCells; ++i) t[a].v[i] = *(const u32x4*)(stage + get_at + (i >> 2) * 256u + (((i & 3) ^ h) * 16u));
     lds_order();
-    stored += count_tile<FMT>(t[a], lane);
-    if (lane == 0) entries_of[wave * kTilesPerWave + a] = t[a].entries;
+    entries[a] = count_lane<FMT>(t[a], stored[a], lane);
   }
-  if (lane == 0) stored_of[wave] = stored;
+  // both tiles in one prefix sum: a tile has at most 4096 stored elements and 65 bridges
+  static_assert(kTilesPerWave == 2, "two sums of 16 bits to a word");
+  const uint32_t incl = wave_inclusive_scan(entries[0] | entries[1] << 16), sums = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  t[0].before = (incl & 0xffffu) - entries[0];
+  t[1].before = (incl >> 16) - entries[1];
+  t[0].entries = sums & 0xffffu;
+  t[1].entries = sums >> 16;
+  uint32_t wave_stored = t[0].entries + t[1].entries;
+  if constexpr (FMT == 2) {
+    const uint32_t bridges = t[0].bridges + t[1].bridges;
+    if (__builtin_amdgcn_ballot_w64(bridges != 0u) != 0u) wave_stored -= (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(bridges), 63);
+  }
+  if (lane < kTilesPerWave) entries_of[wave * kTilesPerWave + lane] = lane == 0 ? t[0].entries : t[1].entries;
+  if (lane == 0) stored_of[wave] = wave_stored;
   __syncthreads();
 
   // the chunk's sum goes out first, its place is looked up after the first tile has been compacted

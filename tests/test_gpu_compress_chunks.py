@@ -59,3 +59,24 @@ def test_too_small_buffer_is_not_overrun(fls, version):
         assert e.value.code == fls.ECAPACITY
         assert bool((buf[room:] == 0xA5).all())
     assert compress(W, torch.empty(size, dtype=torch.uint8, device="cuda"))[1]["bytes_total"] == size
+
+
+@pytest.mark.parametrize("version", [1, 2])
+def test_lane_edges(fls, oracle_mod, version):
+    """A lane walks 64 consecutive locations in two words of 32: one to four elements a tile around those edges, gaps about the
+    63 locations that a distance reaches, in either half of a word of W, among them bit patterns with an empty byte."""
+    g = np.random.Generator(np.random.Philox(21))
+    bands, kt = 6, 96
+    flat = np.zeros((bands * kt, 4096), dtype=np.uint16)
+    values = np.array([0x8000, 0x0001, 0x00FF, 0x0100, 0xFF00, 0xFFFF, 0x7C00], dtype=np.uint16)
+    for t in flat:
+        at = int(g.choice([0, 1, 31, 32, 33, 62, 63, 64, 65, 127, 128, 4032, 4094, 4095])) if g.random() < 0.5 else int(g.integers(4096))
+        for _ in range(int(g.integers(0, 5))):
+            t[at % 4096] = g.choice(values)
+            at += int(g.choice([1, 2, 31, 32, 62, 63, 64, 65, 126, 127, 128, 190, 1000, 3969]))
+    # location l of a tile is row (l % 1024) // 8, column 8 * (l // 1024) + l % 8
+    tiles = flat.reshape(bands, kt, 4, 128, 8).transpose(0, 3, 1, 2, 4)
+    W = np.ascontiguousarray(tiles.reshape(bands * 128, kt * 32))
+    blob, st = (fls.fls_compress_v2 if version == 2 else fls.fls_compress)(_dev(W))
+    assert np.array_equal(blob.cpu().numpy(), (oracle_mod.ref_compress_v2 if version == 2 else oracle_mod.ref_compress)(W))
+    assert st["nnz"] == int(np.count_nonzero(W))
