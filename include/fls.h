@@ -97,10 +97,11 @@ int fls_compress_bound(int64_t M, int64_t K, size_t* bytes_host);
  *   stats_host   out: may be NULL; filled on FLS_OK; on FLS_ECAPACITY bytes_total holds a size that is enough
  *                     (the exact size once the tiles are counted, the worst-case bound if out_capacity
  *                     did not even hold header and TileOffsets)
- * The result is a pure function of (W bits, M, K, order_policy).  Waits for its own kernels.  On FLS_ECAPACITY
+ * The result is a pure function of (W bits, M, K, order_policy).  Waits for its own kernel.  On FLS_ECAPACITY
  * the contents of out_dev are unspecified (nothing past out_capacity is written).
- * Uses the start of out_dev as scratch, so out_capacity must cover header and TileOffsets even
- * for an all-zero matrix.  Errors: FLS_EINVAL, FLS_EALIGN, FLS_ECAPACITY, FLS_EHIP.
+ * out_capacity must cover header and TileOffsets even for an all-zero matrix.  The scratch is a static device array
+ * inside the library (16.8 MB on every GPU it runs on, places for 16 calls at once: a call of a seventeenth thread waits
+ * for one), and 128 KB of pinned host memory, allocated with the first call, receive the header.  Errors: FLS_EINVAL, FLS_EALIGN, FLS_ECAPACITY, FLS_EHIP.
  */
 int fls_compress(const void* W_dev, int64_t M, int64_t K, void* out_dev, size_t out_capacity,
                  int order_policy, fls_stats* stats_host, fls_stream_t stream);

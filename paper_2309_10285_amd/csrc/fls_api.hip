@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <unordered_map>
@@ -58,6 +59,82 @@ unsigned char* scratch_on_current_device(int* err) {
   }
   return g_scratch_ptr[dev];
 }
+
+// Scratch of fls_compress: a device array like the one above and a piece of pinned host memory for what the call returns
+// (allocated with the first call).  A call takes one of the kCompressSlots places of its device for its duration - it waits for its kernel -
+// and calls of other threads take others; when all are taken a call waits for one.
+constexpr int kCompressSlots = 16;
+static __device__ __align__(256) __attribute__((used)) unsigned char compress_scratch[kCompressSlots * sizeof(fls::CompressScratch)];
+struct CompressSlot {
+  bool busy = false;
+  bool dirty = false;  // a call on it failed: cleared before the next one
+  uint32_t calls = 0;
+};
+CompressSlot g_compress_slots[kMaxDevices][kCompressSlots];  // guarded by g_mu, as the next two
+fls::CompressScratch* g_compress_ptr[kMaxDevices] = {};
+fls::CompressHost* g_compress_host = nullptr;  // kMaxDevices x kCompressSlots
+std::condition_variable g_compress_free;
+
+// One call's place in it.
+struct CompressPlace {
+  int dev = -1, slot = -1;
+  bool failed = true;  // until the call says otherwise
+  fls::CompressScratch* scratch = nullptr;
+  fls::CompressHost *host = nullptr, *host_on_device = nullptr;
+  uint32_t call = 0;
+
+  bool take(hipStream_t stream) {
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+    bool clear = false;
+    {
+      std::unique_lock<std::mutex> lk(g_mu);
+      if (!g_compress_ptr[dev]) {
+        void* ptr = nullptr;
+        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(compress_scratch)) != hipSuccess || !ptr) return false;
+        g_compress_ptr[dev] = (fls::CompressScratch*)ptr;
+      }
+      if (!g_compress_host) {
+        void* ptr = nullptr;
+        if (hipHostMalloc(&ptr, sizeof(fls::CompressHost) * kMaxDevices * kCompressSlots, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) !=
+            hipSuccess)
+          return false;
+        g_compress_host = (fls::CompressHost*)ptr;
+      }
+      for (;;) {
+        for (int i = 0; i < kCompressSlots && slot < 0; ++i)
+          if (!g_compress_slots[dev][i].busy) slot = i;
+        if (slot >= 0) break;
+        g_compress_free.wait(lk);
+      }
+      CompressSlot& s = g_compress_slots[dev][slot];
+      s.busy = true;
+      clear = s.dirty || s.calls + 1 == fls::kCompressCalls;
+      if (clear) s.calls = 0;
+      s.dirty = false;
+      call = ++s.calls;
+      scratch = g_compress_ptr[dev] + slot;
+      host = g_compress_host + dev * kCompressSlots + slot;
+    }
+    memset(host, 0, sizeof(*host));
+    void* ptr = nullptr;
+    if (hipHostGetDevicePointer(&ptr, host, 0) != hipSuccess) return false;
+    host_on_device = (fls::CompressHost*)ptr;
+    return !clear || fls::launch_fill_zero(scratch, sizeof(*scratch), stream) == hipSuccess;
+  }
+  ~CompressPlace() {
+    if (slot < 0) return;
+    {
+      std::lock_guard<std::mutex> lk(g_mu);
+      g_compress_slots[dev][slot].dirty = failed;
+      g_compress_slots[dev][slot].busy = false;
+    }
+    g_compress_free.notify_all();
+  }
+};
+
+// Looks of a waiting compress workgroup (a microsecond or more each): a tenth of a second before the call is made again with chunks
+// by ticket, some seconds then.
+constexpr uint32_t kLookLimitByNumber = 1u << 16, kLookLimit = 1u << 22;
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -168,7 +245,7 @@ int fls_inspect(const void* header_host, fls_stats* stats_host) {
 }
 
 static int compress_impl(const void* W_dev, int64_t M, int64_t K, void* out_dev, size_t out_capacity, int order_policy,
-                         uint32_t version, fls_stats* stats_host, fls_stream_t stream) {
+                         uint32_t version, fls_stats* stats_host, fls_stream_t stream, uint32_t look_limit = kLookLimitByNumber) {
   if (!W_dev || !out_dev || !shape_ok(M, K)) return FLS_EINVAL;
   if (order_policy != FLS_ORDER_LOCATION) return FLS_EINVAL;  // FLS_ORDER_BANK: not built yet
   if (!aligned16(W_dev) || !aligned16(out_dev)) return FLS_EALIGN;
@@ -198,10 +275,25 @@ static int compress_impl(const void* W_dev, int64_t M, int64_t K, void* out_dev,
     std::lock_guard<std::mutex> lk(g_mu);
     g_blobs.erase(out_dev);
   }
-  if (fls::launch_compress(a, s) != hipSuccess) return FLS_EHIP;
   unsigned char hdr[FLS_HEADER_BYTES];
-  if (hipMemcpyAsync(hdr, out_dev, FLS_HEADER_BYTES, hipMemcpyDeviceToHost, s) != hipSuccess) return FLS_EHIP;
-  if (hipStreamSynchronize(s) != hipSuccess) return FLS_EHIP;
+  a.look_limit = look_limit;
+  a.by_ticket = false;
+  for (;;) {
+    CompressPlace place;
+    if (!place.take(s)) return FLS_EHIP;
+    a.scratch = place.scratch;
+    a.host = place.host_on_device;
+    a.call = place.call;
+    if (fls::launch_compress(a, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return FLS_EHIP;
+    if (!place.host->gave_up) {
+      place.failed = false;
+      memcpy(hdr, place.host->header, sizeof(hdr));
+      break;
+    }
+    if (a.by_ticket) return FLS_EHIP;
+    a.look_limit = kLookLimit;
+    a.by_ticket = true;  // workgroups did not start in the order of their numbers
+  }
   fls_stats st;
   BlobInfo info;
   if (parse_header(hdr, &st, &info) != FLS_OK) return FLS_EHIP;  // our own kernels wrote it
@@ -452,6 +544,13 @@ void fls_internal_spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t 
   out[1] = plan.share;
   out[2] = plan.rounds;
   out[3] = plan.slices;
+}
+
+// fls_compress (version 1 or 2) whose kernel gives up at the first word that another workgroup has not published yet, so that it
+// is run again with chunks by ticket.  For tests, not part of the C ABI.
+int fls_internal_compress_impatient(const void* W_dev, int64_t M, int64_t K, void* out_dev, size_t out_capacity, uint32_t version,
+                                    fls_stats* stats_host, fls_stream_t stream) {
+  return compress_impl(W_dev, M, K, out_dev, out_capacity, FLS_ORDER_LOCATION, version, stats_host, stream, 1u);
 }
 
 const char* fls_strerror(int code) {

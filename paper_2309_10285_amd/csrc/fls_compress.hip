@@ -1,13 +1,11 @@
 // fls_compress: dense masked W -> Tiled-CSL blob on the GPU (the paper's offline weight
 // reformatting step, Sec. 5; format Sec. 4.3.1-4.3.2; tile walk of Alg. 3), both format versions.
 //
-// All integer work on fp16 bit patterns (no value passes through a float op).  W is read from memory
+// All integer work on fp16 bit patterns (no value passes through a float op).  One kernel that reads W from memory
 // once: a workgroup takes a chunk of 16 consecutive tiles, holds it in registers, counts it, learns
 // where its words start from the chunks before it while they are still at work (a scan by look-back over
-// published chunk sums), and writes the words.  Two kernels:
-//   emit   : everything but the index; leaves the chunk's running sum and its tiles' counts in the
-//            place of the chunk's own TileOffsets entries
-//   finish : turns those into TileOffsets, fills the guard entries and writes the header
+// published chunk sums), and writes its TileOffsets and words.  The header's sums meet in the scratch of the call; the workgroup that
+// adds the last chunk's writes the header, to the blob and to host memory that the caller waits for anyway.
 // Format version 1: an entry is a stored element, one 32-bit word (value, location), runs padded to a
 // multiple of four.  Format version 2, three bytes per entry: a tile's entries, in ascending location, go in
 // groups of four that take three words - two of values, one with the first entry's location in
@@ -32,27 +30,34 @@ constexpr int kCells = kTileElems / 8 / 64;  // (row, K chunk) cells of a tile t
 // out in two rounds.
 constexpr uint32_t kStageEntries = 2048;
 
-// Where chunk q's state stands until the finish kernel runs: in words 16 q ... 16 q + 9 of TileOffsets (n_off
-// is a multiple of 16 and at least T + 4, so the last, partly empty chunk has room too).
-//   words 0, 1  running sum of words in bits 0 - 31, the chunk's stored elements in bits 32 - 48, kState* in bits 62 - 63
-//   words 2 - 9 entries of its 16 tiles, 16 bits each
+// A chunk's words in the scratch, with the call's number in bits 32 - 61; those of an earlier call count as missing.
+//   sums:   words in bits 0 - 31, kState* in bits 62 - 63
+//   counts: stored elements in bits 0 - 16, words of its longest tile in bits 17 - 29
 constexpr uint64_t kStateSum = 1ull << 62;     // the sum is the chunk's own
 constexpr uint64_t kStatePrefix = 2ull << 62;  // the sum is that of all chunks up to and including this one
-static_assert(kChunkTiles == 16, "the state of a chunk stands in the place of its 16 offsets");
-
-constexpr int kHeaderTicket = 7;   // header word: next chunk to be taken (0 again in a finished blob)
-constexpr int kHeaderGaveUp = 15;  // header word (upper half of total_words): 1 if a look-back gave up
+constexpr uint64_t kStateCounts = 3ull << 62;
+constexpr int kCountsLongest = 17;
+static_assert(kChunkTiles == kCompressChunkTiles, "the scratch has words for every chunk of the largest matrix");
 
 struct CompressParams {
   const uint16_t* W;
   unsigned char* out;
+  CompressScratch* scratch;
+  CompressHost* host;
   uint64_t capacity_words;  // words that fit behind TileOffsets
-  uint32_t M, K, KT, T, n_off, policy;
+  uint32_t M, K, KT, T, n_off, policy, chunks;
+  uint32_t call;            // number of the call on this scratch
+  uint32_t look_limit;      // looks at a word that another workgroup publishes, before a workgroup gives up
+  bool by_ticket;
 };
 
 __device__ __forceinline__ uint32_t* offs_of(const CompressParams& p) { return (uint32_t*)(p.out + 64); }
 __device__ __forceinline__ uint32_t* words_of(const CompressParams& p) { return (uint32_t*)(p.out + 64 + 4 * (size_t)p.n_off); }
-__device__ __forceinline__ uint64_t* state_of(const CompressParams& p, uint32_t q) { return (uint64_t*)(p.out + 64 + (size_t)q * 64); }
+__device__ __forceinline__ void publish(const CompressParams& p, uint64_t* to, uint64_t kind, uint32_t value) {
+  __hip_atomic_store(to, kind | (uint64_t)p.call << 32 | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t published(const uint64_t* from) { return __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ bool of_call(const CompressParams& p, uint64_t word) { return ((uint32_t)(word >> 32) & 0x3fffffffu) == p.call; }
 
 template <int FMT>
 __device__ __forceinline__ uint32_t run_words(uint32_t entries) {
@@ -67,12 +72,6 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
   v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
   v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
   v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
-__device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
   return v;
 }
 
@@ -211,10 +210,9 @@ __device__ __forceinline__ void stage_entries(TileCells& t, unsigned char* stage
     words[slot - base] = FMT == 2 ? t.last + 1u + (uint32_t)lane : (uint32_t)kTileElems;
 }
 
-// Copies the staged part of the run to the blob; dst = where the words of entry `base` go.
+// Copies n staged entries and their padding to the blob.
 template <int FMT>
-__device__ __forceinline__ void flush_stage(const TileCells& t, const unsigned char* stage, uint32_t base, uint32_t* dst, int lane) {
-  const uint32_t left = t.entries - base, n = left < kStageEntries ? left : kStageEntries;
+__device__ __forceinline__ void flush_stage(uint32_t n, const unsigned char* stage, uint32_t* dst, int lane) {
   const uint32_t groups = (n + kPad - 1) / kPad;
   for (uint32_t g = (uint32_t)lane; g < groups; g += 64) {
     if constexpr (FMT == 2) {
@@ -232,19 +230,17 @@ __device__ __forceinline__ void flush_stage(const TileCells& t, const unsigned c
 // Words of all chunks before chunk q.  Run by one whole wave; q's own sum is published.  Each look takes the
 // states of 64 chunks, nearest first, and ends at the nearest one that knows its prefix already.
 __device__ __forceinline__ uint32_t look_back(const CompressParams& p, uint32_t q, int lane) {
-  constexpr uint32_t kLookLimit = 1u << 22;
   uint32_t sum = 0, looks = 0;
   for (uint32_t top = q; top > 0;) {
-    uint64_t st = kStatePrefix;  // before the first chunk: nothing
-    if ((uint32_t)lane < top)
-      st = __hip_atomic_load(state_of(p, top - 1u - (uint32_t)lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t prefix = __builtin_amdgcn_ballot_w64((st & kStatePrefix) != 0);
-    const uint64_t missing = __builtin_amdgcn_ballot_w64((st >> 62) == 0);
+    uint64_t st = kStatePrefix | (uint64_t)p.call << 32;  // before the first chunk: nothing
+    if ((uint32_t)lane < top) st = published(p.scratch->sums + (top - 1u - (uint32_t)lane));
+    const bool known = of_call(p, st);
+    const uint64_t prefix = __builtin_amdgcn_ballot_w64(known && (st & kStatePrefix) != 0);
+    const uint64_t missing = __builtin_amdgcn_ballot_w64(!known);
     const int end = prefix ? __builtin_ctzll(prefix) : 63;  // last lane that counts
     if (missing & (~0ull >> (63 - end))) {
-      // chunks are taken in order, so every chunk before this one is being worked on and the wait ends; bounded all the same
-      if (++looks == kLookLimit) {
-        if (lane == 0) __hip_atomic_store((uint32_t*)p.out + kHeaderGaveUp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (++looks == p.look_limit) {
+        if (lane == 0) p.host->gave_up = 1u;
         return sum;
       }
       __builtin_amdgcn_s_sleep(1);
@@ -258,25 +254,95 @@ __device__ __forceinline__ uint32_t look_back(const CompressParams& p, uint32_t 
   return sum;
 }
 
-// Bound by memory, at 0.85 of a copy's rate: 28672 x 7168 at 80 % (411 MB in, 164 MB out) 123 us, 12288 x 12288 at 90 % in version 2
-// (302 in, 45 out) 85 us.  The walk of a lane over 64 consecutive locations takes a third of the vector instructions that one over eight
-// cells strewn over the tile took, with a prefix sum, a search for the element before and a loop for bridges per cell: the whole call 165.7 ->
-// 157.1 us in version 1 and 162.5 -> 118.1 us in version 2, whose vector ALUs were 72 % busy (1509 instructions a tile).  The same work as count, scan
-// and emit kernels that each read W (or its counts) again: 491 and 744 us a call.  Sixteen tiles to a chunk keep the look-back and the ticket rare (one of
-// each per 128 KB of W); eight waves with two tiles each leave room for two workgroups on a CU, one loading while the other writes.
+// By the last chunk's workgroup, the one that finds all others at work or done: what all chunks counted, and the header.  (All
+// workgroups adding to one address took 5 % of a large call, looks at one address as much again.)
 template <int FMT>
-__global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(CompressParams p) {
+__device__ __forceinline__ void finish_header(const CompressParams& p, uint32_t total_words, uint32_t* of_wave, uint32_t wave, int lane) {
+  uint32_t stored = 0, longest = 0;  // (2^16 chunks of 2^16 elements: a thread's part is at most 2^24)
+  for (uint32_t c0 = threadIdx.x; c0 < p.chunks; c0 += 4u * kChunkWaves * 64) {
+    uint64_t w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t c = c0 + j * (kChunkWaves * 64);
+      w[j] = published(p.scratch->counts + (c < p.chunks ? c : c0));
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t c = c0 + j * (kChunkWaves * 64);
+      if (c >= p.chunks) continue;
+      uint32_t looks = 0;
+      while (!of_call(p, w[j])) {
+        if (++looks == p.look_limit) {
+          p.host->gave_up = 1u;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+        w[j] = published(p.scratch->counts + c);
+      }
+      stored += (uint32_t)w[j] & ((1u << kCountsLongest) - 1u);
+      const uint32_t l = ((uint32_t)w[j] & 0x3fffffffu) >> kCountsLongest;
+      longest = l > longest ? l : longest;
+    }
+  }
+  uint64_t nnz = (uint64_t)stored;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    nnz += __shfl_xor(nnz, d, 64);
+    const uint32_t l = (uint32_t)__shfl_xor((int)longest, d, 64);
+    longest = l > longest ? l : longest;
+  }
+  if (lane == 0) {
+    of_wave[3 * wave] = (uint32_t)nnz;
+    of_wave[3 * wave + 1] = (uint32_t)(nnz >> 32);
+    of_wave[3 * wave + 2] = longest;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  nnz = 0;
+  for (int i = 0; i < kChunkWaves; ++i) {
+    nnz += (uint64_t)of_wave[3 * i + 1] << 32 | of_wave[3 * i];
+    longest = of_wave[3 * i + 2] > longest ? of_wave[3 * i + 2] : longest;
+  }
+  const uint32_t h[kHeaderWords] = {FMT == 2 ? kMagic2 : kMagic, FMT, (uint32_t)kTileM, (uint32_t)kTileK, kPad, p.policy, longest, 0u,
+                                    p.M, 0u, p.K, 0u, (uint32_t)nnz, (uint32_t)(nnz >> 32), total_words, 0u};
+#pragma unroll
+  for (int i = 0; i < kHeaderWords; ++i) {
+    ((uint32_t*)p.out)[i] = h[i];
+    p.host->header[i] = h[i];
+  }
+  if (p.by_ticket) p.scratch->ticket = 0u;  // every workgroup has taken its own
+}
+
+// Near its memory bound: with the place of a chunk's words a constant, no look back, whole calls take 135 us (28672 x 7168 at 80 %: 411 MB in,
+// 164 MB out) and 94 us (12288 x 12288 at 90 % in version 2: 302 and 45), some 17 us of each the host's; with the look back 145.5 and 94.5.  What it came from:
+//  - three and four kernels that each read W or its counts again: 491 and 744 us;
+//  - this kernel between a fill of the index, a kernel for offsets and header, and a copy of the header to the host, each lane walking eight
+//    cells strewn over a tile with a prefix sum, a search for the element before and a loop for bridges per cell: 165.7 and 162.5 us, the vector ALUs
+//    72 % busy in version 2 (1509 instructions a tile);
+//  - a lane walking 64 consecutive locations: 157.1 and 118.1 us;
+//  - one kernel and a header in host memory: 151.1 and 107.1 us;
+//  - no address that all workgroups add to or look at (16 ns each, one after the other), both tiles of a wave in one run: 145.5 and 94.5 us.
+// Sixteen tiles to a chunk keep the look-back rare (eight: 166 and 123 us; 256 instead of 64 chunks to a look 164 and 111); eight waves with two tiles
+// each leave room for two workgroups on a CU, one loading while the other writes.
+template <int FMT>
+__global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_kernel(CompressParams p) {
   __shared__ __align__(16) unsigned char stages[kChunkWaves][kTileBytes];
   __shared__ uint32_t entries_of[kChunkTiles];
   __shared__ uint32_t stored_of[kChunkWaves];
-  __shared__ uint32_t ticket, chunk_base;
+  __shared__ uint32_t ticket, chunk_base, total_words;
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // Chunks are numbered in the order in which workgroups start, not by workgroup id: whatever the order in which
-  // the chip starts them, a workgroup only waits for others that run already.
-  if (threadIdx.x == 0) ticket = atomicAdd((uint32_t*)p.out + kHeaderTicket, 1u);
-  __syncthreads();
-  const uint32_t q = __builtin_amdgcn_readfirstlane(ticket);
+  // A workgroup waits for the chunks before its own.  By number, chunk = workgroup: the chip starts workgroups in the order of their
+  // numbers, so those run or have run; but nothing promises that order, and where one waits in vain it gives up after p.look_limit looks.  By
+  // ticket, chunks are numbered in the order in which workgroups start, so whatever that is, the wait ends; the host
+  // takes this way only when the other gave up, because all workgroups adding to one address delays the first ones: 28672 x 7168 at 80 % 145.5 us by
+  // number, 146.8 by ticket, 12288 x 12288 at 90 % in version 2 94.5 and 103.3, 22656 x 2112 at 76 % in version 2 48.2 and 56.2.
+  uint32_t q = blockIdx.x;
+  if (p.by_ticket) {
+    if (threadIdx.x == 0) ticket = atomicAdd(&p.scratch->ticket, 1u);
+    __syncthreads();
+    q = __builtin_amdgcn_readfirstlane(ticket);
+  }
   unsigned char* stage = stages[wave];
 
   // Loads: lane j takes row 16 i + (j >> 2), K chunk j & 3 - a quad reads the 64 contiguous bytes of a row of the tile.
@@ -334,109 +400,73 @@ __global__ __launch_bounds__(kChunkWaves * 64, 4) void compress_emit_kernel(Comp
   if (lane == 0) stored_of[wave] = wave_stored;
   __syncthreads();
 
-  // the chunk's sum goes out first, its place is looked up after the first tile has been compacted
-  uint32_t words = 0, chunk_words = 0, nz = 0;
+  // The chunk's sum and counts go out first; its place is looked up after the wave's tiles have been compacted, one behind the other
+  // (the first of them, if they have more entries than the stage holds).
+  uint32_t words = 0, incl_words = 0;
   if (wave == 0) {
-    const uint32_t mine = lane < kChunkTiles ? entries_of[lane] : 0u;
-    words = run_words<FMT>(mine);
-    chunk_words = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(words), 63);
-    nz = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(lane < kChunkWaves ? stored_of[lane] : 0u), 63);
-    if (lane == 0)
-      __hip_atomic_store(state_of(p, q), (q == 0 ? kStatePrefix : kStateSum) | (uint64_t)nz << 32 | chunk_words, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t next = (uint32_t)__shfl_down((int)mine, 1, 64);
-    if (lane < kChunkTiles && (lane & 1) == 0) offs_of(p)[(size_t)q * kChunkTiles + 2 + lane / 2] = mine | next << 16;
-  }
-  if (t[0].entries <= kStageEntries) stage_entries<FMT, true>(t[0], stage, 0, lane);
-  if (wave == 0) {
-    const uint32_t before = look_back(p, q, lane);
-    if (lane == 0) {
-      if (q != 0)
-        __hip_atomic_store(state_of(p, q), kStatePrefix | (uint64_t)nz << 32 | (uint64_t)(before + chunk_words), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-      chunk_base = before;
+    words = run_words<FMT>(lane < kChunkTiles ? entries_of[lane] : 0u);
+    incl_words = wave_inclusive_scan(words);
+    const uint32_t nz = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(lane < kChunkWaves ? stored_of[lane] : 0u), 63);
+    uint32_t longest = words;  // of 16 lanes
+#pragma unroll
+    for (int d = kChunkTiles / 2; d >= 1; d >>= 1) {
+      const uint32_t v = (uint32_t)__shfl_xor((int)longest, d, 64);
+      longest = v > longest ? v : longest;
     }
+    if (lane == 0) {
+      publish(p, p.scratch->sums + q, q == 0 ? kStatePrefix : kStateSum, (uint32_t)__builtin_amdgcn_readlane((int)incl_words, 63));
+      publish(p, p.scratch->counts + q, kStateCounts, nz | longest << kCountsLongest);
+    }
+  }
+  const uint32_t padded0 = (t[0].entries + kPad - 1) / kPad * kPad, padded1 = (t[1].entries + kPad - 1) / kPad * kPad;
+  const bool together = padded0 + padded1 <= kStageEntries;
+  if (t[0].entries <= kStageEntries) stage_entries<FMT, true>(t[0], stage, 0, lane);
+  if (together) stage_entries<FMT, true>(t[1], stage + padded0 * 4u, 0, lane);
+  if (wave == 0) {
+    const uint32_t before = look_back(p, q, lane), chunk_words = (uint32_t)__builtin_amdgcn_readlane((int)incl_words, 63);
+    if (lane == 0) {
+      if (q != 0) publish(p, p.scratch->sums + q, kStatePrefix, before + chunk_words);
+      chunk_base = before;
+      total_words = before + chunk_words;
+    }
+    // TileOffsets of the chunk's tiles; behind the last tile, up to the end (at most 16 entries past the last chunk's), the total
+    const uint32_t off = q * kChunkTiles + (uint32_t)lane;
+    if (lane < kChunkTiles || (q + 1 == p.chunks && off < p.n_off))
+      offs_of(p)[off] = before + (lane < kChunkTiles ? incl_words - words : chunk_words);
   }
   __syncthreads();
 
   uint32_t begin = chunk_base;
   for (uint32_t j = 0; j < wave * kTilesPerWave; ++j) begin += run_words<FMT>(entries_of[j]);
-#pragma unroll
-  for (int a = 0; a < kTilesPerWave; ++a) {
-    const uint32_t n = t[a].entries, end = begin + run_words<FMT>(n);
-    uint32_t* dst = words_of(p) + begin;
-    const bool fits = (uint64_t)begin + (end - begin) <= p.capacity_words;  // (a buffer that turns out too small gets the tiles that fit)
-    if (n <= kStageEntries) {
-      if (a > 0) stage_entries<FMT, true>(t[a], stage, 0, lane);
-      lds_order();
-      if (fits) flush_stage<FMT>(t[a], stage, 0, dst, lane);
-    } else {
-      for (uint32_t base = 0; base < n; base += kStageEntries) {
-        stage_entries<FMT, false>(t[a], stage, base, lane);
-        lds_order();
-        if (fits) flush_stage<FMT>(t[a], stage, base, dst + run_words<FMT>(base), lane);
-        lds_order();
-      }
-    }
+  // (a buffer that turns out too small gets the tiles that fit)
+  auto fits = [&](uint32_t words) { return (uint64_t)begin + words <= p.capacity_words; };
+  const uint32_t words0 = run_words<FMT>(t[0].entries), words1 = run_words<FMT>(t[1].entries);
+  if (together && fits(words0 + words1)) {
     lds_order();
-    begin = end;
-  }
-}
-
-// A thread per chunk: its state -> its TileOffsets (nothing of another chunk's is read).
-template <int FMT>
-__global__ __launch_bounds__(256) void compress_finish_kernel(CompressParams p) {
-  const uint32_t q = blockIdx.x * 256 + threadIdx.x, chunks = (p.T + kChunkTiles - 1) / kChunkTiles;
-  uint32_t* h = (uint32_t*)p.out;
-  uint64_t stored = 0;
-  uint32_t longest = 0;
-  if (q < chunks) {
-    u32x4* cell = (u32x4*)(offs_of(p) + (size_t)q * kChunkTiles);
-    u32x4 in[3], o[4];
+    flush_stage<FMT>(padded0 + padded1, stage, words_of(p) + begin, lane);
+  } else {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) in[i] = cell[i];
-    const uint64_t st = (uint64_t)in[0][1] << 32 | in[0][0];
-    stored = (st >> 32) & 0x1ffffu;
-    uint32_t w[kChunkTiles], sum = 0;
-#pragma unroll
-    for (int j = 0; j < kChunkTiles; ++j) {
-      const uint32_t pair = in[(2 + j / 2) / 4][(2 + j / 2) % 4];
-      w[j] = run_words<FMT>((j & 1) ? pair >> 16 : pair & 0xffffu);
-      sum += w[j];
-      longest = w[j] > longest ? w[j] : longest;
-    }
-    uint32_t run = (uint32_t)st - sum;
-#pragma unroll
-    for (int j = 0; j < kChunkTiles; ++j) {
-      o[j / 4][j % 4] = run;  // the tiles past the end of a last, partly empty chunk have no words: their entries are the total
-      run += w[j];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) cell[i] = o[i];
-    if (q + 1 == chunks) {
-      for (uint32_t i = chunks * kChunkTiles; i < p.n_off; ++i) offs_of(p)[i] = run;
-      h[0] = FMT == 2 ? kMagic2 : kMagic;
-      h[1] = FMT;
-      h[2] = kTileM;
-      h[3] = kTileK;
-      h[4] = kPad;
-      h[5] = p.policy;
-      h[kHeaderTicket] = 0u;
-      unsigned long long* d = (unsigned long long*)(p.out + 32);
-      d[0] = p.M;
-      d[1] = p.K;
-      h[kHeaderTotalWords] = run;
+    for (int a = 0; a < kTilesPerWave; ++a) {
+      const uint32_t n = t[a].entries;
+      if (fits(run_words<FMT>(n))) {
+        uint32_t* dst = words_of(p) + begin;
+        for (uint32_t base = 0; base < n; base += kStageEntries) {
+          lds_order();
+          if (n <= kStageEntries) {
+            if (a > 0) stage_entries<FMT, true>(t[a], stage, 0, lane);
+          } else {
+            stage_entries<FMT, false>(t[a], stage, base, lane);
+          }
+          lds_order();
+          flush_stage<FMT>(n - base < kStageEntries ? n - base : kStageEntries, stage, dst + run_words<FMT>(base), lane);
+        }
+      }
+      begin += run_words<FMT>(n);
     }
   }
-  stored = wave_sum64(stored);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const uint32_t v = (uint32_t)__shfl_xor((int)longest, d, 64);
-    longest = v > longest ? v : longest;
-  }
-  if ((threadIdx.x & 63) == 0) {
-    atomicAdd((unsigned long long*)(p.out + 48), (unsigned long long)stored);
-    atomicMax(h + kHeaderMaxTileWords, longest);
+  if (q + 1 == p.chunks) {
+    __syncthreads();  // the stages are free
+    finish_header<FMT>(p, total_words, (uint32_t*)stages[0], wave, lane);
   }
 }
 
@@ -454,30 +484,26 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int FMT>
-static hipError_t launch_compress_fmt(const CompressParams& p, hipStream_t stream) {
-  const uint32_t chunks = (p.T + kChunkTiles - 1) / kChunkTiles;
-  // states and header start at zero
-  hipError_t e = launch_fill_zero(p.out, 64 + 4 * (size_t)p.n_off, stream);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((compress_emit_kernel<FMT>), dim3(chunks), dim3(kChunkWaves * 64), 0, stream, p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL((compress_finish_kernel<FMT>), dim3((chunks + 255) / 256), dim3(256), 0, stream, p);
-  return hipGetLastError();
-}
-
 hipError_t launch_compress(const CompressLaunch& a, hipStream_t stream) {
   CompressParams p;
   p.W = a.W;
   p.out = a.out;
+  p.scratch = a.scratch;
+  p.host = a.host;
+  p.call = a.call;
+  p.look_limit = a.look_limit;
+  p.by_ticket = a.by_ticket;
   p.M = a.M;
   p.K = a.K;
   p.KT = a.K / kTileK;
   p.T = (a.M / kTileM) * p.KT;
   p.n_off = (p.T + 4 + 15) / 16 * 16;
   p.policy = a.policy;
+  p.chunks = (p.T + kChunkTiles - 1) / kChunkTiles;
   p.capacity_words = (a.capacity - (64 + 4 * (size_t)p.n_off)) / 4;
-  return a.version == 2 ? launch_compress_fmt<2>(p, stream) : launch_compress_fmt<1>(p, stream);
+  if (a.version == 2) hipLaunchKernelGGL((compress_kernel<2>), dim3(p.chunks), dim3(kChunkWaves * 64), 0, stream, p);
+  else hipLaunchKernelGGL((compress_kernel<1>), dim3(p.chunks), dim3(kChunkWaves * 64), 0, stream, p);
+  return hipGetLastError();
 }
 
 }  // namespace fls

@@ -33,8 +33,29 @@ struct DenseLaunch {
   int num_cus;
 };
 
+// Scratch of a compress call on the GPU: the next chunk to be taken (zero between calls) and, for every chunk, two words that
+// bear the number of the call that wrote them, so that nothing else is cleared between calls.
+constexpr uint32_t kCompressChunkTiles = 16;
+constexpr uint32_t kCompressMaxChunks = (1u << 20) / kCompressChunkTiles;  // M * K < 2^32: fewer than 2^20 tiles
+constexpr uint32_t kCompressCalls = 1u << 30;                              // a call's number is 1 ... kCompressCalls - 1
+struct CompressScratch {
+  alignas(256) uint32_t ticket;
+  alignas(256) uint64_t sums[kCompressMaxChunks];
+  uint64_t counts[kCompressMaxChunks];
+};
+// What a call leaves in host memory.
+struct alignas(64) CompressHost {
+  uint32_t header[16];
+  uint32_t gave_up;  // 1 if a look-back gave up
+};
+
 struct CompressLaunch {
   const uint16_t* W;
+  CompressScratch* scratch;
+  CompressHost* host;  // as the device addresses it
+  uint32_t call;       // 1 ... kCompressCalls - 1, another one than those of the calls before on this scratch
+  uint32_t look_limit; // looks at another workgroup's word before the kernel gives up (host->gave_up; the blob is of no use then)
+  bool by_ticket;      // chunks in the order in which workgroups start, not by their number
   unsigned char* out;  // blob
   size_t capacity;     // bytes of `out`, at least header and TileOffsets: no word goes past it
   uint32_t M, K;
@@ -227,7 +248,7 @@ hipError_t launch_spmm_block(const SpmmLaunch& a, const SpmmPlan& plan, hipStrea
 // layout32: the partial results are in the 32x32 accumulator layout (sparse pass), else 16x16 (dense pass)
 hipError_t launch_wide_reduce(const WideParams& p, bool layout32, hipStream_t stream);
 hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream);
-// header, TileOffsets and every tile whose words fit the capacity
+// header, TileOffsets and every tile whose words fit the capacity: one kernel
 hipError_t launch_compress(const CompressLaunch& a, hipStream_t stream);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 

@@ -80,3 +80,58 @@ def test_lane_edges(fls, oracle_mod, version):
     blob, st = (fls.fls_compress_v2 if version == 2 else fls.fls_compress)(_dev(W))
     assert np.array_equal(blob.cpu().numpy(), (oracle_mod.ref_compress_v2 if version == 2 else oracle_mod.ref_compress)(W))
     assert st["nnz"] == int(np.count_nonzero(W))
+
+
+def test_more_threads_than_the_library_has_scratch_for(fls, oracle_mod):
+    """24 threads on streams of their own, several matrices each, against the oracle: a call waits for a place of the 16."""
+    import threading
+
+    import torch
+
+    shapes = [(1, 1), (3, 5), (2, 40), (7, 33)]
+    Ws = [_weights(b, kt, [700 + 40 * i, 3, 0, 2100], 31 + i) for i, (b, kt) in enumerate(shapes)]
+    refs = {v: [(oracle_mod.ref_compress_v2 if v == 2 else oracle_mod.ref_compress)(W) for W in Ws] for v in (1, 2)}
+    on_gpu = [_dev(W) for W in Ws]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(n):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for k in range(8):
+                    i, v = (n + k) % len(Ws), 1 + (n + k // 4) % 2
+                    blob, st = (fls.fls_compress_v2 if v == 2 else fls.fls_compress)(on_gpu[i])
+                    if not np.array_equal(blob.cpu().numpy(), refs[v][i]) or st["nnz"] != int(np.count_nonzero(Ws[i])):
+                        wrong.append((n, k))
+        except Exception as e:  # an exception in a thread would go unseen
+            wrong.append((n, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(n,)) for n in range(24)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
+@pytest.mark.parametrize("version", [1, 2])
+@pytest.mark.parametrize("bands,kt", [(1, 1), (3, 5), (16, 1025)])
+def test_a_kernel_that_gives_up_is_run_again_by_ticket(fls, oracle_mod, version, bands, kt):
+    """With 1025 chunks, four to a CU, some workgroup looks for a word that is not there yet: the call is made again with chunks by
+    ticket, and twice in a row (the ticket counts from 0 each time)."""
+    import ctypes
+
+    import torch
+
+    W = _weights(bands, kt, [800, 0, 2049, 30], 41)
+    ref = (oracle_mod.ref_compress_v2 if version == 2 else oracle_mod.ref_compress)(W)
+    Wd = _dev(W)
+    f = fls.lib().fls_internal_compress_impatient
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint32,
+                  ctypes.POINTER(fls.FlsStats), ctypes.c_void_p]
+    for _ in range(2):
+        out = torch.zeros(len(ref) + 16, dtype=torch.uint8, device="cuda")
+        st = fls.FlsStats()
+        stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert f(Wd.data_ptr(), bands * 128, kt * 32, out.data_ptr(), out.numel(), version, ctypes.byref(st), stream) == fls.OK
+        assert np.array_equal(out[:len(ref)].cpu().numpy(), ref) and st.nnz == int(np.count_nonzero(W))
