@@ -431,6 +431,7 @@ int fls_spmm(const void* Wc_dev, const void* X_dev, void* C_dev, int64_t M, int6
   a.version = info.version;
   a.num_cus = cus;
   a.wide32 = true;
+  a.raised = 1u;
   return fls::launch_spmm(a, (hipStream_t)stream) == hipSuccess ? FLS_OK : FLS_EHIP;
 }
 
@@ -472,6 +473,7 @@ int fls_spmm_stats(const void* Wc_dev, const fls_stats* stats_host, const void* 
   a.version = stats_host->format_version;
   a.num_cus = cus;
   a.wide32 = true;
+  a.raised = 1u;
   return fls::launch_spmm(a, (hipStream_t)stream) == hipSuccess ? FLS_OK : FLS_EHIP;
 }
 
@@ -505,6 +507,7 @@ int fls_spmm_noalloc(const void* Wc_dev, const fls_stats* stats_host, const void
   a.max_tile_words = (uint32_t)stats_host->max_tile_words;
   a.version = stats_host->format_version;
   a.num_cus = cus;
+  a.raised = 1u;
   a.wide32 = false;  // the static array has the narrow kernel's partial sums only
   return fls::launch_spmm(a, s) == hipSuccess ? FLS_OK : FLS_EHIP;
 }
@@ -544,6 +547,13 @@ void fls_internal_spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t 
   out[1] = plan.share;
   out[2] = plan.rounds;
   out[3] = plan.slices;
+}
+
+void fls_internal_shares(uint32_t M, uint32_t K, int cus, float tile_us, int wide, uint32_t* out) {
+  const fls::Shares s = fls::pick_shares(M / FLS_TILE_M, K / FLS_TILE_K, cus, tile_us, wide != 0);
+  out[0] = s.P;
+  out[1] = s.unit;
+  out[2] = s.grid;
 }
 
 // fls_compress (version 1 or 2) whose kernel gives up at the first word that another workgroup has not published yet, so that it

@@ -29,8 +29,11 @@ __global__ __launch_bounds__(WAVES * 64) void dense_kernel(DenseParams p) {
   constexpr int kDenseK = 32 * H;
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t T = p.out.T, KT = p.out.KT;  // steps of 128 x 64 here
-  const uint32_t share0 = share_begin(blockIdx.x, T, gridDim.x), share1 = share_begin(blockIdx.x + 1, T, gridDim.x);
+  const uint32_t KT = p.out.KT;  // steps of 128 x 64 here
+  uint32_t wg, near_end;  // this workgroup's share, the end of those on its XCD
+  if (!share_of_block(p.out, wg, near_end)) return;
+  const uint32_t share0 = share_begin(p.out, wg), share1 = share_begin(p.out, wg + 1);
+  if (threadIdx.x == 0) announce_owner(p.out, wg, share0, share1);
   // The waves of a workgroup take the steps of its share in turn (wave w: share0 + w, + WAVES,
   // ...), so at any time they read neighbouring 128 B pieces of the same rows: 1 KB runs for the
   // DRAM instead of eight unrelated ones.
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(WAVES * 64) void dense_kernel(DenseParams p) {
     tc += WAVES;
     ktc += WAVES;
     if (ktc >= KT || tc >= t1) {  // the wave's next step is in another band, or there is none
-      hand_over_piece<NB>(p.out, red, acc, hs, bandc, piece_tiles, share0, share1, blockIdx.x, lane, false, false);
+      hand_over_piece<NB>(p.out, red, acc, hs, bandc, piece_tiles, share0, share1, wg, lane, false, false);
       piece_tiles = 0;
       while (ktc >= KT) {
         ktc -= KT;
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(WAVES * 64) void dense_kernel(DenseParams p) {
 #pragma unroll
   for (int i = 0; i < NS - 1; ++i)
     if (tc < t1) step(a[i], x[i]);
-  hand_over_finish<NB>(p.out, acc, hs, blockIdx.x, gridDim.x, lane);
+  hand_over_finish<NB>(p.out, acc, hs, wg, near_end, lane);
 }
 
 template <int NB, int WAVES, int NS, int H>
@@ -305,7 +308,13 @@ hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream) {
   p.out.flags = a.flags;
   p.out.M = a.M;
   p.out.N = a.N;
-  const int grid = pick_grid(a.M / kTileM, a.K / kTileK, a.num_cus);
+  p.out.raised = 1u;
+  const Shares shares = pick_shares(a.M / kTileM, a.K / kTileK, a.num_cus, 0.27f, a.N > 16u);
+  p.out.P = shares.P;
+  p.out.unit = shares.unit;
+  p.out.units = shares.unit ? shares.P / shares.unit : 0u;
+  p.out.bands = a.M / kTileM;
+  const int grid = (int)shares.grid;
   if (a.N > kGroupCols) {
     hipError_t e = launch_xpack(a.X, a.xpack, a.K, a.N, stream);  // the 64-column passes read X in fragment order
     if (e != hipSuccess) return e;

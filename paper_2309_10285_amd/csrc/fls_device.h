@@ -27,6 +27,10 @@ constexpr int kBufferFlags = 0x00020000;    // raw buffer, 32-bit data format (g
 constexpr int kAuxNonTemporal = 2;          // nt: streamed once, do not keep in the caches
 constexpr int kAuxCoherent = 16;            // sc1: device scope - through to memory / past the per-XCD L2
 
+// Control words of the hand-over, from `flags` on: flags of partial sums released at device scope, the error word, the XCDs of
+// waiting owners, flags of partial sums that stay in an XCD's L2.  2048 words (what the static scratch has).
+constexpr uint32_t kErrorWord = kMaxGrid, kOwnerXcd = 2 * kMaxGrid, kLocalFlags = 3 * kMaxGrid;
+
 // LDS byte address a word of a tile goes to: base + 2 * location (the word's low half), in one
 // instruction (v_mad_u32_u16: D = S0.u16 * S1.u16 + S2.u32).
 __device__ __forceinline__ uint32_t scatter_addr(uint32_t word, uint32_t base) {
@@ -48,7 +52,12 @@ __device__ __forceinline__ uint32_t scatter_addr(uint32_t word, uint32_t base) {
 struct OutParams {
   _Float16* C;      // column-major M x N
   float* parts;     // [workgroup][NB * 2048] fp32 partial sums in accumulator order
-  uint32_t* flags;  // [workgroup] 1 while a published partial sum waits for its band's owner; [kMaxGrid] error word
+  uint32_t* flags;  // control words; [share] `raised` while a published partial sum waits for its band's owner
+  uint32_t raised;  // a flag that is up, nonzero
+  uint32_t P;       // shares
+  uint32_t unit;    // ... that stay together on an XCD, `units` such groups; 0: shares are whole bands, nothing is handed over
+  uint32_t units;
+  uint32_t bands;
   uint32_t M, N;    // N = columns of the whole problem
   uint32_t n0;      // first column of this launch's column group
   uint32_t KT;      // K tiles per band
@@ -86,10 +95,28 @@ __device__ __forceinline__ bool wide_unit(uint32_t quads, uint32_t S, uint32_t G
   return true;
 }
 
-// First tile of workgroup q's share when T tiles are cut over P workgroups.
-__device__ __forceinline__ uint32_t share_begin(uint32_t q, uint32_t T, uint32_t P) {
-  return (uint32_t)((uint64_t)q * T / P);
+// First tile of share q: all tiles cut evenly over the shares, or the bands.  (At most kMaxGrid shares, fewer than 2^20 tiles.)
+__device__ __forceinline__ uint32_t share_begin(const OutParams& o, uint32_t q) {
+  return o.unit == 0 ? q * o.bands / o.P * o.KT : q * o.T / o.P;
 }
+
+// This workgroup's share, and the end of the shares that go to the same XCD.  Consecutive workgroup ids go to the chip's
+// eight XCDs in turn, so id 8 i + x takes the i-th share of the x-th eighth of the units: neighbouring shares, which hand partial
+// sums of a cut band to each other, run on one XCD.  (share_grid of the launchers sizes the grid.)
+__device__ __forceinline__ bool share_of_block(const OutParams& o, uint32_t& wg, uint32_t& near_end) {
+  if (o.unit == 0) {  // nothing to hand over
+    wg = blockIdx.x;
+    near_end = 0;
+    return wg < o.P;
+  }
+  const uint32_t x = blockIdx.x & 7u;
+  wg = x * o.units / 8u * o.unit + (blockIdx.x >> 3);
+  near_end = (x + 1u) * o.units / 8u * o.unit;
+  return wg < near_end;
+}
+
+// The XCD this wave runs on (hardware register XCC_ID, bits 0 - 3).
+__device__ __forceinline__ uint32_t my_xcd() { return __builtin_amdgcn_s_getreg(20 | (4 - 1) << 11); }
 
 // MFMA 16x16 accumulator layout: lane l holds column (l & 15), rows 4*(l >> 4) .. +3 of its block.
 // Converts a wave's 128 x (NB*16) accumulators to fp16 and stores them to column-major C.
@@ -124,11 +151,13 @@ struct WgReduceLds {
   uint32_t cnt[kSlots];           // tiles added to the slot so far
   uint32_t gen[kSlots];           // how many bands the slot has served
   uint32_t lock[kSlots][kParts];  // 1 while a wave is adding to that part of the slot
+  uint32_t far;                   // 1 once a wave has stored its part of the workgroup's partial sum through to memory
 };
 
 template <int NB>
 __device__ __forceinline__ void wg_reduce_init(WgReduceLds<NB>* red, int tid, int nthreads) {
   for (int i = tid; i < (int)WgReduceLds<NB>::kSlots * NB * kRowBlocks * 64; i += nthreads) (&red->slot[0][0])[i] = float4v{0.f, 0.f, 0.f, 0.f};
+  if (tid == 0) red->far = 0;
   if (tid < (int)WgReduceLds<NB>::kSlots) {
     red->cnt[tid] = 0;
     red->gen[tid] = 0;
@@ -209,16 +238,23 @@ __device__ __forceinline__ void wg_reduce_skip(WgReduceLds<NB>* red, uint32_t se
 // A band that is cut between workgroups is finished by its owner: the workgroup whose share holds
 // the band's first tile.  The owner's piece of the band is the last thing in its share, so its
 // sum is still in registers when its run ends.  Every other workgroup that holds tiles of the
-// band stores its sum to its slot when its piece ends (write-through stores, nothing waits for
-// them) and publishes the slot when its own run ends, by raising its flag behind a device-scope
-// release.  The owner then polls those flags, acquires, adds the slots in workgroup order and
-// writes fp16 C.
+// band stores its sum to its slot when its piece ends (nothing waits for the stores) and publishes
+// the slot when its own run ends, by raising its flag.  The owner then polls those flags, adds the
+// slots in workgroup order and writes fp16 C.
 //
-// Partial sums cross between the L2 caches of different XCDs, which are not coherent with each
-// other inside a kernel: the contributor releases at device scope before it raises its flag, the
-// owner acquires at device scope after it has seen the flags (2 - 3 us of the kernel's tail on
-// shapes that split bands; the stores and loads of the slots also carry sc1, so little is left for
-// the release to write back).  A workgroup publishes at most one
+// How a sum gets across depends on where the two run.  On one XCD they share an L2: a store has arrived there once
+// it counts as done, and loads that miss the CU's L1 find it.  The L2 caches of different XCDs are not coherent with each
+// other inside a kernel: there the contributor stores through to memory and releases at device scope before it raises its flag,
+// and the owner loads at device scope after it has seen the flags - trips to memory, one after the other, when
+// the kernel is about to end.  Which way a contributor takes it decides from the owner's word: a workgroup that will own a cut
+// band writes the XCD it runs on there when it starts (the hardware's number, not one worked out from the workgroup's
+// number: that only decides how likely the short way is), and takes it back once it has seen all flags.  An owner that has not
+// started yet, or runs elsewhere, gets the long way.  Each way has its own flags, so the owner knows which one it was.
+// Measured, against the long way for all: 12288 x 12288 at 80 %, N = 13 30.4 -> 27.9 us a call (0.67 of the bands cut), 48640 x 1056 at 89 %, N = 4 17.1 ->
+// 14.0, 49152 x 12288 at 70 % in version 2, N = 8 96.6 -> 94.7, a 7168-wide decoder layer, N = 16 114.5 -> 110.3; with the shares of a band kept together
+// 1536 x 17312 at 71 %, N = 2 17.4 -> 14.9.
+//
+// A workgroup publishes at most one
 // partial sum per launch (only the first band of a share can begin outside it) and exactly one
 // owner waits for it; the owner lowers the flag it has seen, so all flags are down again when the
 // launch ends: nothing is cleared between calls, and a launch recorded in a graph can be replayed.
@@ -227,9 +263,27 @@ __device__ __forceinline__ void wg_reduce_skip(WgReduceLds<NB>* red, uint32_t se
 // ends as soon as those workgroups have run; the spin is bounded all the same.
 constexpr uint32_t kSpinLimit = 1u << 20;
 
-template <int NB>
-__device__ __forceinline__ void store_partial(const OutParams& o, const float4v (&acc)[kRowBlocks][NB], uint32_t wg,
-                                              int lane) {
+// Does share [share0, share1) hold the first tile of a band that it does not hold the last tile of?
+__device__ __forceinline__ bool owns_cut_band(const OutParams& o, uint32_t share0, uint32_t share1) {
+  return share1 % o.KT != 0 && share1 > share0 && share1 - share1 % o.KT >= share0;
+}
+// By one thread of a workgroup when it starts.
+__device__ __forceinline__ void announce_owner(const OutParams& o, uint32_t wg, uint32_t share0, uint32_t share1) {
+  if (owns_cut_band(o, share0, share1))
+    __hip_atomic_store(o.flags + kOwnerXcd + wg, my_xcd() + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// XCD + 1 of the owner of `band`, 0 if it has not started: a load that the caller lets run until it needs the answer.
+__device__ __forceinline__ uint32_t owner_word(const OutParams& o, uint32_t band) {
+  const uint32_t first = band * o.KT;
+  uint32_t q = first * o.P / o.T;
+  while (q + 1 < o.P && share_begin(o, q + 1) <= first) ++q;
+  return __hip_atomic_load(o.flags + kOwnerXcd + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool runs_here(uint32_t owner_word) { return __builtin_amdgcn_readfirstlane(owner_word) == my_xcd() + 1u; }
+
+template <int NB, int AUX>
+__device__ __forceinline__ void store_partial_as(const OutParams& o, const float4v (&acc)[kRowBlocks][NB], uint32_t wg,
+                                                 int lane) {
   const __amdgpu_buffer_rsrc_t mine = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(o.parts + (size_t)wg * (NB * kAccPerBlock)), 0, NB * kAccPerBlock * 4, kBufferFlags);
 #pragma unroll
@@ -237,100 +291,115 @@ __device__ __forceinline__ void store_partial(const OutParams& o, const float4v 
 #pragma unroll
     for (int rb = 0; rb < kRowBlocks; ++rb)
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[rb][nb]), mine,
-                                             ((nb * kRowBlocks + rb) * 64 + lane) * 16, 0, kAuxCoherent);
+                                             ((nb * kRowBlocks + rb) * 64 + lane) * 16, 0, AUX);
+}
+template <int NB>
+__device__ __forceinline__ void store_partial(const OutParams& o, const float4v (&acc)[kRowBlocks][NB], uint32_t wg, bool local,
+                                              int lane) {
+  if (local) store_partial_as<NB, 0>(o, acc, wg, lane);
+  else store_partial_as<NB, kAuxCoherent>(o, acc, wg, lane);
 }
 
 // A device-scope release in two halves, so that the time the write-back takes can pass behind
 // other work: release_begin right after the stores (the L2 of this XCD starts writing back what
 // it holds), release_end before the flag is raised (waits for that and for every earlier store).
 // Together they are the instruction sequence of a release fence at device scope.  Waiting for the
-// stores alone is not enough: a store counts as done when the XCD's L2 has it, and the flag could
+// stores alone is not enough across XCDs: a store counts as done when the XCD's L2 has it, and the flag could
 // reach memory before the data does (seen as a wrong band about once in a thousand calls).
 __device__ __forceinline__ void release_begin() { asm volatile("buffer_wbl2 sc1" ::: "memory"); }
 __device__ __forceinline__ void release_end() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // By the wave that called store_partial, once its run is over; `begun` tells whether it has called
 // release_begin behind the stores already.
-__device__ __forceinline__ void publish_partial(const OutParams& o, uint32_t wg, int lane, bool begun) {
+__device__ __forceinline__ void publish_partial(const OutParams& o, uint32_t wg, int lane, bool local, bool begun) {
+  if (local) {
+    release_end();  // the stores have reached the L2
+    if (lane == 0) __hip_atomic_store(o.flags + kLocalFlags + wg, o.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return;
+  }
   if (!begun) release_begin();
   release_end();
-  if (lane == 0) __hip_atomic_store(o.flags + wg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane == 0) __hip_atomic_store(o.flags + wg, o.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // acc holds the owner's own sum for `band`; adds the other workgroups' and writes C.
 template <int NB>
 __device__ __forceinline__ void owner_finish(const OutParams& o, float4v (&acc)[kRowBlocks][NB], uint32_t band,
-                                             uint32_t wg, uint32_t P, int lane) {
+                                             uint32_t wg, uint32_t near_end, int lane) {
   const uint32_t band_hi = (band + 1) * o.KT;
-  // The flags of all contributors are polled at once, one per lane: a look at a flag is a trip to
-  // memory (it lives behind another XCD's L2), and one after the other those trips would add up at the
-  // very end of the kernel.
-  for (uint32_t base = wg + 1; base < P && share_begin(base, o.T, P) < band_hi; base += 64) {
+  // The flags of up to 64 contributors are polled at once, one per lane: a look at a flag is a trip to
+  // L2 or memory, and one after the other those trips would add up at the very end of the kernel.
+  for (uint32_t base = wg + 1; base < o.P && share_begin(o, base) < band_hi; base += 64) {
     const uint32_t q = base + (uint32_t)lane;
     // workgroup q holds tiles of the band (an empty share contributes nothing)
-    const bool mine = q < P && share_begin(q, o.T, P) < band_hi && share_begin(q + 1, o.T, P) != share_begin(q, o.T, P);
+    const bool mine = q < o.P && share_begin(o, q) < band_hi && share_begin(o, q + 1) != share_begin(o, q);
     uint32_t spins = 0;
-    bool seen = !mine;
+    bool seen = !mine, local = false;
     for (;;) {
-      if (!seen) seen = __hip_atomic_load(o.flags + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+      if (!seen) {
+        // (the kind of flag that the contributor's number lets expect each time, the other one now and then)
+        const bool expected = q < near_end, both = (spins & 7u) == 7u;
+        // (an atomic, which also lowers the flag: the L2 executes it, where the CU's L1 may serve a load at workgroup scope for ever)
+        uint32_t up = o.raised;
+        if (expected || both)
+          local = __hip_atomic_compare_exchange_strong(o.flags + kLocalFlags + q, &up, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        seen = local;
+        if (!seen && (!expected || both)) seen = __hip_atomic_load(o.flags + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == o.raised;
+      }
       if (__builtin_amdgcn_ballot_w64(!seen) == 0) break;
-      __builtin_amdgcn_s_sleep(8);
+      __builtin_amdgcn_s_sleep(2);
       if (++spins == kSpinLimit) {  // never seen; gives up rather than hang, and says so
-        if (lane == 0) __hip_atomic_store(o.flags + kMaxGrid, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) __hip_atomic_store(o.flags + kErrorWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         break;
       }
     }
-    // workgroup q raises its flag once per launch and nobody else looks at it: down again for the next launch
-    if (mine && seen) __hip_atomic_store(o.flags + q, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  // What pairs with the contributors' release: the loads below are issued after the flags have been
-  // seen, and each carries sc1 like the look at a flag does - a load at device scope, which nothing
-  // that this CU's L1 or this XCD's L2 still holds of the slots may serve.  (An acquire fence here
-  // would invalidate both caches wholesale on top of that: a microsecond at the very end of the kernel.)
-  // As many loads as the registers allow are issued before the first is used: each is a trip
-  // to memory, and this runs when the kernel is about to end, with nothing left to hide it behind.
-  constexpr int kBatch = NB == 1 ? 4 : 2;  // slots in flight
-  constexpr int kBlocks = NB > 2 ? 2 : NB;  // column blocks of a slot in flight
-  uint32_t q = wg + 1;
-  while (q < P && share_begin(q, o.T, P) < band_hi) {
-    __amdgpu_buffer_rsrc_t src[kBatch];
+    // workgroup q raises one flag once per launch and nobody else looks at it: down again for the next launch
+    if (mine && seen && !local) __hip_atomic_store(o.flags + q, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The loads below are issued after the flags have been seen.  Slots filled through this XCD's L2 are read by ordinary loads: no line of
+    // theirs can be in this CU's L1, which starts a launch empty and has seen no read of them since.  Loads at device scope are what pairs with the contributors'
+    // release: nothing that this CU's L1 or this XCD's L2 still holds of the slots may serve them.  (An acquire fence here would invalidate
+    // both caches wholesale on top of that: a microsecond at the very end of the kernel.)
+    asm volatile("" ::: "memory");
+    // As many loads as the registers allow are issued before the first is used: nothing is left to hide one behind.
+    constexpr int kBatch = NB == 1 ? 4 : 2;  // slots in flight
+    uint64_t left = __builtin_amdgcn_ballot_w64(mine);
+    const uint64_t far = __builtin_amdgcn_ballot_w64(mine && !local);
+    while (left != 0) {
+      u32x4 v[kBatch][NB][kRowBlocks];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      // next workgroup with tiles of the band; past the last one the descriptor is empty and reads 0
-      bool found = false;
-      while (!found && q < P && share_begin(q, o.T, P) < band_hi) {
-        found = share_begin(q + 1, o.T, P) != share_begin(q, o.T, P);
-        if (!found) ++q;
+      for (int j = 0; j < kBatch; ++j) {
+        // the next contributor; past the last one the descriptor is empty and reads 0
+        const uint32_t i = left ? (uint32_t)__builtin_ctzll(left) : 0u;
+        const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc((void*)(o.parts + (size_t)(base + i) * (NB * kAccPerBlock)), 0,
+                                                                             left ? NB * kAccPerBlock * 4 : 0, kBufferFlags);
+        if (left & far & (1ull << i)) {
+#pragma unroll
+          for (int e = 0; e < NB * kRowBlocks; ++e)
+            v[j][e / kRowBlocks][e % kRowBlocks] = __builtin_amdgcn_raw_buffer_load_b128(src, (e * 64 + lane) * 16, 0, kAuxCoherent);
+        } else {
+#pragma unroll
+          for (int e = 0; e < NB * kRowBlocks; ++e)
+            v[j][e / kRowBlocks][e % kRowBlocks] = __builtin_amdgcn_raw_buffer_load_b128(src, (e * 64 + lane) * 16, 0, 0);
+        }
+        left &= left - 1;
       }
-      src[j] = __builtin_amdgcn_make_buffer_rsrc((void*)(o.parts + (size_t)(found ? q : 0u) * (NB * kAccPerBlock)), 0,
-                                                 found ? NB * kAccPerBlock * 4 : 0, kBufferFlags);
-      if (found) ++q;
-    }
-#pragma unroll
-    for (int nb0 = 0; nb0 < NB; nb0 += kBlocks) {
-      u32x4 v[kBatch][kBlocks][kRowBlocks];
 #pragma unroll
       for (int j = 0; j < kBatch; ++j)
 #pragma unroll
-        for (int nb = 0; nb < kBlocks; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-          for (int rb = 0; rb < kRowBlocks; ++rb)
-            v[j][nb][rb] = __builtin_amdgcn_raw_buffer_load_b128(src[j], (((nb0 + nb) * kRowBlocks + rb) * 64 + lane) * 16, 0,
-                                                                 kAuxCoherent);
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j)
-#pragma unroll
-        for (int nb = 0; nb < kBlocks; ++nb)
-#pragma unroll
-          for (int rb = 0; rb < kRowBlocks; ++rb) acc[rb][nb0 + nb] += __builtin_bit_cast(float4v, v[j][nb][rb]);
+          for (int rb = 0; rb < kRowBlocks; ++rb) acc[rb][nb] += __builtin_bit_cast(float4v, v[j][nb][rb]);
     }
   }
+  // all contributors have read the owner's word
+  if (lane == 0) __hip_atomic_store(o.flags + kOwnerXcd + wg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   store_band<NB>(o, acc, band, lane);
 }
 
 // What a wave carries from the tile loop to the end of its run.
 struct HandoverState {
   bool publish = false;  // it stored its workgroup's partial sum and still has to publish it
+  bool local = false;    // ... to the owner's L2
   bool released = false; // release_begin has been called behind those stores
   bool own = false;      // it holds the owner's sum of band own_band in its accumulators
   uint32_t own_band = 0;
@@ -352,6 +421,10 @@ __device__ __forceinline__ void hand_over_piece(const OutParams& o, WgReduceLds<
     const uint32_t band_lo = band * o.KT, band_hi = band_lo + o.KT;
     const uint32_t lo = share0 > band_lo ? share0 : band_lo;
     const uint32_t hi = share1 < band_hi ? share1 : band_hi;
+    uint32_t owner = 0;
+    // asked for here, needed once the workgroup's sum is complete (in the dense kernel asked for then: a load that is not waited for on
+    // every way through here would make its ring wait for everything)
+    if (early_release && lo != band_lo) owner = owner_word(o, band);
     if (wg_reduce_add<NB>(red, acc, seq, tiles, hi - lo, lane)) {
       wg_reduce_take<NB>(red, acc, seq, lane);  // acc = the workgroup's sum over [lo, hi)
       if ((lo == band_lo && hi == band_hi) || local_only) {
@@ -360,11 +433,13 @@ __device__ __forceinline__ void hand_over_piece(const OutParams& o, WgReduceLds<
         st.own = true;  // the share ends inside this band: nothing follows, keep the sum
         st.own_band = band;
       } else {
-        store_partial<NB>(o, acc, wg, lane);
+        if (!early_release) owner = owner_word(o, band);
+        st.local = runs_here(owner);
+        store_partial<NB>(o, acc, wg, st.local, lane);
         // the sparse kernel's load ring is empty at the end of a piece, so nothing of it has to be
         // waited for to start the write-back here; the dense kernel keeps its ring going and
         // releases in one go at the end
-        if (early_release) {
+        if (early_release && !st.local) {
           release_begin();
           st.released = true;
         }
@@ -383,12 +458,12 @@ __device__ __forceinline__ void hand_over_piece(const OutParams& o, WgReduceLds<
 // After the tile loop.
 template <int NB>
 __device__ __forceinline__ void hand_over_finish(const OutParams& o, float4v (&acc)[kRowBlocks][NB],
-                                                 const HandoverState& st, uint32_t wg, uint32_t P, int lane) {
+                                                 const HandoverState& st, uint32_t wg, uint32_t near_end, int lane) {
   if (st.publish) {
-    publish_partial(o, wg, lane, st.released);
+    publish_partial(o, wg, lane, st.local, st.released);
   }
   if (st.own) {
-    owner_finish<NB>(o, acc, st.own_band, wg, P, lane);
+    owner_finish<NB>(o, acc, st.own_band, wg, near_end, lane);
   }
 }
 

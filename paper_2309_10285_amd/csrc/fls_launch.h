@@ -17,6 +17,7 @@ struct SpmmLaunch {
   uint32_t max_tile_words;
   uint32_t version;  // format version of the blob (1 or 2)
   int num_cus;
+  uint32_t raised;   // what a raised flag of the hand-over holds, nonzero
   // the partial-sum area was sized by parts_floats(N): a call of 17 - 32 columns may take the 64-column pass
   // (false for the static scratch of the entry point that allocates nothing, which has the narrow kernel's area only)
   bool wide32;
@@ -187,31 +188,66 @@ inline size_t xpack_bytes(uint32_t K, uint32_t N) {
   return N > kGroupCols ? (size_t)K * ((N + 15u) / 16u * 16u) * 2u : 0;
 }
 
-// Number of workgroups for a matrix of `bands` row bands on `cus` compute units (one workgroup
-// per CU at most).  A count of the form bands * k gives every band to exactly k workgroups: with
-// k = 1 no partial sum ever crosses between workgroups, and the serial hand-over chain at the end
-// of the kernel (store, count, read back: a few microseconds with the whole chip waiting) goes
-// away.  That is worth leaving up to a fifth of the CUs without a workgroup: the kernel is paced by
-// HBM, not by the CUs.  Otherwise every CU gets an equal share, cut wherever it falls (see below
-// for the one exception).
-// A workgroup should also have enough tiles to amortise its start and its hand-over: small
-// problems get fewer workgroups (at least kMinShare tiles each).
-constexpr uint32_t kMinShare = 32;
-inline int pick_grid(uint32_t bands, uint32_t tiles_per_band, int cus) {
+// How the tiles of a matrix of `bands` row bands are shared out to workgroups, at most one per CU, in the passes of up to 32
+// columns.
+struct Shares {
+  uint32_t P;     // shares
+  uint32_t unit;  // shares that stay together on an XCD; 0: a share is whole bands, no partial sum crosses between workgroups
+  uint32_t grid;  // workgroups, the idle ones that fill up the XCDs' parts among them (see share_of_block)
+};
+// What a tile costs a workgroup, in us, by the rounds that its variant stages (tiles of W that was left dense: 0.27).
+inline float tile_us(uint32_t rounds, bool wide) { return 0.035f + 0.0175f * (float)rounds + (wide ? 0.02f : 0.f); }
+inline Shares shares_of(uint32_t P, uint32_t unit) { return {P, unit, unit == 0 ? P : (P / unit + 7u) / 8u * unit * 8u}; }
+// Shares that cut bands.  Those of one band, or of a pair of bands, stay together where no XCD gets more workgroups than it has CUs.
+inline Shares cut_shares(uint32_t P, uint32_t bands, int cus) {
+  uint32_t unit = P % bands == 0 ? P / bands : bands % 2u == 0 && P % (bands / 2u) == 0 ? P / (bands / 2u) : 1u;
+  const uint32_t per_xcd = cus >= 8 ? (uint32_t)cus / 8u : 1u;
+  if ((P / unit + 7u) / 8u * unit > per_xcd) unit = 1u;
+  return shares_of(P, unit);
+}
+// A workgroup should have enough tiles to pay for its start, and cutting a band costs a hand-over.  Up to 64 tiles per CU the shares are the
+// ones with the lowest estimate
+//   tile_us x tiles of a workgroup + (a band cut into k shares: 1.6 us and 0.6 for every four slots that the owner adds - with 17 - 32 columns
+//   1.9 and 0.52 for every two -, and 1.5 more where the shares of a band do not stay on one XCD),
+// fitted to forced cuts into 1 - 32 shares of bands of 16 - 512 tiles (8, 32, 60 and 100 bands, 65 - 90 %, both formats, dense); a workgroup's LDS work is
+// what a tile costs there.  Some of them (us, N = 8, 80 %, 8 bands): 32 tiles a band 7.3 whole, 7.8 / 6.7 in 2 / 4 shares; 64 tiles 10.9
+// whole, 9.5 / 7.8 / 7.4 / 9.0 in 2 / 4 / 8 / 10; 256 tiles 12.9 / 10.1 / 9.8 / 11.2 in 4 / 8 / 16 / 32; N = 32, 64 tiles 12.8 whole, 9.6 / 9.3 / 9.6 in 4 / 5 / 8.
+// A share has at least eight tiles, one for every wave: fewer take the slow way to a sum (32 tiles in 5 shares 7.7).
+inline Shares pick_shares(uint32_t bands, uint32_t KT, int cus, float tile_us, bool wide) {
   if (cus > (int)kMaxWorkgroups) cus = (int)kMaxWorkgroups;
-  const uint64_t by_size = (uint64_t)bands * tiles_per_band / kMinShare;
-  if (by_size < (uint64_t)cus) cus = by_size > 0 ? (int)by_size : 1;
-  if ((int)bands <= cus) {
-    const int aligned = (int)bands * (cus / (int)bands);
-    if (aligned * 5 >= cus * 4) return aligned;
-    // next best: every pair of bands to an odd number of workgroups (only the middle one of each
-    // group spans two bands), if that leaves next to no CU idle - 168 bands on 256 CUs: 252
-    // workgroups measured 3 % faster than 256
-    const int j = 2 * cus / (int)bands;
-    const int halves = (int)bands * j;
-    if (halves % 2 == 0 && halves / 2 * 100 >= cus * 97) return halves / 2;
+  const uint64_t T = (uint64_t)bands * KT;
+  // More bands than CUs, or bands of fewer than eight tiles: `per` whole bands to a workgroup, which leaves CUs idle, unless cutting
+  // all tiles evenly gains more than the hand-over costs.  (49152 x 256 at 80 %, N = 8: 192 workgroups of two bands 7.3 us, 256 cut ones 9.7; 49152 x
+  // 512 9.0 / 10.4; 34816 x 1024 13.4 / 13.0; 49152 x 12288 at 80 %, N = 16: 96.4 / 87.8; 1024 x 256: eight workgroups 4.5, one 9.3.)
+  const uint32_t m = (bands + (uint32_t)cus - 1u) / (uint32_t)cus, eight = KT <= 2u ? 8u : (8u + KT - 1u) / KT, per = m > eight ? m : eight;
+  if (per > 1u) {
+    if (per > m || tile_us * ((float)per * (float)KT - (float)T / (float)cus) < 2.5f) return shares_of((bands + per - 1u) / per, 0u);
+    return cut_shares((uint32_t)cus, bands, cus);
   }
-  return cus;
+  const uint32_t most = (uint32_t)cus / bands;
+  if (T < 64u * (uint64_t)cus) {
+    uint32_t best = 1;
+    float us = tile_us * (float)KT;
+    for (uint32_t k = 2; k <= most && k * 8u <= KT; ++k) {
+      float t = tile_us * (float)((KT + k - 1u) / k) + (wide ? 1.9f + 0.52f * (float)(k / 2u) : 1.6f + 0.6f * (float)((k + 2u) / 4u));
+      if (cut_shares(bands * k, bands, cus).unit != k) t += 1.5f;
+      if (t < us) {
+        us = t;
+        best = k;
+      }
+    }
+    return best > 1u ? cut_shares(bands * best, bands, cus) : shares_of(bands, 0u);
+  }
+  // Larger problems are paced by HBM, not by the CUs: a count of the form bands * k, where every band has its own k workgroups, is
+  // worth leaving up to a fifth of the CUs without one.
+  const int aligned = (int)(bands * most);
+  if (aligned * 5 >= cus * 4) return most > 1u ? cut_shares((uint32_t)aligned, bands, cus) : shares_of(bands, 0u);
+  // next best: every pair of bands to an odd number of workgroups (only the middle one of each
+  // group spans two bands), if that leaves next to no CU idle - 168 bands on 256 CUs: 252
+  // workgroups measured 3 % faster than 256
+  const int halves = (int)bands * (2 * cus / (int)bands);
+  if (halves % 2 == 0 && halves / 2 * 100 >= cus * 97) return cut_shares((uint32_t)halves / 2u, bands, cus);
+  return cut_shares((uint32_t)cus, bands, cus);
 }
 
 // Arguments of the 64-column passes (sparse and dense) and of the kernel that adds their K slices.
@@ -259,3 +295,6 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 // label, not part of the C ABI.
 extern "C" void fls_internal_spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t M, uint32_t K, uint32_t N, int cus, int wide32,
                                        uint32_t* out);
+
+// How the tiles of an M x K matrix are shared out in the passes of up to 32 columns: out = P, unit, grid of Shares.  As above.
+extern "C" void fls_internal_shares(uint32_t M, uint32_t K, int cus, float tile_us, int wide, uint32_t* out);

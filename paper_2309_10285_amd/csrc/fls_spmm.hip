@@ -57,10 +57,11 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t g = blockIdx.x * WAVES + wave, G = gridDim.x * WAVES;
+  uint32_t wg, near_end;  // this workgroup's share, the end of those on its XCD
+  if (!share_of_block(p.out, wg, near_end)) return;
   const uint32_t T = p.out.T, KT = p.out.KT;
-  const uint32_t t0 = (uint32_t)((uint64_t)g * T / G), t1 = (uint32_t)((uint64_t)(g + 1) * T / G);
-  const uint32_t share0 = share_begin(blockIdx.x, T, gridDim.x), share1 = share_begin(blockIdx.x + 1, T, gridDim.x);
+  const uint32_t share0 = share_begin(p.out, wg), share1 = share_begin(p.out, wg + 1);
+  const uint32_t t0 = share0 + wave * (share1 - share0) / WAVES, t1 = share0 + (wave + 1) * (share1 - share0) / WAVES;
   constexpr int kWaveLds = wave_lds(NB);
   // the first offsets are on their way while LDS is set up
   OffsetWindow win;
@@ -69,6 +70,7 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
   win.total = p.offs[kHeaderTotalWords - kHeaderWords];  // from the blob's own header, like every length
   win.lane = lane;
   win.request(t0 < T ? t0 : T);
+  if (threadIdx.x == 0 && !(FLS_ABLATE & (1 | 64 | 128))) announce_owner(p.out, wg, share0, share1);
   WgReduceLds<NB>* red = (WgReduceLds<NB>*)(lds + WAVES * kWaveLds);
   wg_reduce_init<NB>(red, threadIdx.x, WAVES * 64);
   __syncthreads();  // the only barrier: from here on the waves run independently
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
     } else if (FLS_ABLATE & 128) {
       store_band<NB>(p.out, acc, band, lane);
     } else {
-      hand_over_piece<NB>(p.out, red, acc, hs, band, tiles, share0, share1, blockIdx.x, lane, (FLS_ABLATE & 64) != 0, true);
+      hand_over_piece<NB>(p.out, red, acc, hs, band, tiles, share0, share1, wg, lane, (FLS_ABLATE & 64) != 0, true);
     }
     if (FLS_ABLATE & (1 | 128)) {
 #pragma unroll
@@ -305,7 +307,9 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
     const bool whole = (from_start && to_end) || (FLS_ABLATE & 64);
     const uint32_t col = lane & 15, rsub = (lane >> 4) * 4;
     const __amdgpu_buffer_rsrc_t mine = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(p.out.parts + (size_t)blockIdx.x * (NB * kAccPerBlock)), 0, NB * kAccPerBlock * 4, kBufferFlags);
+        (void*)(p.out.parts + (size_t)wg * (NB * kAccPerBlock)), 0, NB * kAccPerBlock * 4, kBufferFlags);
+    const uint32_t owner = from_start ? 0u : owner_word(p.out, band);  // (read by every wave for itself, so they may differ)
+    bool here = false;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       if (nb > 0) __syncthreads();  // every wave is done reading the buffers of the column block before
@@ -326,8 +330,12 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
       } else if (from_start) {
         red->slot[0][(nb * kRowBlocks + wave) * 64 + lane] = sum;
       } else {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, sum), mine, ((nb * kRowBlocks + wave) * 64 + lane) * 16,
-                                               0, kAuxCoherent);
+        if (nb == 0) here = runs_here(owner);
+        if (here)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, sum), mine, ((nb * kRowBlocks + wave) * 64 + lane) * 16, 0, 0);
+        else
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, sum), mine, ((nb * kRowBlocks + wave) * 64 + lane) * 16,
+                                                 0, kAuxCoherent);
       }
     }
     if (whole) return;
@@ -343,9 +351,11 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
       }
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the partial sum has reached the L2
+      if (!here && lane == 0) red->far = 1;
       __syncthreads();
       if (wave == 0) {
-        release_begin();
+        hs.local = red->far == 0;  // (a part that a wave left in the L2 while another stored through is written back by the release)
+        if (!hs.local) release_begin();
         hs.released = true;
         hs.publish = true;
       }
@@ -375,7 +385,7 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
       ++bandc;
     }
   }
-  hand_over_finish<NB>(p.out, acc, hs, blockIdx.x, gridDim.x, lane);
+  hand_over_finish<NB>(p.out, acc, hs, wg, near_end, lane);
 }
 
 // ---------------------------------------------------------------- host launcher
@@ -452,13 +462,20 @@ hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream) {
   p.out.M = a.M;
   p.out.N = a.N;
   p.out.KT = a.K / kTileK;
-  const int grid = pick_grid(a.M / kTileM, a.K / kTileK, a.num_cus);
+  p.out.raised = a.raised;
   const bool v2 = a.version == 2;
   const int R = (int)plan.rounds;
   for (uint32_t n0 = 0; n0 < a.N; n0 += a.N - n0 <= 16 ? 16 : kGroupCols) {
+    const bool wide = a.N - n0 > 16;
+    const Shares shares = pick_shares(a.M / kTileM, a.K / kTileK, a.num_cus, tile_us(plan.rounds, wide), wide);
+    const int grid = (int)shares.grid;
+    p.out.P = shares.P;
+    p.out.unit = shares.unit;
+    p.out.units = shares.unit ? shares.P / shares.unit : 0u;
+    p.out.bands = a.M / kTileM;
     p.out.n0 = n0;
     hipError_t e;
-    if (a.N - n0 <= 16) e = v2 ? launch_r<1, 8, 2>(R, p, grid, stream) : launch_r<1, 8, 1>(R, p, grid, stream);
+    if (!wide) e = v2 ? launch_r<1, 8, 2>(R, p, grid, stream) : launch_r<1, 8, 1>(R, p, grid, stream);
     else e = v2 ? launch_r<2, 8, 2>(R, p, grid, stream) : launch_r<2, 8, 1>(R, p, grid, stream);
     if (e != hipSuccess) return e;
   }

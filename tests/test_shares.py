@@ -1,0 +1,80 @@
+"""How the passes of up to 32 columns share tiles out to workgroups: the library's rule, asked on the host."""
+import ctypes
+import random
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def shares():
+    import os
+
+    import paper_2309_10285_amd as fls
+    from paper_2309_10285_amd import _build
+
+    if not os.path.exists(fls.LIB_PATH):
+        _build.build()
+    f = fls.lib().fls_internal_shares
+    f.argtypes = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_int, ctypes.c_float, ctypes.c_int, ctypes.POINTER(ctypes.c_uint32)]
+    f.restype = None
+
+    def ask(bands, kt, cus=256, tile_us=0.105, wide=False):
+        out = (ctypes.c_uint32 * 3)()
+        f(bands * 128, kt * 32, cus, tile_us, int(wide), out)
+        return tuple(out)
+
+    return ask
+
+
+def _begin(P, unit, bands, kt, q):
+    return q * bands // P * kt if unit == 0 else q * bands * kt // P
+
+
+def _share(P, unit, block):
+    """The share of a workgroup id, None for an idle one."""
+    if unit == 0:
+        return block if block < P else None
+    x, units = block % 8, P // unit
+    q = x * units // 8 * unit + block // 8
+    return q if q < (x + 1) * units // 8 * unit else None
+
+
+def _shapes(count):
+    rng = random.Random(5)
+    for _ in range(count):
+        bands, kt = int(400 ** rng.random()), int(2000 ** rng.random())
+        yield bands, kt, rng.choice([0.07, 0.105, 0.14, 0.27]), rng.random() < 0.5
+    yield from ((2**20 - 1, 1, 0.105, False), (1, 2**18, 0.105, False), (1, 2**18, 0.27, True), (2**10, 2**10 - 1, 0.07, False))
+
+
+@pytest.mark.parametrize("cus", [1, 8, 20, 64, 256, 304])
+def test_every_share_runs_once_and_holds_tiles(shares, cus):
+    for bands, kt, tile_us, wide in _shapes(1500):
+        P, unit, grid = shares(bands, kt, cus, tile_us, wide)
+        assert 1 <= P <= cus and (unit == 0 or P % unit == 0)
+        assert P * bands * kt < 2**32  # the kernels' share arithmetic is 32 bits wide
+        assert sorted(q for q in (_share(P, unit, b) for b in range(grid)) if q is not None) == list(range(P))
+        begins = [_begin(P, unit, bands, kt, q) for q in range(P + 1)]
+        assert begins[0] == 0 and begins[-1] == bands * kt and all(a < b for a, b in zip(begins, begins[1:]))
+        if unit == 0:
+            assert all(b % kt == 0 for b in begins)
+        elif unit > 1:  # the shares of a band, or of a pair of bands, on one XCD, and at most one workgroup to a CU there
+            assert begins[unit] in (kt, 2 * kt) and -(-P // unit // 8) * unit <= max(1, cus // 8)
+
+
+@pytest.mark.parametrize("bands,kt,tile_us,wide,want", [
+    # us, N = 8 (wide: 32), measured with forced cuts
+    (8, 16, 0.105, False, [8]),     # whole 5.6, in 2 shares 6.7
+    (8, 32, 0.105, False, [32]),    # whole 7.3, in 2 / 4 shares 7.8 / 6.7
+    (8, 64, 0.105, False, [40, 64]),  # whole 10.9, in 4 / 5 / 8 / 10 7.8 / 7.6 / 7.4 / 9.0
+    (8, 32, 0.07, False, [8]),      # 90 %: whole 6.1, in 4 6.4
+    (8, 512, 0.105, False, range(128, 193)),  # in 12 / 16 / 24 12.2 / 11.5 / 11.7
+    (8, 64, 0.125, True, [40]),     # whole 12.8, in 4 / 5 / 8 9.6 / 9.3 / 9.6
+    (384, 8, 0.105, False, [192]),  # two bands to a workgroup 7.3, cut over 256 9.7
+    (384, 384, 0.105, False, [256]),
+    (224, 224, 0.105, False, [224]),
+    (96, 384, 0.105, False, [256]),
+    (168, 224, 0.105, False, [252]),
+])
+def test_the_rule_takes_what_measured_fastest(shares, bands, kt, tile_us, wide, want):
+    assert shares(bands, kt, 256, tile_us, wide)[0] in want
