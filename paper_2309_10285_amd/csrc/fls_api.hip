@@ -556,6 +556,8 @@ void fls_internal_shares(uint32_t M, uint32_t K, int cus, float tile_us, int wid
   out[2] = s.grid;
 }
 
+uint32_t fls_internal_divide(uint32_t n, uint32_t d) { return fls::divide(n, fls::divisor(d)); }
+
 // fls_compress (version 1 or 2) whose kernel gives up at the first word that another workgroup has not published yet, so that it
 // is run again with chunks by ticket.  For tests, not part of the C ABI.
 int fls_internal_compress_impatient(const void* W_dev, int64_t M, int64_t K, void* out_dev, size_t out_capacity, uint32_t version,

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(WAVES * 64) void dense_kernel(DenseParams p) {
   const bool lane_past = kgrp + 8 * H > (K % kDenseK);  // this lane's k are past K in a ragged last step
 
   // load side (ti) runs NS steps ahead of the consume side (tc)
-  uint32_t ti = t0, kti = t0 % KT, bandi = t0 / KT;
+  uint32_t ti = t0, bandi = divide(t0, p.out.by_KT), kti = t0 - bandi * KT;
   uint32_t tc = t0, ktc = kti, bandc = bandi, piece_tiles = 0;
 
   // No branch encloses the ring's loads: a step past the end of the wave's run gets an empty
@@ -314,6 +314,7 @@ hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream) {
   p.out.unit = shares.unit;
   p.out.units = shares.unit ? shares.P / shares.unit : 0u;
   p.out.bands = a.M / kTileM;
+  p.out.by_P = divisor(shares.P);
   const int grid = (int)shares.grid;
   if (a.N > kGroupCols) {
     hipError_t e = launch_xpack(a.X, a.xpack, a.K, a.N, stream);  // the 64-column passes read X in fragment order
@@ -331,6 +332,7 @@ hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream) {
       const uint32_t h = left <= 16 ? 2 : 1;
       p.out.KT = (a.K + 32 * h - 1) / (32 * h);
       p.out.T = (a.M / kTileM) * p.out.KT;
+      p.out.by_KT = divisor(p.out.KT);
       if (left <= 16) e = launch_dense_variant<1, 8, 2, 2>(p, grid, stream);
       else e = launch_dense_variant<2, 8, 2, 1>(p, grid, stream);
       n0 += kGroupCols;

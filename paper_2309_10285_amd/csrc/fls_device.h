@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fls_launch.h"
+
 namespace fls {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -58,6 +60,7 @@ struct OutParams {
   uint32_t unit;    // ... that stay together on an XCD, `units` such groups; 0: shares are whole bands, nothing is handed over
   uint32_t units;
   uint32_t bands;
+  Divisor by_P, by_KT;
   uint32_t M, N;    // N = columns of the whole problem
   uint32_t n0;      // first column of this launch's column group
   uint32_t KT;      // K tiles per band
@@ -97,7 +100,7 @@ __device__ __forceinline__ bool wide_unit(uint32_t quads, uint32_t S, uint32_t G
 
 // First tile of share q: all tiles cut evenly over the shares, or the bands.  (At most kMaxGrid shares, fewer than 2^20 tiles.)
 __device__ __forceinline__ uint32_t share_begin(const OutParams& o, uint32_t q) {
-  return o.unit == 0 ? q * o.bands / o.P * o.KT : q * o.T / o.P;
+  return o.unit == 0 ? divide(q * o.bands, o.by_P) * o.KT : divide(q * o.T, o.by_P);
 }
 
 // This workgroup's share, and the end of the shares that go to the same XCD.  Consecutive workgroup ids go to the chip's
@@ -265,7 +268,8 @@ constexpr uint32_t kSpinLimit = 1u << 20;
 
 // Does share [share0, share1) hold the first tile of a band that it does not hold the last tile of?
 __device__ __forceinline__ bool owns_cut_band(const OutParams& o, uint32_t share0, uint32_t share1) {
-  return share1 % o.KT != 0 && share1 > share0 && share1 - share1 % o.KT >= share0;
+  const uint32_t first = divide(share1, o.by_KT) * o.KT;  // of the band that share1 lies in
+  return first != share1 && first >= share0;
 }
 // By one thread of a workgroup when it starts.
 __device__ __forceinline__ void announce_owner(const OutParams& o, uint32_t wg, uint32_t share0, uint32_t share1) {
@@ -413,7 +417,7 @@ __device__ __forceinline__ void hand_over_piece(const OutParams& o, WgReduceLds<
                                                 HandoverState& st, uint32_t band, uint32_t tiles, uint32_t share0,
                                                 uint32_t share1, uint32_t wg, int lane, bool local_only,
                                                 bool early_release) {
-  const uint32_t seq = band - share0 / o.KT;
+  const uint32_t seq = band - divide(share0, o.by_KT);
   if (tiles == o.KT) {
     store_band<NB>(o, acc, band, lane);  // this wave alone saw the whole band
     wg_reduce_skip<NB>(red, seq, lane);

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
   // A wave's run [t0, t1) is walked piece by piece, a piece being its tiles of one row band
   // [tc, pend).  Load side: tile ti is the next to be requested; consume side: tile tc is the
   // next to be used.
-  uint32_t tc = t0, ktc = t0 % KT, bandc = t0 / KT;
+  uint32_t tc = t0, bandc = divide(t0, p.out.by_KT), ktc = t0 - bandc * KT;
   uint32_t ti = tc, kti = ktc, pend = tc;
 
   // gmem2reg.  No branch may enclose the ring's loads (the compiler's vmcnt bookkeeping would fall
@@ -300,10 +300,10 @@ __global__ __launch_bounds__(WAVES * 64) void spmm_kernel(SpmmParams p) {
   //    the release once all eight parts have reached the L2, and publishes the slot after the loop.
   // (A build that erases the hand-over erases it in every workgroup: were this path left in, its owners would wait
   // out their bounded spin for partial sums that the erased path never publishes.)
-  const bool one_band = !(FLS_ABLATE & (1 | 128)) && share0 / KT == (share1 - 1) / KT && share1 - share0 >= (uint32_t)WAVES;
+  const bool one_band = !(FLS_ABLATE & (1 | 128)) && divide(share0, p.out.by_KT) == divide(share1 - 1, p.out.by_KT) && share1 - share0 >= (uint32_t)WAVES;
   auto one_band_sum = [&](uint32_t band) {
     static_assert(WAVES == kRowBlocks, "one row block per wave");
-    const bool from_start = share0 % KT == 0, to_end = share1 % KT == 0;
+    const bool from_start = share0 == band * KT, to_end = share1 == (band + 1) * KT;
     const bool whole = (from_start && to_end) || (FLS_ABLATE & 64);
     const uint32_t col = lane & 15, rsub = (lane >> 4) * 4;
     const __amdgpu_buffer_rsrc_t mine = __builtin_amdgcn_make_buffer_rsrc(
@@ -473,6 +473,8 @@ hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream) {
     p.out.unit = shares.unit;
     p.out.units = shares.unit ? shares.P / shares.unit : 0u;
     p.out.bands = a.M / kTileM;
+    p.out.by_P = divisor(shares.P);
+    p.out.by_KT = divisor(p.out.KT);
     p.out.n0 = n0;
     hipError_t e;
     if (!wide) e = v2 ? launch_r<1, 8, 2>(R, p, grid, stream) : launch_r<1, 8, 1>(R, p, grid, stream);

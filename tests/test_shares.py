@@ -78,3 +78,17 @@ def test_every_share_runs_once_and_holds_tiles(shares, cus):
 ])
 def test_the_rule_takes_what_measured_fastest(shares, bands, kt, tile_us, wide, want):
     assert shares(bands, kt, 256, tile_us, wide)[0] in want
+
+
+def test_division_by_multiplication(shares):
+    """Exact below 2^29 for every divisor a launch can have (shares up to 512, K tiles up to 2^18)."""
+    import paper_2309_10285_amd as fls
+
+    f = fls.lib().fls_internal_divide
+    f.argtypes, f.restype = [ctypes.c_uint32] * 2, ctypes.c_uint32
+    rng = random.Random(6)
+    for d in [*range(1, 600), *(rng.randrange(600, 2**18 + 1) for _ in range(400)), 2**18, 2**18 - 1]:
+        for q in (0, 1, 2**29 // d - 1, *(rng.randrange(2**29 // d) for _ in range(8))):
+            for n in (q * d - 1, q * d, q * d + d - 1):
+                if 0 <= n < 2**29:
+                    assert f(n, d) == n // d, (n, d)
