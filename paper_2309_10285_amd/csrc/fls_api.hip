@@ -40,6 +40,7 @@ constexpr size_t kScratchBytes = kScratchControlBytes + kScratchPartsBytes;
 static __device__ __align__(256) __attribute__((used)) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};  // by device id; guarded by g_mu
+uint32_t g_scratch_calls = 0;                    // calls of fls_spmm_noalloc; guarded by g_mu
 
 // Address of `scratch` on the current device (nullptr after setting *err on failure).
 unsigned char* scratch_on_current_device(int* err) {
@@ -490,9 +491,14 @@ int fls_spmm_noalloc(const void* Wc_dev, const fls_stats* stats_host, const void
   const int cus = num_cus();
   if (cus <= 0) return FLS_EHIP;
   hipStream_t s = (hipStream_t)stream;
-  // the array keeps what the last call left: flags and error word start every call at zero (a fill
-  // kernel, not a memset node, so that the call can be recorded into a graph)
-  if (fls::launch_fill_zero(ptr, kScratchControlBytes, s) != hipSuccess) return FLS_EHIP;
+  // Every call leaves its flags lowered.  A call's flags bear its number, so one that a call which gave up left raised is not taken for
+  // its own by a later call.
+  uint32_t number;
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    number = ++g_scratch_calls;
+    if (number == 0) number = ++g_scratch_calls;
+  }
   fls::SpmmLaunch a;
   a.offs = (const uint32_t*)((const unsigned char*)Wc_dev + FLS_HEADER_BYTES);
   a.words = a.offs + n_off_of(num_tiles(M, K));
@@ -507,7 +513,7 @@ int fls_spmm_noalloc(const void* Wc_dev, const fls_stats* stats_host, const void
   a.max_tile_words = (uint32_t)stats_host->max_tile_words;
   a.version = stats_host->format_version;
   a.num_cus = cus;
-  a.raised = 1u;
+  a.raised = number;
   a.wide32 = false;  // the static array has the narrow kernel's partial sums only
   return fls::launch_spmm(a, s) == hipSuccess ? FLS_OK : FLS_EHIP;
 }
