@@ -1,6 +1,7 @@
 // Host-side launch descriptors: the C ABI layer fills these, each kernel file implements its launcher.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace fls {
@@ -163,36 +164,9 @@ inline uint32_t block_rounds(uint32_t share, uint32_t need) {
 // fp32 values of the split-K partial sums: [workgroup][column blocks][128 x 16] for the passes of
 // up to 32 columns, [band][slice][4][128 x 16] for the 64-column pass
 inline size_t parts_floats(uint32_t N) {
-  // (from 17 columns on: a call of 17 - 32 columns takes the 64-column pass where that is faster, see wide32_pays)
+  // (from 17 columns on: a call of 17 - 32 columns takes the 64-column pass where that is faster, see wide_pays)
   if (N > 16u) return (size_t)4 * kMaxWorkgroups * 4 * 2048;
   return (size_t)kMaxWorkgroups * group_blocks(N) * 2048;
-}
-
-// A call (or the rest of a call) of 17 - 32 columns: the narrow kernel with two column blocks per wave, or the
-// 64-column pass multiplying only its first 32-column block.  Every tile asks for 2 KB of X here, as much as a
-// sparse tile's words, and the narrow kernel's waves fetch X from L2 each for themselves; the pass shares X between
-// four bands through LDS.  Measured in format version 1 (us, narrow / pass): 12288 x 49152 at 90 % 73.7 / 63.2, 80 %
-// 105.0 / 93.7, 70 % 135.5 / 117.5, 60 % 164.4 / 150.0, 50 % 200.1 / 184.7; 49152 x 12288 at 90 - 60 % 74.3 / 70.0,
-// 104.6 / 101.7, 134.7 / 128.6, 164.4 / 157.6; 12288 x 24576 at 70 % 73.1 / 66.5; 12288 x 12288 at 90 - 50 % 28.2 / 27.3,
-// 37.0 / 35.3, 44.2 / 41.3, 51.7 / 49.6, 60.8 / 58.5; but 28672 x 7168 at 90 % 28.7 / 31.4, at 80 % 40.3 / 41.6,
-// 7168 x 7168 16.0 / 19.0: the pass pays its second kernel and needs long bands.  So, in version 1: bands of at
-// least 384 K tiles, any tile the pass can stage (ten rounds).
-// In format version 2 the narrow kernel has a quarter fewer bytes to wait for and stays ahead longer (12288 x
-// 12288: 32.9 / 34.7 at 80 %, 26.2 / 27.2 at 90 %; 12288 x 49152 at 90 %: 65.6 / 62.7, at 70 %: 114.1 / 116.1; 49152 x
-// 12288 at 70 %: 113.8 / 136.6): tiles of up to four rounds on bands of at least 1024 K tiles.
-// Bands of 288 - 383 K tiles: the pass still wins where its K slices come out even and the tiles are not the
-// sparsest (27648 x 9216 at 70 % 61.9 / 59.0, at 80 % 49.0 / 47.2, at 90 % 34.8 / 35.1; 20480 x 9216 at 80 % 42.1 /
-// 37.7; 12288 x 10240 at 80 % 32.6 / 31.2, at 60 % 45.3 / 43.8; but 12288 x 9216 at 80 %, whose ten slices are
-// three or four bodies long, 30.5 / 31.0, and 12288 x 8192 at 80 % 27.5 / 30.6).
-inline bool wide32_pays(uint32_t max_tile_words, uint32_t round_words, uint32_t KT, uint32_t version, uint32_t bands, int cus) {
-  if (version == 2u) return max_tile_words <= 4u * round_words && KT >= 1024u;
-  if (max_tile_words > 10u * round_words) return false;
-  if (KT >= 384u) return true;
-  if (KT < 288u || max_tile_words <= 2u * round_words) return false;
-  // the longest K slice at most a tenth above the mean (bodies of 8 tiles up to four rounds, of 4 beyond: as the pass picks them)
-  const uint32_t body = wide_body((max_tile_words + round_words - 1u) / round_words);
-  const uint32_t bodies = KT / body, S = wide_quad_slices(bands, 1u, KT, cus, body);
-  return (uint64_t)((bodies + S - 1u) / S) * S * 10u <= (uint64_t)bodies * 11u;
 }
 
 // Workspace bytes for X repacked into MFMA fragment order, [K tile][column block][lane][8 halves]
@@ -210,6 +184,8 @@ struct Shares {
 };
 // What a tile costs a workgroup, in us, by the rounds that its variant stages (tiles of W that was left dense: 0.27).
 inline float tile_us(uint32_t rounds, bool wide) { return 0.035f + 0.0175f * (float)rounds + (wide ? 0.02f : 0.f); }
+// ... and a hand-over, of a band cut into k shares on one XCD.
+inline float hand_over_us(uint32_t k, bool wide) { return wide ? 1.9f + 0.52f * (float)(k / 2u) : 1.6f + 0.6f * (float)((k + 2u) / 4u); }
 inline Shares shares_of(uint32_t P, uint32_t unit) { return {P, unit, unit == 0 ? P : (P / unit + 7u) / 8u * unit * 8u}; }
 // Shares that cut bands.  Those of one band, or of a pair of bands, stay together where no XCD gets more workgroups than it has CUs.
 inline Shares cut_shares(uint32_t P, uint32_t bands, int cus) {
@@ -242,7 +218,7 @@ inline Shares pick_shares(uint32_t bands, uint32_t KT, int cus, float tile_us, b
     uint32_t best = 1;
     float us = tile_us * (float)KT;
     for (uint32_t k = 2; k <= most && k * 8u <= KT; ++k) {
-      float t = tile_us * (float)((KT + k - 1u) / k) + (wide ? 1.9f + 0.52f * (float)(k / 2u) : 1.6f + 0.6f * (float)((k + 2u) / 4u));
+      float t = tile_us * (float)((KT + k - 1u) / k) + hand_over_us(k, wide);
       if (cut_shares(bands * k, bands, cus).unit != k) t += 1.5f;
       if (t < us) {
         us = t;
@@ -261,6 +237,53 @@ inline Shares pick_shares(uint32_t bands, uint32_t KT, int cus, float tile_us, b
   const int halves = (int)bands * (2 * cus / (int)bands);
   if (halves % 2 == 0 && halves / 2 * 100 >= cus * 97) return cut_shares((uint32_t)halves / 2u, bands, cus);
   return cut_shares((uint32_t)cus, bands, cus);
+}
+
+// A call of 17 - 64 columns: passes of up to 32 columns, or the 64-column pass (up to 32 columns with one 32-column block multiplied).
+// The narrow kernel streams W once per 32 columns and fetches X per tile and wave; the pass shares X between four bands and
+// streams W once, but cuts K into slices whose sums a second kernel adds.  Which one is an estimate of each in us:
+//   narrow, a pass   4.9 + the larger of 1.02 tile_us x tiles of a workgroup and W at 7.3 TB/s + 64 B of X per tile and column at 8.8 TB/s + the
+//                    hand-over of pick_shares, 1.5 more where the shares of a band are not kept on one XCD
+//   64 columns       6.7 + for a round of workgroups (0.16 + 0.081 R) x tiles of its bodies (0.9 of it with one block) + 1.09 x the K tiles that fill
+//                    no body, or W at 8 TB/s, whichever is larger (fourth powers added); and the partial sums out and back at 4.35 TB/s
+// fitted to 300 products (M 1024 ... 49152, K 1024 ... 49152, 60 - 90 %, both formats; rms 5.5 and 7.5 %).  Its pick takes 1.005 times the better one of
+// the two, and 0.964 and 0.85 times what the pass for all calls of 33 - 64 and a rule on K and density for 17 - 32 columns took.  Some of
+// what was measured (us, narrow / 64-column): N = 64, 80 %: 1024 x 1024 16.3 / 15.0, 32768 x 1024
+// 18.3 / 26.5, 8192 x 8192 35.2 / 35.4, 12288 x 12288 63.7 / 43.8; at 90 % 8192 x 8192 27.7 / 32.7 (and 16384 x 4096 26.4 / 32.5, where it picks the pass); N = 31: 8832 x 48736 at 90 %
+// 62.6 / 51.9, 6272 x 13440 at 90 % 16.6 / 25.4, 16128 x 10400 at 80 % 29.6 / 43.5; N = 32, 27648 x 9216 at 70 % 62.5 / 58.4.
+inline float words_bytes(uint32_t max_tile_words, uint32_t version, uint32_t bands, uint32_t KT) {  // from the longest tile: four deviations above the mean
+  const float longest = version == 2u ? (float)max_tile_words * (4.f / 3.f) : (float)max_tile_words;
+  const float mean = longest - 4.f * sqrtf(longest) > 0.5f * longest ? longest - 4.f * sqrtf(longest) : 0.5f * longest;
+  return (float)bands * (float)KT * mean * (version == 2u ? 3.f : 4.f);
+}
+inline float narrow_us(float w_bytes, uint32_t rounds, uint32_t bands, uint32_t KT, uint32_t N, int cus) {
+  float us = 0.f;
+  for (uint32_t n0 = 0; n0 < N; n0 += N - n0 <= 16u ? 16u : kGroupCols) {
+    const bool wide = N - n0 > 16u;
+    const float tile = tile_us(rounds < 8u ? rounds : 8u, wide), T = (float)bands * (float)KT;
+    const Shares s = pick_shares(bands, KT, cus, tile, wide);
+    const uint32_t cols = N - n0 < kGroupCols ? N - n0 : kGroupCols;
+    const float work = 1.02f * tile * T / (float)s.P, memory = w_bytes / 7.3e6f + T * (float)cols * 64.f / 8.8e6f;
+    us += 4.9f + (work > memory ? work : memory);
+    if (s.unit != 0u) us += hand_over_us(s.unit > 1u ? s.unit : s.P / bands + 1u, wide) + (s.unit > 1u ? 0.f : 1.5f);
+  }
+  return us;
+}
+inline float wide_us(float w_bytes, uint32_t rounds, uint32_t bands, uint32_t KT, uint32_t N, int cus) {  // N <= 64
+  const uint32_t body = wide_body(rounds), quads = (bands + 3u) / 4u, S = wide_quad_slices(bands, 1u, KT, cus, body);
+  const uint32_t bodies = (KT / body + S - 1u) / S, turns = (quads * S + (uint32_t)cus - 1u) / (uint32_t)cus;
+  const float work = (float)(bodies * body) * (0.16f + 0.081f * (float)rounds) * (N <= kGroupCols ? 0.9f : 1.f) + 1.09f * (float)(KT % body);
+  const float memory = w_bytes / 8.0e6f;
+  float us = 6.7f + (float)turns * sqrtf(sqrtf(work * work * work * work + memory * memory * memory * memory));
+  if (S > 1u) us += 0.07f * (float)(1u + S / 8u) + 2.f * (float)bands * (float)S * (N <= kGroupCols ? 16384.f : 32768.f) / 4.35e6f;
+  return us;
+}
+// `rounds` of the variant that the pass would run; version 2 has variants with one block for tiles of up to four rounds.  (Up to 32 columns
+// on short bands stay with the narrow kernel, which checks the offsets it reads against the header, whatever the estimate.)
+inline bool wide_pays(uint32_t max_tile_words, uint32_t rounds, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus) {
+  if (N <= kGroupCols && (version == 2u ? rounds > 4u || KT < 1024u : KT < 288u)) return false;
+  const float w = words_bytes(max_tile_words, version, bands, KT);
+  return 0.98f * wide_us(w, rounds, bands, KT, N, cus) < narrow_us(w, rounds, bands, KT, N, cus);
 }
 
 // Arguments of the 64-column passes (sparse and dense) and of the kernel that adds their K slices.
@@ -284,7 +307,7 @@ struct SpmmPlan {
   SpmmPass pass;
   uint32_t share;   // block pass: 1 or 2, else 0
   uint32_t rounds;  // rounds of a tile that the variant stages
-  uint32_t slices;  // K slices (block and 64-column pass), else 0
+  uint32_t slices;  // K slices (block and 64-column pass); narrow: 1 where the 64-column pass could run too, else 0
 };
 SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus, bool wide32);
 hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream);

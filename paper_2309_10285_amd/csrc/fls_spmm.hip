@@ -432,7 +432,9 @@ SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, ui
   // The 64-column pass stages at most ten rounds of a tile (it has no slow path for more; twelve
   // rounds no longer fit its registers): a matrix with denser tiles - less than 40 % sparse
   // somewhere - takes 32-column passes throughout.
-  if (N > kGroupCols ? need <= 10u : N > 16u && wide32 && wide32_pays(max_tile_words, round_words, KT, version, bands, cus)) {
+  const bool possible = N > 16u && need <= 10u && (N > kGroupCols || wide32);
+  // (the narrow kernel stages eight rounds, and what a tile has beyond goes a slow way that the estimate leaves out)
+  if (possible && (N > kSpmmGroupCols || need > 8u || wide_pays(max_tile_words, wide_rounds(need), version, bands, KT, N, cus))) {
     // ... and beyond 64 columns it or the block pass takes all columns of the call, whichever the estimate prefers
     const uint32_t share = N > kSpmmGroupCols ? spmm_pass_share(need, bands, KT, N, cus) : 0u;
     if (share > 0)
@@ -440,7 +442,7 @@ SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, ui
     const uint32_t rounds = wide_rounds(need);
     return {SpmmPass::kWide, 0u, rounds, wide_quad_slices(bands, groups, KT, cus, wide_body(rounds))};
   }
-  return {SpmmPass::kNarrow, 0u, need <= 8u ? wide_rounds(need) : 8u, 0u};
+  return {SpmmPass::kNarrow, 0u, need <= 8u ? wide_rounds(need) : 8u, possible ? 1u : 0u};
 }
 
 hipError_t launch_spmm(const SpmmLaunch& a, hipStream_t stream) {

@@ -92,3 +92,24 @@ def test_division_by_multiplication(shares):
             for n in (q * d - 1, q * d, q * d + d - 1):
                 if 0 <= n < 2**29:
                     assert f(n, d) == n // d, (n, d)
+
+
+@pytest.mark.parametrize("rounds,version,M,K,N,want", [
+    # us, passes of up to 32 columns / 64-column pass
+    (4, 1, 1024, 1024, 64, "wide"),       # 16.3 / 15.0
+    (4, 1, 32768, 1024, 64, "narrow"),    # 18.3 / 26.5
+    (4, 1, 12288, 12288, 64, "wide"),     # 63.7 / 43.8
+    (2, 1, 8192, 8192, 33, "narrow"),     # 25.1 / 31.2
+    (2, 1, 8832, 48736, 31, "wide"),      # 62.6 / 51.9
+    (2, 1, 6272, 13440, 27, "narrow"),    # 16.6 / 25.4
+    (4, 1, 16128, 10400, 19, "narrow"),   # 29.6 / 43.5
+    (6, 1, 27648, 9216, 32, "wide"),      # 62.5 / 58.4
+    (6, 2, 12288, 49152, 32, "narrow"),   # version 2 has variants with one column block for up to four rounds
+    (9, 1, 32768, 1024, 64, "wide"),      # the narrow kernel stages eight rounds
+])
+def test_the_rule_for_17_to_64_columns(shares, rounds, version, M, K, N, want):
+    import paper_2309_10285_amd as fls
+
+    stats = {"max_tile_words": rounds * (256 if version == 1 else 192) - 12, "format_version": version, "M": M, "K": K}
+    assert fls.spmm_plan(stats, N)["pass"] == want
+    assert fls.spmm_plan(stats, min(N, 32), entry="fls_spmm_noalloc")["pass"] == "narrow"
