@@ -88,14 +88,21 @@ inline uint32_t group_blocks(uint32_t ncols) { return ncols <= 16 ? 1u : (ncols 
 constexpr uint32_t kMaxWorkgroups = 512;    // must equal fls::kMaxGrid of the device code
 // The 64-column pass of the dense kernel cuts its work as (group of 4 bands) x (K slice), one wave
 // per band, and keeps one 128 x 64 fp32 partial result per band and slice.  Slices per group: as
-// many as fill the CUs, but none shorter than 16 steps.  groups * slices <= kMaxWorkgroups, so
+// many as fill the CUs, but none shorter than two steps of 64 k (at least 16 steps before: 1408 x 1120,
+// N = 182 37.9 us against 17.6 with four steps and 18.0 with two, 5120 x 1120, N = 51 71.2 / 24.2 / 22.8, 1280 x 1888, N = 97 90.0 / 21.4 / 18.3;
+// 100 drawn products of 33 - 256 columns 1.55 and 1.58 times faster).  groups * slices <= kMaxWorkgroups, so
 // bands * slices <= 4 * kMaxWorkgroups partial results at most (what parts_floats provides).
 inline uint32_t wide_slices(uint32_t bands, uint32_t col_groups, uint32_t KT, int cus) {
   if (cus > (int)kMaxWorkgroups) cus = (int)kMaxWorkgroups;
   const uint64_t units = (uint64_t)((bands + 3) / 4) * col_groups;  // (group of four bands, group of 64 columns)
   uint32_t S = units < (uint64_t)cus ? (uint32_t)((uint64_t)cus / units) : 1u;
-  const uint32_t by_length = KT / 16u > 0 ? KT / 16u : 1u;
+  const uint32_t by_length = KT / 2u > 0 ? KT / 2u : 1u;
   return S < by_length ? S : by_length;
+}
+// Steps that a CU takes one after the other in that pass.
+inline uint32_t wide_steps(uint32_t bands, uint32_t col_groups, uint32_t KT, int cus) {
+  const uint32_t S = wide_slices(bands, col_groups, KT, cus), wgs = (bands + 3u) / 4u * col_groups * S;
+  return (wgs + (uint32_t)cus - 1u) / (uint32_t)cus * ((KT + S - 1u) / S);
 }
 // The sparse 64-column pass: a workgroup takes four bands (one per wave), a group of 64 columns and a
 // K slice made of whole loop bodies of `body` tiles, and writes one partial result per band, column

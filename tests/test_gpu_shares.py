@@ -61,6 +61,23 @@ def test_products_of_every_cut(fls, oracle_mod, bands, kt, N, version):
     fls.fls_forget(blob)
 
 
+@pytest.mark.parametrize("N", [33, 64, 66, 80, 97, 143, 200])
+@pytest.mark.parametrize("bands,kt", [(1, 1), (3, 3), (9, 5), (5, 131), (241, 2)])
+def test_dense_products_of_many_columns(fls, oracle_mod, bands, kt, N):
+    """K slices down to two steps of 64 k, a half last step, and a rest of up to 32 columns in the launch of the others or in a pass of its own."""
+    import torch
+
+    M, K = bands * 128, kt * 32
+    W, X, Wd, Xd = _operands(bands, kt, N, 0.3, 7500 + 13 * bands + kt)
+    ref = oracle_mod.ref_spmm_f64(W, X)
+    fls.ensure_workspace(M, K, N)
+    for _ in range(2):
+        C = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
+        fls.fls_dense_gemm(Wd, Xd, C, M, K, N)
+        assert float(np.abs(C.cpu().numpy().astype(np.float64) - ref).max()) / float(np.abs(ref).max()) <= TOL
+    fls.fls_check_workspace()
+
+
 @pytest.mark.parametrize("entry", ["fls_spmm_stats", "fls_spmm_noalloc"])
 def test_two_matrices_in_one_graph_with_eager_calls_between_replays(fls, oracle_mod, entry):
     """Slots and flags change hands between two matrices with different cuts, in graph order and out of it."""
