@@ -9,7 +9,9 @@ used for device memory and streams only:
 There is no CPU fallback: without the built library, or without a GPU, calls raise.
 """
 import ctypes
+import operator
 import os
+import struct
 
 TILE_M = 128
 TILE_K = 32
@@ -37,7 +39,19 @@ class FlsStats(ctypes.Structure):
                 ("bytes_offsets", ctypes.c_uint64), ("bytes_nonzeros", ctypes.c_uint64)]
 
     def as_dict(self):
-        return {k: int(getattr(self, k)) for k, _ in self._fields_}
+        return dict(zip(_STATS_NAMES, _STATS_LAYOUT.unpack_from(self)))
+
+
+# A call of a few microseconds feels every attribute that Python looks up, so a struct is filled and read in one go, pointers go to
+# ctypes as integers, and the current stream is asked for as a number.
+_STATS_NAMES = tuple(k for k, _ in FlsStats._fields_)
+_STATS_LAYOUT = struct.Struct("<4I9Q")
+_stats_values = operator.itemgetter(*_STATS_NAMES)
+assert _STATS_LAYOUT.size == ctypes.sizeof(FlsStats)
+
+
+def _stats_struct(stats):
+    return FlsStats.from_buffer_copy(_STATS_LAYOUT.pack(*_stats_values(stats)))
 
 
 class FlsError(RuntimeError):
@@ -93,9 +107,10 @@ def strerror(code):
 
 
 def _stream():
+    """The current stream of the current device, as hipStream_t."""
     import torch
 
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(rc, where):
@@ -124,7 +139,7 @@ def fls_workspace_bytes(M, K, N):
 def fls_set_workspace(ws):
     """ws: uint8 CUDA tensor (caller-owned device memory); kept referenced until replaced."""
     global _ws_tensor
-    _check(lib().fls_set_workspace(ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size(), _stream()),
+    _check(lib().fls_set_workspace(ws.data_ptr(), ws.numel() * ws.element_size(), _stream()),
            "fls_set_workspace")
     _ws_tensor = ws
 
@@ -149,7 +164,7 @@ def fls_compress(W, out=None, order_policy=ORDER_LOCATION):
     if out is None:
         out = torch.empty(fls_compress_bound(M, K), dtype=torch.uint8, device=W.device)
     st = FlsStats()
-    rc = lib().fls_compress(ctypes.c_void_p(W.data_ptr()), M, K, ctypes.c_void_p(out.data_ptr()), out.numel(),
+    rc = lib().fls_compress(W.data_ptr(), M, K, out.data_ptr(), out.numel(),
                             order_policy, ctypes.byref(st), _stream())
     _check(rc, "fls_compress")
     return out[:st.bytes_total], st.as_dict()
@@ -170,7 +185,7 @@ def fls_compress_v2(W, out=None):
     if out is None:
         out = torch.empty(fls_compress_bound_v2(M, K), dtype=torch.uint8, device=W.device)
     st = FlsStats()
-    rc = lib().fls_compress_v2(ctypes.c_void_p(W.data_ptr()), M, K, ctypes.c_void_p(out.data_ptr()), out.numel(),
+    rc = lib().fls_compress_v2(W.data_ptr(), M, K, out.data_ptr(), out.numel(),
                                ctypes.byref(st), _stream())
     _check(rc, "fls_compress_v2")
     return out[:st.bytes_total], st.as_dict()
@@ -180,10 +195,10 @@ def fls_spmm(blob, X, C, M, K, N):
     import torch
 
     assert blob.is_cuda and blob.dtype == torch.uint8 and blob.is_contiguous()
-    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and tuple(X.shape) == (N, K)
-    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and tuple(C.shape) == (N, M)
-    _check(lib().fls_spmm(ctypes.c_void_p(blob.data_ptr()), ctypes.c_void_p(X.data_ptr()),
-                          ctypes.c_void_p(C.data_ptr()), M, K, N, _stream()), "fls_spmm")
+    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape == (N, K)
+    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and C.shape == (N, M)
+    _check(lib().fls_spmm(blob.data_ptr(), X.data_ptr(),
+                          C.data_ptr(), M, K, N, _stream()), "fls_spmm")
     return C
 
 
@@ -193,11 +208,11 @@ def fls_spmm_stats(blob, stats, X, C, M, K, N):
     import torch
 
     assert blob.is_cuda and blob.dtype == torch.uint8 and blob.is_contiguous()
-    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and tuple(X.shape) == (N, K)
-    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and tuple(C.shape) == (N, M)
-    st = FlsStats(**{k: stats[k] for k, _ in FlsStats._fields_})
-    _check(lib().fls_spmm_stats(ctypes.c_void_p(blob.data_ptr()), ctypes.byref(st), ctypes.c_void_p(X.data_ptr()),
-                                ctypes.c_void_p(C.data_ptr()), M, K, N, _stream()), "fls_spmm_stats")
+    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape == (N, K)
+    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and C.shape == (N, M)
+    st = _stats_struct(stats)
+    _check(lib().fls_spmm_stats(blob.data_ptr(), ctypes.byref(st), X.data_ptr(),
+                                C.data_ptr(), M, K, N, _stream()), "fls_spmm_stats")
     return C
 
 
@@ -207,11 +222,11 @@ def fls_spmm_noalloc(blob, stats, X, C, M, K, N):
     import torch
 
     assert blob.is_cuda and blob.dtype == torch.uint8 and blob.is_contiguous()
-    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and tuple(X.shape) == (N, K)
-    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and tuple(C.shape) == (N, M)
-    st = FlsStats(**{k: stats[k] for k, _ in FlsStats._fields_})
-    _check(lib().fls_spmm_noalloc(ctypes.c_void_p(blob.data_ptr()), ctypes.byref(st), ctypes.c_void_p(X.data_ptr()),
-                                  ctypes.c_void_p(C.data_ptr()), M, K, N, _stream()), "fls_spmm_noalloc")
+    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape == (N, K)
+    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and C.shape == (N, M)
+    st = _stats_struct(stats)
+    _check(lib().fls_spmm_noalloc(blob.data_ptr(), ctypes.byref(st), X.data_ptr(),
+                                  C.data_ptr(), M, K, N, _stream()), "fls_spmm_noalloc")
     return C
 
 
@@ -222,10 +237,10 @@ def prepare_spmm(blob, X, C, M, K, N):
     import torch
 
     assert blob.is_cuda and blob.dtype == torch.uint8 and blob.is_contiguous()
-    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and tuple(X.shape) == (N, K)
-    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and tuple(C.shape) == (N, M)
+    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape == (N, K)
+    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and C.shape == (N, M)
     f = lib().fls_spmm
-    args = (ctypes.c_void_p(blob.data_ptr()), ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(C.data_ptr()),
+    args = (blob.data_ptr(), X.data_ptr(), C.data_ptr(),
             M, K, N, _stream())
     keep = (blob, X, C)  # the tensors stay alive as long as the callable does
 
@@ -242,12 +257,12 @@ def prepare_spmm_noalloc(blob, stats, X, C, M, K, N):
     import torch
 
     assert blob.is_cuda and blob.dtype == torch.uint8 and blob.is_contiguous()
-    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and tuple(X.shape) == (N, K)
-    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and tuple(C.shape) == (N, M)
+    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape == (N, K)
+    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and C.shape == (N, M)
     f = lib().fls_spmm_noalloc
-    st = FlsStats(**{k: stats[k] for k, _ in FlsStats._fields_})
-    args = (ctypes.c_void_p(blob.data_ptr()), ctypes.byref(st), ctypes.c_void_p(X.data_ptr()),
-            ctypes.c_void_p(C.data_ptr()), M, K, N, _stream())
+    st = _stats_struct(stats)
+    args = (blob.data_ptr(), ctypes.byref(st), X.data_ptr(),
+            C.data_ptr(), M, K, N, _stream())
     keep = (blob, X, C, st)
 
     def call(_keep=keep):
@@ -262,11 +277,11 @@ def prepare_dense_gemm(W, X, C, M, K, N):
     """As prepare_spmm, for fls_dense_gemm."""
     import torch
 
-    assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous() and tuple(W.shape) == (M, K)
-    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and tuple(X.shape) == (N, K)
-    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and tuple(C.shape) == (N, M)
+    assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous() and W.shape == (M, K)
+    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape == (N, K)
+    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and C.shape == (N, M)
     f = lib().fls_dense_gemm
-    args = (ctypes.c_void_p(W.data_ptr()), ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(C.data_ptr()),
+    args = (W.data_ptr(), X.data_ptr(), C.data_ptr(),
             M, K, N, _stream())
     keep = (W, X, C)
 
@@ -293,15 +308,15 @@ def fls_check_workspace():
 
 
 def fls_forget(blob=None):
-    lib().fls_forget(ctypes.c_void_p(blob.data_ptr()) if blob is not None else None)
+    lib().fls_forget(blob.data_ptr() if blob is not None else None)
 
 
 def fls_dense_gemm(W, X, C, M, K, N):
     import torch
 
-    assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous() and tuple(W.shape) == (M, K)
-    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and tuple(X.shape) == (N, K)
-    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and tuple(C.shape) == (N, M)
-    _check(lib().fls_dense_gemm(ctypes.c_void_p(W.data_ptr()), ctypes.c_void_p(X.data_ptr()),
-                                ctypes.c_void_p(C.data_ptr()), M, K, N, _stream()), "fls_dense_gemm")
+    assert W.is_cuda and W.dtype == torch.float16 and W.is_contiguous() and W.shape == (M, K)
+    assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape == (N, K)
+    assert C.is_cuda and C.dtype == torch.float16 and C.is_contiguous() and C.shape == (N, M)
+    _check(lib().fls_dense_gemm(W.data_ptr(), X.data_ptr(),
+                                C.data_ptr(), M, K, N, _stream()), "fls_dense_gemm")
     return C
