@@ -172,12 +172,12 @@ __global__ __launch_bounds__(256) void dense_wide_kernel(WideParams p) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t group, slice, cg;
-  if (!wide_unit((p.bands + 3u) / 4u, p.S, p.G, p.whole, group, slice, cg)) return;
+  if (!wide_unit(p, (p.bands + 3u) / 4u, group, slice, cg)) return;
   const uint32_t n0 = p.n0 + cg * 64u;
   const uint32_t band = group * 4 + wave;
   if (band >= p.bands) return;
   const uint32_t K = p.K, KT = p.KT;  // KT: steps of 64 k per band (the last one may be half)
-  const uint32_t s0 = (uint32_t)((uint64_t)slice * KT / p.S), s1 = (uint32_t)((uint64_t)(slice + 1) * KT / p.S);
+  const uint32_t s0 = divide(slice * KT, p.by_S), s1 = divide((slice + 1) * KT, p.by_S);
 
   float4v acc[kRowBlocks][NB];
 #pragma unroll
@@ -292,6 +292,9 @@ static hipError_t launch_dense_wide(const DenseLaunch& a, uint32_t n0, uint32_t 
   const uint32_t groups = (p.bands + 3u) / 4u;
   p.whole = whole_pairs(groups * p.S, col_groups, a.num_cus);
   const uint32_t grid = wide_grid(groups * p.S, col_groups, p.whole);
+  p.by_S = divisor(p.S);
+  p.by_G = divisor(p.G);
+  p.by_groups = divisor(groups);
   hipLaunchKernelGGL((dense_wide_kernel<kDenseWideRing>), dim3(grid), dim3(256), 0, stream, p);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && p.S > 1) e = launch_wide_reduce(p, false, stream);

@@ -81,19 +81,19 @@ __device__ __forceinline__ bool xcd_unit(uint32_t units, uint32_t& unit) {
 // `whole` (see whole_pairs of the launchers): (quad, slice) pair 8 i + x goes to XCD x with all its column groups.
 // Otherwise every XCD takes an eighth of all units, slice by slice.  (Two branches, not one formula with selects: that cost 1 - 2 % of
 // calls of 5 - 10 us and half a percent of longer ones.)
-__device__ __forceinline__ bool wide_unit(uint32_t quads, uint32_t S, uint32_t G, bool whole, uint32_t& quad, uint32_t& slice, uint32_t& cg) {
-  if (whole) {
-    const uint32_t i = blockIdx.x >> 3, pair = i / G * 8u + (blockIdx.x & 7u);
-    cg = i % G;
-    quad = pair / S;
-    slice = pair - quad * S;
-    return pair < quads * S;
+__device__ __forceinline__ bool wide_unit(const WideParams& p, uint32_t quads, uint32_t& quad, uint32_t& slice, uint32_t& cg) {
+  if (p.whole) {
+    const uint32_t i = blockIdx.x >> 3, j = divide(i, p.by_G), pair = j * 8u + (blockIdx.x & 7u);
+    cg = i - j * p.G;
+    quad = divide(pair, p.by_S);
+    slice = pair - quad * p.S;
+    return pair < quads * p.S;
   }
   uint32_t unit;
-  if (!xcd_unit(quads * S * G, unit)) return false;
-  const uint32_t pair = unit / G;
-  cg = unit - pair * G;
-  slice = pair / quads;
+  if (!xcd_unit(quads * p.S * p.G, unit)) return false;
+  const uint32_t pair = divide(unit, p.by_G);
+  cg = unit - pair * p.G;
+  slice = divide(pair, p.by_groups);
   quad = pair - slice * quads;
   return true;
 }

@@ -303,6 +303,7 @@ struct WideParams {
   _Float16* C;
   float* parts;           // [band][slice][column block][row block][lane] float4, used when S > 1
   uint32_t M, K, N, n0, KT, bands, S;
+  Divisor by_S, by_G, by_groups;  // of S, G (block pass: of 8 x its column groups), groups of bands
   bool whole;  // whole_pairs: how workgroups spread over the XCDs (64-column passes)
   uint32_t G;  // groups of 64 columns in the launch, from column n0 on (sparse pass; 1 in the dense pass)
   uint32_t cb; // 32-column blocks of a group that are multiplied and hold sums (sparse pass: 2, or 1 for a call of at most 32 columns)

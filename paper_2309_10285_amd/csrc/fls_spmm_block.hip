@@ -64,16 +64,16 @@ __global__ __launch_bounds__(kBlockWaves * 64) __attribute__((amdgpu_waves_per_e
   const uint32_t pairs = bgroups * p.S;
   uint32_t w;
   if (!xcd_unit(pairs * cgroups, w)) return;
-  const uint32_t set = w / (8u * cgroups), in_set = w - set * 8u * cgroups, set_pairs = pairs - set * 8u < 8u ? pairs - set * 8u : 8u;
-  const uint32_t cg = in_set / set_pairs, pair = set * 8u + in_set % set_pairs;
-  const uint32_t slice = pair / bgroups, bgroup = pair - slice * bgroups;
+  const uint32_t set = divide(w, p.by_G), in_set = w - set * 8u * cgroups, set_pairs = pairs - set * 8u < 8u ? pairs - set * 8u : 8u;
+  const uint32_t cg = set_pairs == 8u ? in_set / 8u : in_set / set_pairs, pair = set * 8u + in_set - cg * set_pairs;
+  const uint32_t slice = divide(pair, p.by_groups), bgroup = pair - slice * bgroups;
   const uint32_t band = bgroup * kBands + wb;
   const bool active = band < p.bands;  // a wave past the last band loads no words but shares the X work
   const uint32_t n0 = p.n0 + cg * kCols;  // first column of the workgroup
   const uint32_t KT = p.KT, T = p.bands * KT;
   // the slice: whole bodies of three tiles; the last body of all may reach past K (no words, X reads as zero)
   const uint32_t bodies_all = (KT + NST - 1u) / NST;
-  const uint32_t b0 = (uint32_t)((uint64_t)slice * bodies_all / p.S), b1 = (uint32_t)((uint64_t)(slice + 1) * bodies_all / p.S);
+  const uint32_t b0 = divide(slice * bodies_all, p.by_S), b1 = divide((slice + 1) * bodies_all, p.by_S);
   const uint32_t k0 = b0 * NST, k1 = b1 * NST < KT ? b1 * NST : KT;
   const uint32_t t0 = active ? band * KT + k0 : T;
   const uint32_t ntiles = active ? k1 - k0 : 0;
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kBlockWaves * 64) __attribute__((amdgpu_waves_per_e
 }
 
 template <int SHARE, int RW, int FMT>
-static hipError_t launch_block_variant(const WideParams& p, hipStream_t stream) {
+static hipError_t launch_block_variant(WideParams p, hipStream_t stream) {
   static std::atomic<bool> attr_done{false};  // per kernel variant; setting the attribute twice from two threads is harmless
   constexpr int kLds = block_lds_bytes<SHARE>();
   if (!attr_done.load(std::memory_order_acquire)) {
@@ -348,6 +348,9 @@ static hipError_t launch_block_variant(const WideParams& p, hipStream_t stream) 
   }
   const uint32_t bgroups = block_band_groups(p.bands, SHARE), cgroups = block_col_groups(p.N - p.n0, SHARE);
   const uint32_t grid = (bgroups * p.S * cgroups + 7u) / 8u * 8u;
+  p.by_S = divisor(p.S);
+  p.by_G = divisor(8u * cgroups);
+  p.by_groups = divisor(bgroups);
   hipLaunchKernelGGL((spmm_block_kernel<SHARE, RW, FMT>), dim3(grid), dim3(kBlockWaves * 64), kLds, stream, p);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && p.S > 1) e = launch_wide_reduce(p, true, stream);

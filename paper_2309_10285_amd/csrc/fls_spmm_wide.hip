@@ -97,14 +97,14 @@ __global__ __launch_bounds__(kWideWaves * 64) void spmm_wide_kernel(WideParams p
   // groups (with G groups the chip is filled by G times fewer K slices, so G times fewer partial
   // sums per column go through memory than with a launch per group).
   uint32_t quad, slice, cg;
-  if (!wide_unit((p.bands + 3u) / 4u, p.S, p.G, p.whole, quad, slice, cg)) return;
+  if (!wide_unit(p, (p.bands + 3u) / 4u, quad, slice, cg)) return;
   const uint32_t n0 = p.n0 + cg * 64u;
   const uint32_t band = quad * 4 + wave;
   const bool active = band < p.bands;  // a wave past the last band loads no words but shares the X work
   const uint32_t KT = p.KT, T = p.bands * KT;
   // the slice: whole bodies of NS tiles, cut evenly; the K tiles that fill no body go to the last slice
   const uint32_t bodies_all = KT / NS;
-  const uint32_t b0 = (uint32_t)((uint64_t)slice * bodies_all / p.S), b1 = (uint32_t)((uint64_t)(slice + 1) * bodies_all / p.S);
+  const uint32_t b0 = divide(slice * bodies_all, p.by_S), b1 = divide((slice + 1) * bodies_all, p.by_S);
   const uint32_t bodies = b1 - b0;
   const uint32_t k0 = b0 * NS, k1 = k0 + bodies * NS;          // tiles of the pipelined loop
   const uint32_t ktail = slice + 1 == p.S ? KT : k1;           // ... and of the plain loop behind it
@@ -519,6 +519,9 @@ static hipError_t launch_wide_variant(WideParams p, int cus, hipStream_t stream)
   p.whole = whole_pairs(quads * p.S, p.G, cus);
   const uint32_t grid = wide_grid(quads * p.S, p.G, p.whole);
   p.cb = CB;
+  p.by_S = divisor(p.S);
+  p.by_G = divisor(p.G);
+  p.by_groups = divisor(quads);
   hipLaunchKernelGGL((spmm_wide_kernel<R, NS, FMT, CB>), dim3(grid), dim3(kWideWaves * 64), kLds, stream, p);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && p.S > 1) e = launch_wide_reduce(p, true, stream);
