@@ -114,7 +114,12 @@ inline uint32_t wide_quad_slices(uint32_t bands, uint32_t col_groups, uint32_t K
   if (cus > (int)kMaxWorkgroups) cus = (int)kMaxWorkgroups;
   const uint64_t units = (uint64_t)((bands + 3) / 4) * col_groups;
   uint32_t S = units < (uint64_t)cus ? (uint32_t)((uint64_t)cus / units) : 1u;
-  const uint32_t by_length = KT / (2u * body) > 0 ? KT / (2u * body) : 1u;
+  uint32_t by_length = KT / (2u * body) > 0 ? KT / (2u * body) : 1u;
+  // ... or one, as long as that makes few workgroups and few sums of it: up to 96 and 16 (us, two bodies / one: 2048 x 2880 at 90 % in version 2, N = 54
+  // 17.6 / 13.7, 1152 x 1504 at 70 %, N = 110 18.7 / 14.9; but 1408 x 10944 at 90 %, N = 56, 42 slices, 19.8 / 23.9, 4608 x 1344 at 80 % in
+  // version 2, N = 264, 225 workgroups, 26.6 / 29.9)
+  const uint32_t few = units <= 6u ? 16u : (uint32_t)(96u / units);
+  if (by_length < few) by_length = KT / body < few ? (KT / body > 0 ? KT / body : 1u) : few;
   return S < by_length ? S : by_length;
 }
 // How the 64-column passes spread their (group of four bands, K slice) pairs over the eight XCDs: whole pairs, in turn,
