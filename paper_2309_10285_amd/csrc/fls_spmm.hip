@@ -16,7 +16,8 @@
 //              zeros where their words went, dense ones by clearing all 8 KB
 // Split-K: the tile sequence (band-major) is cut evenly over all waves of the grid; partial
 // bands are summed in LDS inside a workgroup and through fp32 slots in HBM between workgroups.
-// More than 32 columns: fls_spmm_wide.hip and, from 65 on, fls_spmm_block.hip.
+// From 17 to 64 columns this kernel or the pass in fls_spmm_wide.hip runs, whichever an estimate
+// prefers (wide_pays); beyond 64 that pass or the one in fls_spmm_block.hip.
 #include <atomic>
 #include <type_traits>
 
