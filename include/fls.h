@@ -183,8 +183,8 @@ int fls_check_workspace(fls_stream_t stream);
  * from fls_compress is right by construction).  As a guard for blobs that were stored and read back, the
  * passes of up to 32 columns take no offset to lie beyond the header's word count, so a truncated or
  * damaged TileOffsets section gives wrong results, not loads outside NonZeros; the block pass (N > 64) and the 64-column pass
- * (most calls of 33 - 64 columns, and calls of 17 - 32 on long bands, where sharing X between
- * bands makes it the faster one) trust TileOffsets.
+ * (most calls of 33 - 64 columns, and calls of 17 - 32 on long bands - K of at least 9216, in format version 2 32768 - where
+ * sharing X between bands makes it the faster one) trust TileOffsets.
  * Errors: FLS_EINVAL, FLS_EALIGN, FLS_EFORMAT, FLS_EWORKSPACE, FLS_EHIP.
  */
 int fls_spmm(const void* Wc_dev, const void* X_dev, void* C_dev, int64_t M, int64_t K, int64_t N,

@@ -290,10 +290,20 @@ inline float wide_us(float w_bytes, uint32_t rounds, uint32_t bands, uint32_t KT
   if (S > 1u) us += 0.07f * (float)(1u + S / 8u) + 2.f * (float)bands * (float)S * (N <= kGroupCols ? 16384.f : 32768.f) / 4.35e6f;
   return us;
 }
-// `rounds` of the variant that the pass would run; version 2 has variants with one block for tiles of up to four rounds.  (Up to 32 columns
-// on short bands stay with the narrow kernel, which checks the offsets it reads against the header, whatever the estimate.)
+// May a call of 17 - 32 columns take the 64-column pass at all?  The narrow kernel takes no offset to lie beyond the header's word count and
+// the pass trusts TileOffsets, so only calls on long bands leave the narrow kernel, however the estimate falls: in version 1 bands of at least 384 K tiles, or 288 with
+// tiles of more than two rounds and K slices that come out even (the longest at most a tenth above the mean); in version 2, which has variants with
+// one block for tiles of up to four rounds only, bands of at least 1024.  (These are the calls that a rule on K and density gave to the pass before
+// there was an estimate; it would take some on shorter bands too.  The line is there for the check, not for time.)
+inline bool wide32_allowed(uint32_t need, uint32_t version, uint32_t bands, uint32_t KT, int cus) {
+  if (version == 2u) return need <= 4u && KT >= 1024u;
+  if (KT >= 384u) return true;
+  if (KT < 288u || need <= 2u) return false;
+  const uint32_t body = wide_body(wide_rounds(need)), bodies = KT / body, S = wide_quad_slices(bands, 1u, KT, cus, body);
+  return (uint64_t)((bodies + S - 1u) / S) * S * 10u <= (uint64_t)bodies * 11u;
+}
+// `rounds` of the variant that the pass would run.
 inline bool wide_pays(uint32_t max_tile_words, uint32_t rounds, uint32_t version, uint32_t bands, uint32_t KT, uint32_t N, int cus) {
-  if (N <= kGroupCols && (version == 2u ? rounds > 4u || KT < 1024u : KT < 288u)) return false;
   const float w = words_bytes(max_tile_words, version, bands, KT);
   return 0.98f * wide_us(w, rounds, bands, KT, N, cus) < narrow_us(w, rounds, bands, KT, N, cus);
 }

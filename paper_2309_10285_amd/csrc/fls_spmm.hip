@@ -433,7 +433,7 @@ SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, ui
   // The 64-column pass stages at most ten rounds of a tile (it has no slow path for more; twelve
   // rounds no longer fit its registers): a matrix with denser tiles - less than 40 % sparse
   // somewhere - takes 32-column passes throughout.
-  const bool possible = N > 16u && need <= 10u && (N > kGroupCols || wide32);
+  const bool possible = need <= 10u && (N > kGroupCols || (N > 16u && wide32 && wide32_allowed(need, version, bands, KT, cus)));
   // (the narrow kernel stages eight rounds, and what a tile has beyond goes a slow way that the estimate leaves out)
   if (possible && (N > kSpmmGroupCols || need > 8u || wide_pays(max_tile_words, wide_rounds(need), version, bands, KT, N, cus))) {
     // ... and beyond 64 columns it or the block pass takes all columns of the call, whichever the estimate prefers

@@ -535,7 +535,7 @@ static hipError_t launch_wide_rounds(uint32_t rounds, const WideParams& p, int c
     case 2: return launch_wide_variant<2, FMT, CB>(p, cus, stream);
     case 3: return launch_wide_variant<3, FMT, CB>(p, cus, stream);
     case 4: return launch_wide_variant<4, FMT, CB>(p, cus, stream);
-    // (wide_pays asks for no more in version 2 with one column block)
+    // (wide32_allowed asks for no more in version 2 with one column block)
     case 6: return launch_wide_variant<6, FMT, FMT == 2 ? 2 : CB>(p, cus, stream);
     case 8: return launch_wide_variant<8, FMT, FMT == 2 ? 2 : CB>(p, cus, stream);
     default: return launch_wide_variant<10, FMT, FMT == 2 ? 2 : CB>(p, cus, stream);

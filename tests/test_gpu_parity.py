@@ -511,19 +511,20 @@ def test_split_bands_after_wide_passes_many_repeats(fls, oracle_mod):
     fls.fls_forget(blob)
 
 
-@pytest.mark.parametrize("N", [16, 32])
-def test_offsets_past_the_end_of_nonzeros_are_clamped(fls, oracle_mod, N):
+@pytest.mark.parametrize("N,sparsity", [(16, 0.8), (32, 0.8), (32, 0.45), (17, 0.45)])  # 0.45: tiles of nine and ten rounds
+def test_offsets_past_the_end_of_nonzeros_are_clamped(fls, oracle_mod, N, sparsity):
     """A blob whose last TileOffsets entries point past the end of NonZeros (a truncated or damaged file).  The
     passes of up to 32 columns take no offset to lie beyond the word count in the blob's header, so the last tile
     keeps its own words and the result is that of the intact blob.  (The 64-column pass trusts TileOffsets: a
-    clamp there cost 5 - 14 % of its time.)  The buffer has room behind the blob, filled with words (1.0 at
+    clamp there cost 5 - 14 % of its time.  Up to 32 columns it takes calls on long bands only, however dense the tiles.)  The buffer has room behind the blob, filled with words (1.0 at
     location 0) that would change C if they were read: every load of this test stays inside it."""
     import torch
 
     M, K = 512, 2048
-    W = wl.prune_uniform(wl.gen_weights_f32(M, K, 1400), 0.8, 1401)
+    W = wl.prune_uniform(wl.gen_weights_f32(M, K, 1400), sparsity, 1401)
     X = wl.gen_x(N, K, 1402)
     blob, st = fls.fls_compress(_dev_w(W))
+    assert fls.spmm_plan(st, N)["pass"] == "narrow" and (st["max_tile_words"] > 8 * 256) == (sparsity < 0.5)
     Xd = torch.from_numpy(X.view(np.float16)).cuda()
     fls.ensure_workspace(M, K, N)
     good = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")

@@ -55,6 +55,22 @@ def test_columns_and_density_decide(plan, version):
         assert plan(rounds, version, M, K, 64)[2] == staged
 
 
+@pytest.mark.parametrize("N", [17, 24, 32])
+def test_short_bands_stay_with_the_kernel_that_checks_offsets(plan, N):
+    """The 64-column pass trusts TileOffsets: up to 32 columns it takes calls on long bands only, whatever tiles need and the estimate says."""
+    rng = random.Random(11)
+    for version, rounds in itertools.product((1, 2), range(1, 11)):
+        for _ in range(60):
+            kt, bands = int((1024 if version == 2 else 288) ** rng.random()), int(400 ** rng.random())
+            assert plan(rounds, version, bands * 128, kt * 32, N)[0] == "narrow", (version, rounds, bands, kt)
+    for rounds in range(5, 11):  # the pass has no variant with one column block for them in version 2
+        assert plan(rounds, 2, 12288, 49152, N)[0] == "narrow"
+    # bands of 288 - 383 K tiles: sparse tiles, and K slices that do not come out even
+    assert plan(2, 1, 8192, 352 * 32, N)[0] == "narrow" and plan(1, 1, 27648, 9216, N)[0] == "narrow"
+    assert plan(9, 1, 128, 300 * 32, N)[0] == "narrow"
+    assert plan(9, 1, 1024, 384 * 32, N)[0] == "wide"  # tiles of more than eight rounds, on a long band
+
+
 @pytest.mark.parametrize("rounds,version,M,K,N,share", [
     # K tiles that fill no body of the 64-column pass (us there / in the block pass with share 1 / 2)
     (4, 1, 12288, 480, 4096, 2),    # 139 / 70 / 67
