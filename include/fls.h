@@ -217,8 +217,9 @@ int fls_spmm_stats(const void* Wc_dev, const fls_stats* stats_host, const void* 
  * stats_host must describe the blob at Wc_dev (same M, K, tile geometry): FLS_EFORMAT otherwise; a
  * max_tile_words smaller than the blob's costs speed only, as with fls_spmm.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams,
- * two threads) race, and must be serialised by the caller.  Nothing has to be cleared between calls (every
- * call leaves the flags it raised lowered again).  fls_check_workspace also reports a hand-over that
+ * two threads) race, and must be serialised by the caller.  Nothing has to be cleared between calls: a call that gave up may
+ * leave a flag raised, but flags bear the call's number, and a call that is recorded into a graph, whose replays share one, records a
+ * small kernel that lowers them first.  fls_check_workspace also reports a hand-over that
  * gave up inside this call.
  * Errors: FLS_EINVAL, FLS_EALIGN, FLS_EFORMAT, FLS_ESCRATCH, FLS_EHIP.
  */

@@ -491,8 +491,13 @@ int fls_spmm_noalloc(const void* Wc_dev, const fls_stats* stats_host, const void
   const int cus = num_cus();
   if (cus <= 0) return FLS_EHIP;
   hipStream_t s = (hipStream_t)stream;
-  // Every call leaves its flags lowered.  A call's flags bear its number, so one that a call which gave up left raised is not taken for
-  // its own by a later call.
+  // Every call leaves its flags lowered, unless it gave up: the flag it no longer waited for stays up.  A call's flags bear its number, so a
+  // later call does not take one for its own.  A recorded call bears the same number in every replay, so it lowers all flags before its kernel (not the
+  // error word: fls_check_workspace shall hear of a replay that gave up).
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool asked = hipStreamIsCapturing(s, &capture) == hipSuccess;
+  if (!asked) (void)hipGetLastError();
+  if ((!asked || capture != hipStreamCaptureStatusNone) && fls::launch_lower_flags((uint32_t*)ptr, s) != hipSuccess) return FLS_EHIP;
   uint32_t number;
   {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -563,6 +568,18 @@ void fls_internal_shares(uint32_t M, uint32_t K, int cus, float tile_us, int wid
 }
 
 uint32_t fls_internal_divide(uint32_t n, uint32_t d) { return fls::divide(n, fls::divisor(d)); }
+
+// The control words of fls_spmm_noalloc on the current device, the partial sums behind them, and the number of the last call.  As below.
+int fls_internal_noalloc_scratch(void** control, void** parts, uint32_t* number) {
+  int rc = FLS_OK;
+  unsigned char* ptr = scratch_on_current_device(&rc);
+  if (!ptr) return rc;
+  *control = ptr;
+  *parts = ptr + kScratchControlBytes;
+  std::lock_guard<std::mutex> lk(g_mu);
+  *number = g_scratch_calls;
+  return FLS_OK;
+}
 
 // fls_compress (version 1 or 2) whose kernel gives up at the first word that another workgroup has not published yet, so that it
 // is run again with chunks by ticket.  For tests, not part of the C ABI.

@@ -475,6 +475,17 @@ __global__ void fill_zero_kernel(u32x4* p, size_t n16) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x) p[i] = z;
 }
 
+__global__ __launch_bounds__(kMaxGrid) void lower_flags_kernel(uint32_t* flags) {
+#pragma unroll
+  for (uint32_t i = threadIdx.x; i < kLocalFlags + kMaxGrid; i += kMaxGrid)
+    if (i != kErrorWord) flags[i] = 0u;
+}
+
+hipError_t launch_lower_flags(uint32_t* flags, hipStream_t stream) {
+  hipLaunchKernelGGL(lower_flags_kernel, dim3(1), dim3(kMaxGrid), 0, stream, flags);
+  return hipGetLastError();
+}
+
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream) {
   const size_t n16 = bytes / 16;
   if (n16 == 0) return hipSuccess;

@@ -346,6 +346,8 @@ hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream);
 // header, TileOffsets and every tile whose words fit the capacity: one kernel
 hipError_t launch_compress(const CompressLaunch& a, hipStream_t stream);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
+// all control words of a hand-over but the error word
+hipError_t launch_lower_flags(uint32_t* flags, hipStream_t stream);
 
 }  // namespace fls
 

@@ -111,3 +111,61 @@ def test_two_matrices_in_one_graph_with_eager_calls_between_replays(fls, oracle_
             run(*cases[i % 2][:7])
     torch.cuda.synchronize()
     fls.fls_check_workspace()
+
+
+class _Memory:
+    """Device memory of the library as something torch can view."""
+
+    def __init__(self, ptr, words, typestr):
+        self.__cuda_array_interface__ = {"data": (ptr, False), "shape": (words,), "typestr": typestr, "version": 3}
+
+
+@pytest.mark.parametrize("recorded", [False, True])
+def test_flags_that_a_call_which_gave_up_left_raised(fls, oracle_mod, recorded):
+    """A hand-over that was given up leaves its flag raised and its slot filled.  Neither a later call nor a further replay of the same
+    recorded call, which bears the same number, may take them for its own: flags and slots are filled as such a call would leave them (every
+    one, the slots with NaN), and the error word stays for fls_check_workspace."""
+    import ctypes
+
+    import torch
+
+    N, bands, kt = 16, 42, 51
+    M, K = bands * 128, kt * 32
+    W, X, Wd, Xd = _operands(bands, kt, N, 0.8, 7950)
+    ref = oracle_mod.ref_spmm_f64(W, X)
+    blob, stats = fls.fls_compress(Wd)
+    scratch = fls.lib().fls_internal_noalloc_scratch
+    scratch.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_uint32)]
+    control, parts, number = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_uint32()
+    C = torch.empty((N, M), dtype=torch.float16, device="cuda")
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        fls.fls_spmm_noalloc(blob, stats, Xd, C, M, K, N)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            fls.fls_spmm_noalloc(blob, stats, Xd, C, M, K, N)
+        assert scratch(ctypes.byref(control), ctypes.byref(parts), ctypes.byref(number)) == fls.OK
+        words = torch.as_tensor(_Memory(control.value, 2048, "<i4"), device="cuda")
+        slots = torch.as_tensor(_Memory(parts.value, 512 * 2 * 2048, "<f4"), device="cuda")
+        assert words.data_ptr() == control.value and slots.data_ptr() == parts.value
+        for i in range(4):
+            slots.fill_(float("nan"))
+            words[:512] = number.value  # of partial sums in memory, of those in an XCD's L2
+            words[1536:] = number.value
+            words[512] = 1
+            C.fill_(float("nan"))
+            if recorded:
+                graph.replay()
+            else:
+                fls.fls_spmm_noalloc(blob, stats, Xd, C, M, K, N)
+            torch.cuda.synchronize()
+            if recorded:  # none that this replay could have taken for its own, none for the next
+                assert torch.nonzero(words).flatten().tolist() == [512]
+            assert float(np.abs(C.cpu().numpy().astype(np.float64) - ref).max()) / float(np.abs(ref).max()) <= TOL, i
+            with pytest.raises(fls.FlsError) as e:
+                fls.fls_check_workspace()
+            assert e.value.code == fls.EHANDOVER
+            torch.cuda.synchronize()
+            assert int(words.abs().max()) == 0
+        fls.fls_check_workspace()
