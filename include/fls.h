@@ -136,7 +136,7 @@ int fls_inspect(const void* header_host, fls_stats* stats_host);
 
 /*
  * Bytes of device workspace fls_spmm / fls_dense_gemm need for this shape: a 4 MiB control area
- * (per-workgroup flags of the split-K hand-over, an error word), the fp32 partial sums (4 MiB
+ * (control words of the split-K hand-over: flags, owners, an error word), the fp32 partial sums (4 MiB
  * for N <= 16, 64 MiB above: from 17 columns on a call may take the 64-column pass, which keeps
  * one partial result per band and K slice) and, for N > 32, K x N x 2 bytes for X repacked into
  * MFMA fragment order.  Returns 0 on invalid arguments.
@@ -206,7 +206,7 @@ int fls_spmm_stats(const void* Wc_dev, const fls_stats* stats_host, const void* 
  * fls_spmm for callers that cannot allocate device memory or wait on a stream: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same results as fls_spmm, always
  * through the kernel of up to 32 columns per pass, but
- *   - the split-K scratch (hand-over flags, error word, fp32 partial sums) is a static device array
+ *   - the split-K scratch (control words of the hand-over, fp32 partial sums) is a static device array
  *     inside the library, FLS_NOALLOC_SCRATCH_BYTES large, present on every GPU the library runs on
  *     from load time to the end of the process: no workspace has to be registered, and none is used;
  *   - the blob's statistics come from the caller (stats_host: as filled by fls_compress or

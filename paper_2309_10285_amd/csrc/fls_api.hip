@@ -34,9 +34,11 @@ int g_num_cus = 0;
 // fp32 partial sums of up to 32 columns), in device memory that exists from the moment the library
 // is loaded.  Host code never uses the array's name as an address: hipGetSymbolAddress gives the
 // address on the current device (every device has its own copy), looked up once per device.
-constexpr size_t kScratchControlBytes = 8192;  // 512 flags, the error word, spare
+constexpr size_t kScratchControlBytes = 8192;  // control words of the hand-over, none to spare
+static_assert(fls::kControlWords * sizeof(uint32_t) <= kScratchControlBytes, "partial sums follow");
 constexpr size_t kScratchPartsBytes = (size_t)fls::kMaxWorkgroups * 2 * 2048 * sizeof(float);  // 8 MiB
 constexpr size_t kScratchBytes = kScratchControlBytes + kScratchPartsBytes;
+static_assert(kScratchBytes == FLS_NOALLOC_SCRATCH_BYTES && FLS_NOALLOC_MAX_N == fls::kGroupCols, "as the header says");
 static __device__ __align__(256) __attribute__((used)) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};  // by device id; guarded by g_mu
@@ -216,12 +218,13 @@ int check_mm_args(const void* W, const void* X, void* C, int64_t M, int64_t K, i
   return FLS_OK;
 }
 
-// Workspace: a fixed 4 MiB control area (one u32 flag per workgroup and an error word; the rest
-// is spare; cleared when the workspace is registered, and every launch leaves its flags cleared),
+// Workspace: a fixed 4 MiB control area (the control words of the hand-over; the rest
+// is spare; cleared when the workspace is registered, and every launch leaves its flags lowered and its owners' XCDs taken back),
 // then the split-K partial slots (fp32), then, for N > 32, X repacked into MFMA fragment order
 // (K x N rounded up to 16 columns, fp16).  The control area has the same place for every shape, so
 // partial sums of one call can never be read as flags by the next.
 constexpr size_t kCounterAreaBytes = (size_t)4 << 20;
+static_assert(fls::kControlWords * sizeof(uint32_t) <= kCounterAreaBytes, "partial sums follow");
 
 void workspace_layout(int64_t K, int64_t N, size_t* total, size_t* xpack_offset) {
   const size_t parts = fls::parts_floats((uint32_t)N) * sizeof(float);
@@ -358,7 +361,7 @@ int fls_check_workspace(fls_stream_t stream) {
   hipStream_t s = (hipStream_t)stream;
   uint32_t word = 0;
   if (st) {  // the scratch of fls_spmm_noalloc, if this device has used it
-    if (hipMemcpyAsync(&word, (const uint32_t*)st + fls::kMaxWorkgroups, sizeof(word), hipMemcpyDeviceToHost, s) != hipSuccess)
+    if (hipMemcpyAsync(&word, (const uint32_t*)st + fls::kErrorWord, sizeof(word), hipMemcpyDeviceToHost, s) != hipSuccess)
       return FLS_EHIP;
     if (hipStreamSynchronize(s) != hipSuccess) return FLS_EHIP;
     if (word != 0) {
@@ -367,7 +370,7 @@ int fls_check_workspace(fls_stream_t stream) {
     }
     if (!ws) return FLS_OK;
   }
-  if (hipMemcpyAsync(&word, (const uint32_t*)ws + fls::kMaxWorkgroups, sizeof(word), hipMemcpyDeviceToHost, s) != hipSuccess)
+  if (hipMemcpyAsync(&word, (const uint32_t*)ws + fls::kErrorWord, sizeof(word), hipMemcpyDeviceToHost, s) != hipSuccess)
     return FLS_EHIP;
   if (hipStreamSynchronize(s) != hipSuccess) return FLS_EHIP;
   if (word == 0) return FLS_OK;

@@ -475,14 +475,14 @@ __global__ void fill_zero_kernel(u32x4* p, size_t n16) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x) p[i] = z;
 }
 
-__global__ __launch_bounds__(kMaxGrid) void lower_flags_kernel(uint32_t* flags) {
+__global__ __launch_bounds__(kMaxWorkgroups) void lower_flags_kernel(uint32_t* flags) {
 #pragma unroll
-  for (uint32_t i = threadIdx.x; i < kLocalFlags + kMaxGrid; i += kMaxGrid)
+  for (uint32_t i = threadIdx.x; i < kControlWords; i += kMaxWorkgroups)
     if (i != kErrorWord) flags[i] = 0u;
 }
 
 hipError_t launch_lower_flags(uint32_t* flags, hipStream_t stream) {
-  hipLaunchKernelGGL(lower_flags_kernel, dim3(1), dim3(kMaxGrid), 0, stream, flags);
+  hipLaunchKernelGGL(lower_flags_kernel, dim3(1), dim3(kMaxWorkgroups), 0, stream, flags);
   return hipGetLastError();
 }
 

@@ -24,14 +24,9 @@ constexpr int kHeaderMaxTileWords = 6;      // header word that holds the length
 constexpr int kHeaderTotalWords = 14;       // header word that holds the number of words in NonZeros (low half of a u64)
 
 constexpr int kAccPerBlock = kTileM * 16;   // fp32 values of one 128 x 16 column block
-constexpr int kMaxGrid = 512;               // workgroups a launch may use (sizes the workspace)
 constexpr int kBufferFlags = 0x00020000;    // raw buffer, 32-bit data format (gfx9 descriptor word 3)
 constexpr int kAuxNonTemporal = 2;          // nt: streamed once, do not keep in the caches
 constexpr int kAuxCoherent = 16;            // sc1: device scope - through to memory / past the per-XCD L2
-
-// Control words of the hand-over, from `flags` on: flags of partial sums released at device scope, the error word, the XCDs of
-// waiting owners, flags of partial sums that stay in an XCD's L2.  2048 words (what the static scratch has).
-constexpr uint32_t kErrorWord = kMaxGrid, kOwnerXcd = 2 * kMaxGrid, kLocalFlags = 3 * kMaxGrid;
 
 // LDS byte address a word of a tile goes to: base + 2 * location (the word's low half), in one
 // instruction (v_mad_u32_u16: D = S0.u16 * S1.u16 + S2.u32).
@@ -54,7 +49,7 @@ __device__ __forceinline__ uint32_t scatter_addr(uint32_t word, uint32_t base) {
 struct OutParams {
   _Float16* C;      // column-major M x N
   float* parts;     // [workgroup][NB * 2048] fp32 partial sums in accumulator order
-  uint32_t* flags;  // control words; [share] `raised` while a published partial sum waits for its band's owner
+  uint32_t* flags;  // control words (kControlWords of them); [share] `raised` while a published partial sum waits for its band's owner
   uint32_t raised;  // a flag that is up, nonzero
   uint32_t P;       // shares
   uint32_t unit;    // ... that stay together on an XCD, `units` such groups; 0: shares are whole bands, nothing is handed over
@@ -98,7 +93,7 @@ __device__ __forceinline__ bool wide_unit(const WideParams& p, uint32_t quads, u
   return true;
 }
 
-// First tile of share q: all tiles cut evenly over the shares, or the bands.  (At most kMaxGrid shares, fewer than 2^20 tiles.)
+// First tile of share q: all tiles cut evenly over the shares, or the bands.  (At most kMaxWorkgroups shares, fewer than 2^20 tiles.)
 __device__ __forceinline__ uint32_t share_begin(const OutParams& o, uint32_t q) {
   return o.unit == 0 ? divide(q * o.bands, o.by_P) * o.KT : divide(q * o.T, o.by_P);
 }

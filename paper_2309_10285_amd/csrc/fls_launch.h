@@ -85,7 +85,10 @@ struct CompressLaunch {
 constexpr uint32_t kGroupCols = 32;
 constexpr uint32_t kSpmmGroupCols = 64;
 inline uint32_t group_blocks(uint32_t ncols) { return ncols <= 16 ? 1u : (ncols <= 32 ? 2u : 4u); }
-constexpr uint32_t kMaxWorkgroups = 512;    // must equal fls::kMaxGrid of the device code
+constexpr uint32_t kMaxWorkgroups = 512;    // most shares of a launch of up to 32 columns, most K slices x units of the wider passes
+// Control words of the hand-over between workgroups, one array of kMaxWorkgroups words after the other: flags of partial sums released at device
+// scope; the error word, the rest of its array unused; the XCDs of waiting owners; flags of partial sums that stay in an XCD's L2.
+constexpr uint32_t kErrorWord = kMaxWorkgroups, kOwnerXcd = 2 * kMaxWorkgroups, kLocalFlags = 3 * kMaxWorkgroups, kControlWords = 4 * kMaxWorkgroups;
 // The 64-column pass of the dense kernel cuts its work as (group of 4 bands) x (K slice), one wave
 // per band, and keeps one 128 x 64 fp32 partial result per band and slice.  Slices per group: as
 // many as fill the CUs, but none shorter than two steps of 64 k (at least 16 steps before: 1408 x 1120,
