@@ -155,7 +155,7 @@ int fls_set_workspace(void* ws_dev, size_t bytes, fls_stream_t stream);
 /*
  * Waits for `stream` and reads the workspace's error word.  The split-K hand-over (Alg. 1 has
  * none: a thread block there walks the whole K) makes one workgroup wait for the partial sums of
- * others; that wait is bounded (about a second), and a kernel that gives up says so here instead
+ * others; that wait is bounded (one to a few seconds), and a kernel that gives up says so here instead
  * of hanging.  Returns FLS_OK, or FLS_EHANDOVER after clearing the control area again so that
  * later calls start clean; FLS_EWORKSPACE if none is registered; FLS_EHIP.
  */

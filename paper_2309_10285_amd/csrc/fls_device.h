@@ -258,8 +258,12 @@ __device__ __forceinline__ void wg_reduce_skip(WgReduceLds<NB>* red, uint32_t se
 // launch ends: nothing is cleared between calls, and a launch recorded in a graph can be replayed.
 //
 // A workgroup publishes before it polls, and only polls workgroups of higher index, so the wait
-// ends as soon as those workgroups have run; the spin is bounded all the same.
-constexpr uint32_t kSpinLimit = 1u << 20;
+// ends as soon as those workgroups have run; the spin is bounded all the same.  How long that is: a look is a trip to the L2, some 600 clocks,
+// or to memory, some 2000, and a sleep.  (A launch whose workgroups wait for room because another stream's kernel holds the chip must outlast
+// that kernel, so the bound is a second or more at the shorter of the two.)
+constexpr int kSpinSleep = 2;  // x 64 clocks: sums are due within a microsecond or two
+constexpr uint32_t kSpinLimit = 1u << 22;
+static_assert((uint64_t)kSpinLimit * (64u * kSpinSleep + 600u) >= 2400000000ull, "a second at 2.4 GHz");
 
 // Does share [share0, share1) hold the first tile of a band that it does not hold the last tile of?
 __device__ __forceinline__ bool owns_cut_band(const OutParams& o, uint32_t share0, uint32_t share1) {
@@ -346,7 +350,7 @@ __device__ __forceinline__ void owner_finish(const OutParams& o, float4v (&acc)[
         if (!seen && (!expected || both)) seen = __hip_atomic_load(o.flags + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == o.raised;
       }
       if (__builtin_amdgcn_ballot_w64(!seen) == 0) break;
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(kSpinSleep);
       if (++spins == kSpinLimit) {  // never seen; gives up rather than hang, and says so
         if (lane == 0) __hip_atomic_store(o.flags + kErrorWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         break;
