@@ -312,12 +312,26 @@ __device__ __forceinline__ void store_partial(const OutParams& o, const float4v 
 __device__ __forceinline__ void release_begin() { asm volatile("buffer_wbl2 sc1" ::: "memory"); }
 __device__ __forceinline__ void release_end() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// A flag of the short way, raised and taken down again as instructions of this chip: no scope of the memory model stands for "the
+// workgroups of one XCD" (workgroup scope promises nothing beyond the workgroup, agent scope is the trip to memory that is to be saved).  What they rely on: a
+// store passes through the CU's L1 and is done when the XCD's L2 has it; an atomic is executed by the L2 (sc0: it returns the old value), where a load may be
+// served by the L1 for ever.
+__device__ __forceinline__ void raise_local(uint32_t* flag, uint32_t raised) {
+  asm volatile("global_store_dword %0, %1, off sc0" ::"v"(flag), "v"(raised) : "memory");
+}
+__device__ __forceinline__ bool lower_local(uint32_t* flag, uint32_t raised) {
+  uint32_t old;
+  const uint64_t swap = (uint64_t)raised << 32;  // the new value, 0; the one to compare with
+  asm volatile("global_atomic_cmpswap %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)" : "=&v"(old) : "v"(flag), "v"(swap) : "memory");
+  return old == raised;
+}
+
 // By the wave that called store_partial, once its run is over; `begun` tells whether it has called
 // release_begin behind the stores already.
 __device__ __forceinline__ void publish_partial(const OutParams& o, uint32_t wg, int lane, bool local, bool begun) {
   if (local) {
     release_end();  // the stores have reached the L2
-    if (lane == 0) __hip_atomic_store(o.flags + kLocalFlags + wg, o.raised, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (lane == 0) raise_local(o.flags + kLocalFlags + wg, o.raised);
     return;
   }
   if (!begun) release_begin();
@@ -342,10 +356,7 @@ __device__ __forceinline__ void owner_finish(const OutParams& o, float4v (&acc)[
       if (!seen) {
         // (the kind of flag that the contributor's number lets expect each time, the other one now and then)
         const bool expected = q < near_end, both = (spins & 7u) == 7u;
-        // (an atomic, which also lowers the flag: the L2 executes it, where the CU's L1 may serve a load at workgroup scope for ever)
-        uint32_t up = o.raised;
-        if (expected || both)
-          local = __hip_atomic_compare_exchange_strong(o.flags + kLocalFlags + q, &up, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (expected || both) local = lower_local(o.flags + kLocalFlags + q, o.raised);
         seen = local;
         if (!seen && (!expected || both)) seen = __hip_atomic_load(o.flags + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == o.raised;
       }
