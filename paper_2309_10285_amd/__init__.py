@@ -51,7 +51,10 @@ assert _STATS_LAYOUT.size == ctypes.sizeof(FlsStats)
 
 
 def _stats_struct(stats):
-    return FlsStats.from_buffer_copy(_STATS_LAYOUT.pack(*_stats_values(stats)))
+    try:
+        return FlsStats.from_buffer_copy(_STATS_LAYOUT.pack(*_stats_values(stats)))
+    except struct.error:  # a value that its field does not hold: cut to the field as ctypes does, for the library to judge; TypeError for one that is no integer
+        return FlsStats(**{k: stats[k] for k in _STATS_NAMES})
 
 
 class FlsError(RuntimeError):

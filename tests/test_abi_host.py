@@ -98,3 +98,20 @@ def test_measurement_probe_library_loads(fls):
     assert L.fls_probe_stream_read(None, 1024, 8, 8, 16, None) == -1
     assert L.fls_probe_stream_read(16, 1024, 8, 5, 16, None) == -1   # unroll not offered
     assert L.fls_probe_stream_read(16, 1024, 0, 8, 16, None) == -1   # empty grid
+
+
+@pytest.mark.parametrize("key,value", [("M", 128), ("M", -128), ("nnz", 2**64), ("format_version", 2**32 + 1), ("tile_m", -1)])
+def test_statistics_reach_the_library_as_ctypes_would_pass_them(fls, key, value):
+    """A value that its field does not hold is the library's to refuse (FLS_EFORMAT), not the binding's."""
+    stats = {**dict.fromkeys((k for k, _ in fls.FlsStats._fields_), 7), key: value}
+    st = fls._stats_struct(stats)
+    assert st.as_dict() == fls.FlsStats(**stats).as_dict()
+    dummy, K = ctypes.c_void_p(4096), 32  # never read: the shape does not match
+    assert fls.lib().fls_spmm_stats(dummy, ctypes.byref(st), dummy, dummy, 256, K, 8, None) == fls.EFORMAT
+
+
+@pytest.mark.parametrize("value", [1.0, "1", None])
+def test_statistics_that_are_no_integers_are_a_type_error(fls, value):
+    stats = {**dict.fromkeys((k for k, _ in fls.FlsStats._fields_), 7), "K": value}
+    with pytest.raises(TypeError):
+        fls._stats_struct(stats)
