@@ -109,11 +109,23 @@ def strerror(code):
     return lib().fls_strerror(code).decode()
 
 
+_raw_stream = None
+
+
 def _stream():
     """The current stream of the current device, as hipStream_t."""
-    import torch
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
 
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        torch.cuda.current_stream()  # initialises torch's GPU side, or raises
+        # what that call is made of, without the Stream object: a microsecond less, but names that torch does not promise
+        get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if get and device:
+            _raw_stream = lambda: get(device())
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _raw_stream()
 
 
 def _check(rc, where):

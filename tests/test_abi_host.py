@@ -115,3 +115,31 @@ def test_statistics_that_are_no_integers_are_a_type_error(fls, value):
     stats = {**dict.fromkeys((k for k, _ in fls.FlsStats._fields_), 7), "K": value}
     with pytest.raises(TypeError):
         fls._stats_struct(stats)
+
+
+def test_the_stream_is_asked_for_by_torchs_public_call_where_the_short_way_is_missing(fls, monkeypatch):
+    import types
+
+    import torch
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(fls, "_raw_stream", None)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert fls._stream() == fls._stream() == 1234
+    now = [1234]
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: now[0] if device == 3 else 0, raising=False)
+    monkeypatch.setattr(fls, "_raw_stream", None)
+    assert fls._stream() == 1234
+    now[0] = 77
+    assert fls._stream() == 77
+
+
+def test_without_a_gpu_a_call_raises(fls, monkeypatch):
+    import torch
+
+    if torch.cuda.is_available():
+        pytest.skip("there is a GPU")
+    monkeypatch.setattr(fls, "_raw_stream", None)
+    with pytest.raises(RuntimeError):
+        fls.fls_check_workspace()
