@@ -249,7 +249,8 @@ int fls_inspect(const void* header_host, fls_stats* stats_host) {
 }
 
 static int compress_impl(const void* W_dev, int64_t M, int64_t K, void* out_dev, size_t out_capacity, int order_policy,
-                         uint32_t version, fls_stats* stats_host, fls_stream_t stream, uint32_t look_limit = kLookLimitByNumber) {
+                         uint32_t version, fls_stats* stats_host, fls_stream_t stream, uint32_t look_limit = kLookLimitByNumber,
+                         bool by_ticket = false, uint32_t* runs = nullptr) {
   if (!W_dev || !out_dev || !shape_ok(M, K)) return FLS_EINVAL;
   if (order_policy != FLS_ORDER_LOCATION) return FLS_EINVAL;  // FLS_ORDER_BANK: not built yet
   if (!aligned16(W_dev) || !aligned16(out_dev)) return FLS_EALIGN;
@@ -281,8 +282,9 @@ static int compress_impl(const void* W_dev, int64_t M, int64_t K, void* out_dev,
   }
   unsigned char hdr[FLS_HEADER_BYTES];
   a.look_limit = look_limit;
-  a.by_ticket = false;
+  a.by_ticket = by_ticket;
   for (;;) {
+    if (runs) ++runs[a.by_ticket ? 1 : 0];
     CompressPlace place;
     if (!place.take(s)) return FLS_EHIP;
     a.scratch = place.scratch;
@@ -584,11 +586,13 @@ int fls_internal_noalloc_scratch(void** control, void** parts, uint32_t* number)
   return FLS_OK;
 }
 
-// fls_compress (version 1 or 2) whose kernel gives up at the first word that another workgroup has not published yet, so that it
-// is run again with chunks by ticket.  For tests, not part of the C ABI.
-int fls_internal_compress_impatient(const void* W_dev, int64_t M, int64_t K, void* out_dev, size_t out_capacity, uint32_t version,
-                                    fls_stats* stats_host, fls_stream_t stream) {
-  return compress_impl(W_dev, M, K, out_dev, out_capacity, FLS_ORDER_LOCATION, version, stats_host, stream, 1u);
+// fls_compress (version 1 or 2) with the looks after which its kernel gives up and the order of chunks that it starts with; runs_host gets the
+// number of kernel runs by number and by ticket.  With one look it gives up at the first word that another workgroup has not published
+// yet, and is run again by ticket.  For tests, not part of the C ABI.
+int fls_internal_compress(const void* W_dev, int64_t M, int64_t K, void* out_dev, size_t out_capacity, uint32_t version, uint32_t look_limit,
+                          int by_ticket, uint32_t* runs_host, fls_stats* stats_host, fls_stream_t stream) {
+  runs_host[0] = runs_host[1] = 0;
+  return compress_impl(W_dev, M, K, out_dev, out_capacity, FLS_ORDER_LOCATION, version, stats_host, stream, look_limit, by_ticket != 0, runs_host);
 }
 
 const char* fls_strerror(int code) {

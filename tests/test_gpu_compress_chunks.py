@@ -114,24 +114,47 @@ def test_more_threads_than_the_library_has_scratch_for(fls, oracle_mod):
     assert not wrong
 
 
-@pytest.mark.parametrize("version", [1, 2])
-@pytest.mark.parametrize("bands,kt", [(1, 1), (3, 5), (16, 1025)])
-def test_a_kernel_that_gives_up_is_run_again_by_ticket(fls, oracle_mod, version, bands, kt):
-    """With 1025 chunks, four to a CU, some workgroup looks for a word that is not there yet: the call is made again with chunks by
-    ticket, and twice in a row (the ticket counts from 0 each time)."""
+def _compress_as(fls, Wd, bands, kt, version, room, look_limit, by_ticket):
+    """fls_compress with those looks before it gives up and that order of chunks: the buffer, nnz, kernel runs by number and by ticket."""
     import ctypes
 
     import torch
 
+    f = fls.lib().fls_internal_compress
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_int,
+                  ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(fls.FlsStats), ctypes.c_void_p]
+    out = torch.zeros(room, dtype=torch.uint8, device="cuda")
+    st, runs = fls.FlsStats(), (ctypes.c_uint32 * 2)()
+    stream = torch.cuda.current_stream().cuda_stream
+    assert f(Wd.data_ptr(), bands * 128, kt * 32, out.data_ptr(), out.numel(), version, look_limit, by_ticket, runs, ctypes.byref(st), stream) == fls.OK
+    return out.cpu().numpy(), st.nnz, tuple(runs)
+
+
+@pytest.mark.parametrize("version", [1, 2])
+@pytest.mark.parametrize("bands,kt", [(1, 1), (3, 5), (4, 33), (16, 1025)])
+def test_chunks_by_ticket(fls, oracle_mod, version, bands, kt):
+    """One chunk, several, and four to a CU, in the order in which workgroups start: three times on one place of the scratch (the
+    ticket counts from 0 each time), and by number on that place afterwards."""
     W = _weights(bands, kt, [800, 0, 2049, 30], 41)
     ref = (oracle_mod.ref_compress_v2 if version == 2 else oracle_mod.ref_compress)(W)
-    Wd = _dev(W)
-    f = fls.lib().fls_internal_compress_impatient
-    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint32,
-                  ctypes.POINTER(fls.FlsStats), ctypes.c_void_p]
-    for _ in range(2):
-        out = torch.zeros(len(ref) + 16, dtype=torch.uint8, device="cuda")
-        st = fls.FlsStats()
-        stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-        assert f(Wd.data_ptr(), bands * 128, kt * 32, out.data_ptr(), out.numel(), version, ctypes.byref(st), stream) == fls.OK
-        assert np.array_equal(out[:len(ref)].cpu().numpy(), ref) and st.nnz == int(np.count_nonzero(W))
+    Wd, nnz = _dev(W), int(np.count_nonzero(W))
+    for by_ticket in (1, 1, 1, 0):
+        got, stored, runs = _compress_as(fls, Wd, bands, kt, version, len(ref) + 16, 1 << 22, by_ticket)
+        assert np.array_equal(got[:len(ref)], ref) and stored == nnz and runs == (1 - by_ticket, by_ticket)
+
+
+@pytest.mark.parametrize("version", [1, 2])
+def test_a_kernel_that_gives_up_is_run_again_by_ticket(fls, oracle_mod, version):
+    """With 1025 chunks, four to a CU, some workgroup looks for a word that is not there yet: the call is made again with chunks by
+    ticket, on the place that the run before left marked and that is cleared first.  Several in a row, and ordinary ones in between."""
+    bands, kt = 16, 1025
+    W = _weights(bands, kt, [800, 0, 2049, 30], 41)
+    ref = (oracle_mod.ref_compress_v2 if version == 2 else oracle_mod.ref_compress)(W)
+    Wd, nnz = _dev(W), int(np.count_nonzero(W))
+    again = 0
+    for look_limit in (1, 1, 1 << 22, 1):
+        got, stored, runs = _compress_as(fls, Wd, bands, kt, version, len(ref) + 16, look_limit, 0)
+        assert np.array_equal(got[:len(ref)], ref) and stored == nnz
+        assert runs in ((1, 0), (1, 1)) and (look_limit == 1 or runs == (1, 0))
+        again += runs[1]
+    assert again > 0
