@@ -113,3 +113,19 @@ def test_partial_sums_fit_their_area(plan, cus):
             groups = -(-N // 64)
             units = -(-M // 512) * groups if kind == "wide" else -(-M * share // 512) * -(-N // (128 * share))
             assert units * slices <= min(cus, 512) and M // 128 * groups * slices <= 2048
+
+
+@pytest.mark.parametrize("cus", [8, 64, 256, 304])
+def test_what_the_wider_passes_divide_is_small_enough(plan, cus):
+    """Unit numbers and slice x K tiles: the kernels' division by multiplication is exact below 2^29."""
+    largest = [(128, 2**23, 64), (2**23, 480, 64), (128 * 512, 2**15, 8192), (2**25, 96, 31), (2**17 - 128, 2**14, 8191)]
+    for M, K, N in [*_shapes(200), *largest]:
+        assert M * K < 2**32 and max(M, K) * N < 2**30  # what a call may have
+        bands, groups, kt = M // 128, -(-N // 64), K // 32
+        for rounds, version in itertools.product((2, 6, 10), (1, 2)):
+            kind, share, _, slices = plan(rounds, version, M, K, N, cus)
+            if kind != "narrow":
+                units = (-(-bands * share // 4) * -(-N // (128 * share)) if kind == "block" else -(-bands // 4) * groups) * slices
+                assert units + 8 * groups < 2**29 and (slices + 1) * kt < 2**29, (M, K, N)
+        # the dense product: units of four bands and 64 columns, as many slices as fill the CUs
+        assert max(-(-bands // 4) * groups, cus) + 8 * groups < 2**29 and (cus + 1) * kt < 2**29

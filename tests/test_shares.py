@@ -52,7 +52,7 @@ def test_every_share_runs_once_and_holds_tiles(shares, cus):
     for bands, kt, tile_us, wide in _shapes(1500):
         P, unit, grid = shares(bands, kt, cus, tile_us, wide)
         assert 1 <= P <= cus and (unit == 0 or P % unit == 0)
-        assert P * bands * kt < 2**32  # the kernels' share arithmetic is 32 bits wide
+        assert P * bands * kt < 2**29  # the kernels' division by multiplication is exact below
         assert sorted(q for q in (_share(P, unit, b) for b in range(grid)) if q is not None) == list(range(P))
         begins = [_begin(P, unit, bands, kt, q) for q in range(P + 1)]
         assert begins[0] == 0 and begins[-1] == bands * kt and all(a < b for a, b in zip(begins, begins[1:]))
@@ -60,6 +60,19 @@ def test_every_share_runs_once_and_holds_tiles(shares, cus):
             assert all(b % kt == 0 for b in begins)
         elif unit > 1:  # the shares of a band, or of a pair of bands, on one XCD, and at most one workgroup to a CU there
             assert begins[unit] in (kt, 2 * kt) and -(-P // unit // 8) * unit <= max(1, cus // 8)
+
+
+@pytest.mark.parametrize("cus", [8, 64, 256])
+def test_shares_begin_where_the_kernels_division_says(shares, cus):
+    """share_begin of the kernels, with the library's own division: no tile is left out or done twice."""
+    import paper_2309_10285_amd as fls
+
+    div = fls.lib().fls_internal_divide
+    div.argtypes, div.restype = [ctypes.c_uint32] * 2, ctypes.c_uint32
+    for bands, kt, tile_us, wide in _shapes(150):
+        P, unit, _ = shares(bands, kt, cus, tile_us, wide)
+        for q in range(P + 1):
+            assert (div(q * bands, P) * kt if unit == 0 else div(q * bands * kt, P)) == _begin(P, unit, bands, kt, q), (bands, kt, q)
 
 
 @pytest.mark.parametrize("bands,kt,tile_us,wide,want", [
