@@ -232,9 +232,10 @@ inline Shares pick_shares(uint32_t bands, uint32_t KT, int cus, float tile_us, b
   if (T < 64u * (uint64_t)cus) {
     uint32_t best = 1;
     float us = tile_us * (float)KT;
+    const uint32_t near = (uint32_t)(cus >= 8 ? cus / 8 : 1) / ((bands + 7u) / 8u);  // k up to which cut_shares keeps a band's shares on one XCD
     for (uint32_t k = 2; k <= most && k * 8u <= KT; ++k) {
       float t = tile_us * (float)((KT + k - 1u) / k) + hand_over_us(k, wide);
-      if (cut_shares(bands * k, bands, cus).unit != k) t += 1.5f;
+      if (k > near) t += 1.5f;
       if (t < us) {
         us = t;
         best = k;
