@@ -108,22 +108,29 @@ inline uint32_t wide_steps(uint32_t bands, uint32_t col_groups, uint32_t KT, int
   return (wgs + (uint32_t)cus - 1u) / (uint32_t)cus * ((KT + S - 1u) / S);
 }
 // The sparse 64-column pass: a workgroup takes four bands (one per wave), a group of 64 columns and a
-// K slice made of whole loop bodies of `body` tiles, and writes one partial result per band, column
+// K slice made of whole loop bodies, and writes one partial result per band, column
 // group and slice.  Slices per (group of four bands, column group): as many as fill the CUs, none
-// shorter than two bodies.  With S > 1, groups of bands x column groups x S <= CUs <= kMaxWorkgroups,
+// shorter than two bodies, or one where that pays.  With S > 1, groups of bands x column groups x S <= CUs <= kMaxWorkgroups,
 // so at most 4 * kMaxWorkgroups partial results exist (what parts_floats provides).
 inline uint32_t wide_body(uint32_t rounds) { return rounds <= 4u ? 8u : 4u; }  // by the rounds of a tile that the variant stages
-inline uint32_t wide_quad_slices(uint32_t bands, uint32_t col_groups, uint32_t KT, int cus, uint32_t body) {
+inline uint32_t wide_quad_slices(uint32_t bands, uint32_t col_groups, uint32_t KT, int cus, uint32_t rounds) {
   if (cus > (int)kMaxWorkgroups) cus = (int)kMaxWorkgroups;
+  const uint32_t body = wide_body(rounds), bodies = KT / body;
   const uint64_t units = (uint64_t)((bands + 3) / 4) * col_groups;
-  uint32_t S = units < (uint64_t)cus ? (uint32_t)((uint64_t)cus / units) : 1u;
-  uint32_t by_length = KT / (2u * body) > 0 ? KT / (2u * body) : 1u;
-  // ... or one, as long as that makes few workgroups and few sums of it: up to 96 and 16 (us, two bodies / one: 2048 x 2880 at 90 % in version 2, N = 54
-  // 17.6 / 13.7, 1152 x 1504 at 70 %, N = 110 18.7 / 14.9; but 1408 x 10944 at 90 %, N = 56, 42 slices, 19.8 / 23.9, 4608 x 1344 at 80 % in
-  // version 2, N = 264, 225 workgroups, 26.6 / 29.9)
-  const uint32_t few = units <= 6u ? 16u : (uint32_t)(96u / units);
-  if (by_length < few) by_length = KT / body < few ? (KT / body > 0 ? KT / body : 1u) : few;
-  return S < by_length ? S : by_length;
+  const uint32_t fill = units < (uint64_t)cus ? (uint32_t)((uint64_t)cus / units) : 1u;
+  const uint32_t two = bodies / 2u > 0 ? bodies / 2u : 1u, S2 = fill < two ? fill : two;  // slices of two bodies and more
+  // ... or of one, as long as that makes few workgroups and few sums of it (up to 96 and 16), where the bodies that a workgroup has less to walk take longer than
+  // what the further slices cost: 0.96 of the pass's step times against 1.66 us for the second kernel, where there was none, and the sums out and back at 4.9 TB/s.
+  // Fitted to 212 products of 33 - 640 columns on which the two differ (M 128 ... 6000, K 256 ... 16384, 60 - 90 %, both formats; rms 0.7 us): one body always is
+  // 1.146 times faster than two and up to 1.46 times slower, the pick 1.157 and 1.06, the better of both 1.159.  On 238 others 1.186, 1.187 and
+  // 1.190, at worst 1.17 times slower than two bodies (1024 x 2944, N = 192 17.5 / 20.4), next 1.10.  Some of them (us, two
+  // bodies / one): 2944 x 1088, N = 58 16.3 / 14.2; 1152 x 1504, N = 110 18.7 / 14.9; 2560 x 288, N = 564 12.1 / 17.7; 3584 x 608, N = 378 14.9 / 17.8; 4608 x 416, N = 260
+  // 14.5 / 18.6; 2176 x 1056, N = 360 17.4 / 19.0.  Beyond 96 workgroups: 1408 x 10944, N = 56, 42 slices, 19.8 / 23.9; 4608 x 1344, N = 264, 225 workgroups, 26.6 / 29.9.
+  const uint32_t few = units <= 6u ? 16u : (uint32_t)(96u / units), one = bodies < few ? bodies : few, S1 = fill < one ? fill : one;
+  if (S1 <= S2) return S2;
+  const float saved = 0.96f * (float)((bodies + S2 - 1u) / S2 - (bodies + S1 - 1u) / S1) * (float)body * (0.16f + 0.081f * (float)rounds);
+  const float sums = 2.f * 32768.f / 4.9e6f * (float)bands * (float)col_groups * (float)(S1 - (S2 > 1u ? S2 : 0u));
+  return saved > sums + (S2 > 1u ? 0.f : 1.66f) ? S1 : S2;
 }
 // How the 64-column passes spread their (group of four bands, K slice) pairs over the eight XCDs: whole pairs, in turn,
 // unless that leaves an XCD so many more workgroups than others that it takes a round more than an even cut of
@@ -286,7 +293,7 @@ inline float narrow_us(float w_bytes, uint32_t rounds, uint32_t bands, uint32_t 
   return us;
 }
 inline float wide_us(float w_bytes, uint32_t rounds, uint32_t bands, uint32_t KT, uint32_t N, int cus) {  // N <= 64
-  const uint32_t body = wide_body(rounds), quads = (bands + 3u) / 4u, S = wide_quad_slices(bands, 1u, KT, cus, body);
+  const uint32_t body = wide_body(rounds), quads = (bands + 3u) / 4u, S = wide_quad_slices(bands, 1u, KT, cus, rounds);
   const uint32_t bodies = (KT / body + S - 1u) / S, turns = (quads * S + (uint32_t)cus - 1u) / (uint32_t)cus;
   const float work = (float)(bodies * body) * (0.16f + 0.081f * (float)rounds) * (N <= kGroupCols ? 0.9f : 1.f) + 1.09f * (float)(KT % body);
   const float memory = w_bytes / 8.0e6f;
@@ -303,7 +310,7 @@ inline bool wide32_allowed(uint32_t need, uint32_t version, uint32_t bands, uint
   if (version == 2u) return need <= 4u && KT >= 1024u;
   if (KT >= 384u) return true;
   if (KT < 288u || need <= 2u) return false;
-  const uint32_t body = wide_body(wide_rounds(need)), bodies = KT / body, S = wide_quad_slices(bands, 1u, KT, cus, body);
+  const uint32_t bodies = KT / wide_body(wide_rounds(need)), S = wide_quad_slices(bands, 1u, KT, cus, wide_rounds(need));
   return (uint64_t)((bodies + S - 1u) / S) * S * 10u <= (uint64_t)bodies * 11u;
 }
 // `rounds` of the variant that the pass would run.

@@ -441,7 +441,7 @@ SpmmPlan spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t bands, ui
     if (share > 0)
       return {SpmmPass::kBlock, share, block_rounds(share, need), block_slices(block_band_groups(bands, share) * block_col_groups(N, share), KT, cus)};
     const uint32_t rounds = wide_rounds(need);
-    return {SpmmPass::kWide, 0u, rounds, wide_quad_slices(bands, groups, KT, cus, wide_body(rounds))};
+    return {SpmmPass::kWide, 0u, rounds, wide_quad_slices(bands, groups, KT, cus, rounds)};
   }
   return {SpmmPass::kNarrow, 0u, need <= 8u ? wide_rounds(need) : 8u, possible ? 1u : 0u};
 }

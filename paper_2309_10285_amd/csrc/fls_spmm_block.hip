@@ -393,7 +393,7 @@ uint32_t spmm_pass_share(uint32_t need, uint32_t bands, uint32_t KT, uint32_t N,
     return us;
   };
   // the 64-column pass: whole bodies, and in the last slice tile by tile what is left of K
-  const uint32_t groups = (N + 63u) / 64u, S0 = wide_quad_slices(bands, groups, KT, cus, body), bodies = (KT / body + S0 - 1u) / S0;
+  const uint32_t groups = (N + 63u) / 64u, S0 = wide_quad_slices(bands, groups, KT, cus, R), bodies = (KT / body + S0 - 1u) / S0;
   float best = 0.97f * estimate(4.0f, (bands + 3u) / 4u * groups, S0, bodies > 0u ? 3.0f : 0.0f,
                                 (float)(bodies * body) * (0.24f + 0.08f * (float)R) + (float)(KT % body) * (0.90f + 0.28f * (float)R));
   uint32_t pick = 0;

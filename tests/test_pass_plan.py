@@ -94,6 +94,23 @@ def test_the_rule_takes_the_pass_that_measured_faster(plan, rounds, version, M, 
     assert plan(rounds, version, M, K, N)[1] == share
 
 
+@pytest.mark.parametrize("rounds,version,M,K,N,slices", [
+    # us, slices of two bodies and more / of one
+    (6, 1, 2560, 288, 564, 1),    # 12.1 / 17.7: one slice has no second kernel and no sums
+    (6, 1, 4608, 416, 260, 1),    # 14.5 / 18.6
+    (6, 2, 4096, 288, 244, 1),    # 12.4 / 15.1
+    (3, 1, 3584, 608, 378, 1),    # 14.9 / 17.8
+    (4, 1, 2176, 512, 341, 1),    # 13.5 / 15.8
+    (6, 2, 4096, 1536, 50, 6),    # 15.6 / 17.6 with twelve
+    (3, 1, 2176, 1056, 360, 2),   # 17.4 / 19.0 with three
+    (6, 2, 2944, 1088, 58, 8),    # 16.3 with four / 14.2
+    (4, 1, 1024, 1024, 64, 4),    # 15.0 with two / 11.5
+    (2, 2, 2048, 2880, 54, 11),   # 17.6 with five / 13.7
+])
+def test_slices_of_one_body_where_they_measured_faster(plan, rounds, version, M, K, N, slices):
+    assert plan(rounds, version, M, K, N)[3] == slices
+
+
 def _shapes(count):
     rng = random.Random(7)
     for _ in range(count):
