@@ -265,12 +265,16 @@ inline Shares pick_shares(uint32_t bands, uint32_t KT, int cus, float tile_us, b
 // A call of 17 - 64 columns: passes of up to 32 columns, or the 64-column pass (up to 32 columns with one 32-column block multiplied).
 // The narrow kernel streams W once per 32 columns and fetches X per tile and wave; the pass shares X between four bands and
 // streams W once, but cuts K into slices whose sums a second kernel adds.  Which one is an estimate of each in us:
-//   narrow, a pass   4.9 + the larger of 1.02 tile_us x tiles of a workgroup and W at 7.3 TB/s + 64 B of X per tile and column at 8.8 TB/s + the
+//   narrow, a pass   4.9 (6.1 on bands of fewer than eight tiles, whose sums take the slow way) + the larger of 1.02 tile_us x tiles of a workgroup and W at 7.3 TB/s + 64 B of X per tile and column at 8.8 TB/s + the
 //                    hand-over of pick_shares, 1.5 more where the shares of a band are not kept on one XCD
-//   64 columns       6.7 + for a round of workgroups (0.16 + 0.081 R) x tiles of its bodies (0.9 of it with one block) + 1.09 x the K tiles that fill
-//                    no body, or W at 8 TB/s, whichever is larger (fourth powers added); and the partial sums out and back at 4.35 TB/s
+//   64 columns       5.05, 0.7 less without a body + for a round of workgroups (0.16 + 0.081 R) x tiles of its bodies (0.9 of it with one block) + 1.09 x
+//                    the K tiles that fill no body, or W at 8 TB/s, whichever is larger (fourth powers added); with more than one slice 1.65 for the second
+//                    kernel and the partial sums out and back at 4.35 TB/s
 // fitted to 300 products (M 1024 ... 49152, K 1024 ... 49152, 60 - 90 %, both formats; rms 5.5 and 7.5 %).  Its pick takes 1.005 times the better one of
-// the two, and 0.964 and 0.85 times what the pass for all calls of 33 - 64 and a rule on K and density for 17 - 32 columns took.  Some of
+// the two, and 0.964 and 0.85 times what the pass for all calls of 33 - 64 and a rule on K and density for 17 - 32 columns took.  (Charging the second kernel
+// to calls of one slice, which have none, and to bands of less than a body cost short bands up to half: 41216 x 160, N = 35 13.2 / 8.7, 29952 x
+// 192, N = 50 14.8 / 10.3, 384 x 224, N = 57 14.0 / 9.7, 34944 x 448, N = 62 19.1 / 15.4; of 1200 drawn calls of 33 - 64 columns 180 take narrow passes with that charge, and 49 of
+// these the pass without it, 1.14 times faster in the mean, one 1.15 times slower.)  Some of
 // what was measured (us, narrow / 64-column): N = 64, 80 %: 1024 x 1024 16.3 / 15.0, 32768 x 1024
 // 18.3 / 26.5, 8192 x 8192 35.2 / 35.4, 12288 x 12288 63.7 / 43.8; at 90 % 8192 x 8192 27.7 / 32.7 (and 16384 x 4096 26.4 / 32.5, where it picks the pass); N = 31: 8832 x 48736 at 90 %
 // 62.6 / 51.9, 6272 x 13440 at 90 % 16.6 / 25.4, 16128 x 10400 at 80 % 29.6 / 43.5; N = 32, 27648 x 9216 at 70 % 62.5 / 58.4.
@@ -287,7 +291,7 @@ inline float narrow_us(float w_bytes, uint32_t rounds, uint32_t bands, uint32_t 
     const Shares s = pick_shares(bands, KT, cus, tile, wide);
     const uint32_t cols = N - n0 < kGroupCols ? N - n0 : kGroupCols;
     const float work = 1.02f * tile * T / (float)s.P, memory = w_bytes / 7.3e6f + T * (float)cols * 64.f / 8.8e6f;
-    us += 4.9f + (work > memory ? work : memory);
+    us += (KT < 8u ? 6.1f : 4.9f) + (work > memory ? work : memory);
     if (s.unit != 0u) us += hand_over_us(s.unit > 1u ? s.unit : s.P / bands + 1u, wide) + (s.unit > 1u ? 0.f : 1.5f);
   }
   return us;
@@ -297,8 +301,8 @@ inline float wide_us(float w_bytes, uint32_t rounds, uint32_t bands, uint32_t KT
   const uint32_t bodies = (KT / body + S - 1u) / S, turns = (quads * S + (uint32_t)cus - 1u) / (uint32_t)cus;
   const float work = (float)(bodies * body) * (0.16f + 0.081f * (float)rounds) * (N <= kGroupCols ? 0.9f : 1.f) + 1.09f * (float)(KT % body);
   const float memory = w_bytes / 8.0e6f;
-  float us = 6.7f + (float)turns * sqrtf(sqrtf(work * work * work * work + memory * memory * memory * memory));
-  if (S > 1u) us += 0.07f * (float)(1u + S / 8u) + 2.f * (float)bands * (float)S * (N <= kGroupCols ? 16384.f : 32768.f) / 4.35e6f;
+  float us = (KT < body ? 4.35f : 5.05f) + (float)turns * sqrtf(sqrtf(work * work * work * work + memory * memory * memory * memory));
+  if (S > 1u) us += 1.65f + 0.07f * (float)(1u + S / 8u) + 2.f * (float)bands * (float)S * (N <= kGroupCols ? 16384.f : 32768.f) / 4.35e6f;
   return us;
 }
 // May a call of 17 - 32 columns take the 64-column pass at all?  The narrow kernel takes no offset to lie beyond the header's word count and

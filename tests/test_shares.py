@@ -119,6 +119,13 @@ def test_division_by_multiplication(shares):
     (6, 1, 27648, 9216, 32, "wide"),      # 62.5 / 58.4
     (6, 2, 12288, 49152, 32, "narrow"),   # version 2 has variants with one column block for up to four rounds
     (9, 1, 32768, 1024, 64, "wide"),      # the narrow kernel stages eight rounds
+    (3, 1, 41216, 160, 35, "wide"),       # 13.2 / 8.7: one slice, no body
+    (3, 2, 29952, 192, 50, "wide"),       # 14.8 / 10.3
+    (4, 2, 128, 128, 54, "wide"),         # 12.0 / 8.4
+    (3, 2, 384, 224, 57, "wide"),         # 14.0 / 9.7: bands of fewer than eight tiles
+    (3, 1, 34944, 448, 62, "wide"),       # 19.1 / 15.4: one slice
+    (3, 2, 45056, 480, 53, "wide"),       # 19.1 / 16.2
+    (8, 1, 26368, 512, 41, "narrow"),     # 14.6 / 20.5
 ])
 def test_the_rule_for_17_to_64_columns(shares, rounds, version, M, K, N, want):
     import paper_2309_10285_amd as fls
