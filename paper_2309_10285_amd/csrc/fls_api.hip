@@ -565,6 +565,11 @@ void fls_internal_spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t 
   out[3] = plan.slices;
 }
 
+void fls_internal_dense_plan(uint32_t M, uint32_t K, uint32_t N, int cus, uint32_t* out) {
+  out[0] = fls::dense_col_groups(M, K, N, cus);
+  out[1] = fls::wide_slices(M / FLS_TILE_M, out[0], (K + 63u) / 64u, cus);
+}
+
 void fls_internal_shares(uint32_t M, uint32_t K, int cus, float tile_us, int wide, uint32_t* out) {
   const fls::Shares s = fls::pick_shares(M / FLS_TILE_M, K / FLS_TILE_K, cus, tile_us, wide != 0);
   out[0] = s.P;

@@ -328,14 +328,7 @@ hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream) {
     const uint32_t left = a.N - n0;
     hipError_t e;
     if (left > kGroupCols) {
-      // A rest of up to 32 columns joins the launch as its last, partly empty group, whose workgroups find W in their XCD's L2, instead of
-      // a pass of its own (12288 x 12288, N = 80: 163 -> 149 us; 9856 x 4672, N = 94: 74 -> 59; 1152 x 5792, N = 158: 50 -> 36), unless a further
-      // group takes so many K slices away, or a round of workgroups more, that it costs more than the pass: 3 us a step against 8 us and W at 4 TB/s (30848 x 5248,
-      // N = 143 217 us with a pass for the rest, 246 without, 6272 x 16544, N = 199 243 and 253, 35712 x 3808, N = 219 321 and 421).
-      const uint32_t full = left / kSpmmGroupCols, rest = left % kSpmmGroupCols, bands = a.M / kTileM, steps = (a.K + 63u) / 64u;
-      const float longer = 3.f * ((float)wide_steps(bands, full + 1u, steps, a.num_cus) - (float)wide_steps(bands, full > 0 ? full : 1u, steps, a.num_cus));
-      const bool join = rest > kGroupCols || (rest > 0 && longer < 8.f + (float)a.M * (float)a.K * 2.f / 4.0e6f);
-      const uint32_t col_groups = full + (join ? 1u : 0u);
+      const uint32_t col_groups = dense_col_groups(a.M, a.K, left, a.num_cus);
       e = launch_dense_wide(a, n0, col_groups, stream);
       n0 += col_groups * kSpmmGroupCols;
     } else {

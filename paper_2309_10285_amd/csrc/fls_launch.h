@@ -91,21 +91,41 @@ constexpr uint32_t kMaxWorkgroups = 512;    // most shares of a launch of up to 
 constexpr uint32_t kErrorWord = kMaxWorkgroups, kOwnerXcd = 2 * kMaxWorkgroups, kLocalFlags = 3 * kMaxWorkgroups, kControlWords = 4 * kMaxWorkgroups;
 // The 64-column pass of the dense kernel cuts its work as (group of 4 bands) x (K slice), one wave
 // per band, and keeps one 128 x 64 fp32 partial result per band and slice.  Slices per group: as
-// many as fill the CUs, but none shorter than two steps of 64 k (at least 16 steps before: 1408 x 1120,
-// N = 182 37.9 us against 17.6 with four steps and 18.0 with two, 5120 x 1120, N = 51 71.2 / 24.2 / 22.8, 1280 x 1888, N = 97 90.0 / 21.4 / 18.3;
-// 100 drawn products of 33 - 256 columns 1.55 and 1.58 times faster).  groups * slices <= kMaxWorkgroups, so
+// many as fill the CUs, none shorter than 16 steps of 64 k, or than two where the steps that a workgroup has less to walk (2.4 us each) take longer than what the
+// further slices cost: their sums out and back at 4.2 TB/s and 2.5 us for the second kernel where there was none.  1408 x 1120, N = 182 37.9 us with slices
+// of 16 steps, 18.0 with two, 5120 x 1120, N = 51 71.2 / 22.8, 1280 x 1888, N = 97 90.0 / 18.3; but 7424 x 224, N = 356 16.8 / 30.7, 15744 x 352, N = 240 20.9 /
+// 36.7, 28928 x 384, N = 78 25.1 / 34.3.  On 306 products of 33 - 640 columns on which the two differ (M 128 ... 50000, K 64 ... 4096) two steps always are 1.60 times
+// faster and up to 1.8 times slower, the pick 1.62 and (128 rows, a microsecond) 1.15, the better of both 1.63.  groups * slices <= kMaxWorkgroups, so
 // bands * slices <= 4 * kMaxWorkgroups partial results at most (what parts_floats provides).
 inline uint32_t wide_slices(uint32_t bands, uint32_t col_groups, uint32_t KT, int cus) {
   if (cus > (int)kMaxWorkgroups) cus = (int)kMaxWorkgroups;
   const uint64_t units = (uint64_t)((bands + 3) / 4) * col_groups;  // (group of four bands, group of 64 columns)
-  uint32_t S = units < (uint64_t)cus ? (uint32_t)((uint64_t)cus / units) : 1u;
-  const uint32_t by_length = KT / 2u > 0 ? KT / 2u : 1u;
-  return S < by_length ? S : by_length;
+  const uint32_t fill = units < (uint64_t)cus ? (uint32_t)((uint64_t)cus / units) : 1u;
+  auto slices = [&](uint32_t shortest) {
+    const uint32_t by_length = KT / shortest > 0 ? KT / shortest : 1u;
+    return fill < by_length ? fill : by_length;
+  };
+  const uint32_t S16 = slices(16u), S2 = slices(2u);
+  if (S2 <= S16) return S16;
+  const float saved = 2.4f * (float)((KT + S16 - 1u) / S16 - (KT + S2 - 1u) / S2);
+  const float sums = 2.f * 32768.f / 4.2e6f * (float)bands * (float)col_groups * (float)(S2 - (S16 > 1u ? S16 : 0u));
+  return saved > sums + (S16 > 1u ? 0.f : 2.5f) ? S2 : S16;
 }
 // Steps that a CU takes one after the other in that pass.
 inline uint32_t wide_steps(uint32_t bands, uint32_t col_groups, uint32_t KT, int cus) {
   const uint32_t S = wide_slices(bands, col_groups, KT, cus), wgs = (bands + 3u) / 4u * col_groups * S;
   return (wgs + (uint32_t)cus - 1u) / (uint32_t)cus * ((KT + S - 1u) / S);
+}
+// Groups of 64 columns in the launch that the dense product's `left` > 32 columns begin with.
+// A rest of up to 32 columns joins the launch as its last, partly empty group, whose workgroups find W in their XCD's L2, instead of
+// a pass of its own (12288 x 12288, N = 80: 163 -> 149 us; 9856 x 4672, N = 94: 74 -> 59; 1152 x 5792, N = 158: 50 -> 36), unless a further
+// group takes so many K slices away, or a round of workgroups more, that it costs more than the pass: 3 us a step against 8 us and W at 4 TB/s (30848 x 5248,
+// N = 143 217 us with a pass for the rest, 246 without, 6272 x 16544, N = 199 243 and 253, 35712 x 3808, N = 219 321 and 421).
+inline uint32_t dense_col_groups(uint32_t M, uint32_t K, uint32_t left, int cus) {
+  const uint32_t full = left / kSpmmGroupCols, rest = left % kSpmmGroupCols, bands = M / 128u, steps = (K + 63u) / 64u;
+  const float longer = 3.f * ((float)wide_steps(bands, full + 1u, steps, cus) - (float)wide_steps(bands, full > 0 ? full : 1u, steps, cus));
+  const bool join = rest > kGroupCols || (rest > 0 && longer < 8.f + (float)M * (float)K * 2.f / 4.0e6f);
+  return full + (join ? 1u : 0u);
 }
 // The sparse 64-column pass: a workgroup takes four bands (one per wave), a group of 64 columns and a
 // K slice made of whole loop bodies, and writes one partial result per band, column
@@ -371,6 +391,9 @@ hipError_t launch_lower_flags(uint32_t* flags, hipStream_t stream);
 // label, not part of the C ABI.
 extern "C" void fls_internal_spmm_plan(uint32_t max_tile_words, uint32_t version, uint32_t M, uint32_t K, uint32_t N, int cus, int wide32,
                                        uint32_t* out);
+
+// What fls_dense_gemm of more than 32 columns launches first: out = groups of 64 columns, K slices.  As above.
+extern "C" void fls_internal_dense_plan(uint32_t M, uint32_t K, uint32_t N, int cus, uint32_t* out);
 
 // How the tiles of an M x K matrix are shared out in the passes of up to 32 columns: out = P, unit, grid of Shares.  As above.
 extern "C" uint32_t fls_internal_divide(uint32_t n, uint32_t d);  // as the kernels divide

@@ -5,6 +5,8 @@ against the product in 64 bits (a unit that nobody takes leaves its part of C at
 Tolerance: products of fp16 values are exact in fp32, sums of K <= 2048 of them are off by far less than the fp16 rounding of
 C, 2^-11 of the value: 2e-3 of the largest value, as in the other parity tests.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -43,9 +45,10 @@ def test_every_unit_is_taken(M, K, N, whole):
     fls.ensure_workspace(M, K, N)
     blob, stats = fls.fls_compress(Wd)
     plan = fls.spmm_plan(stats, N, cus)
-    dense_slices = max(1, min(cus // (-(-M // 512) * -(-N // 64)), K // 512))
-    assert plan["pass"] == "wide"
-    assert _whole(M, N, plan["slices"], cus) == whole and _whole(M, N, dense_slices, cus) == whole
+    dense = (ctypes.c_uint32 * 2)()
+    fls.lib().fls_internal_dense_plan(M, K, N, cus, dense)
+    assert plan["pass"] == "wide" and dense[0] == -(-N // 64)
+    assert _whole(M, N, plan["slices"], cus) == whole and _whole(M, N, dense[1], cus) == whole
     for call, first in ((fls.fls_spmm, blob), (fls.fls_dense_gemm, Wd)):
         C = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
         call(first, Xd, C, M, K, N)

@@ -1,4 +1,5 @@
 """Which pass and variant a product takes: the library's rule, asked on the host."""
+import ctypes
 import itertools
 import random
 
@@ -109,6 +110,25 @@ def test_the_rule_takes_the_pass_that_measured_faster(plan, rounds, version, M, 
 ])
 def test_slices_of_one_body_where_they_measured_faster(plan, rounds, version, M, K, N, slices):
     assert plan(rounds, version, M, K, N)[3] == slices
+
+
+@pytest.mark.parametrize("M,K,N,groups,slices", [
+    # us, slices of 16 steps and more / of two
+    (7424, 224, 356, 6, 1),     # 16.8 / 30.7: one slice has no second kernel and no sums
+    (15744, 352, 240, 4, 1),    # 20.9 / 36.7
+    (28928, 384, 78, 2, 1),     # 25.1 / 34.3
+    (9088, 352, 202, 4, 1),     # 21.9 / 33.4
+    (1408, 1120, 182, 3, 9),    # 37.9 / 18.0
+    (5120, 1120, 51, 1, 9),     # 71.2 / 22.8
+    (1280, 1888, 97, 2, 15),    # 90.0 / 18.3
+    (30848, 5248, 143, 2, 2),   # with a pass of its own for the rest 217, without 246
+])
+def test_dense_slices_where_they_measured_faster(plan, M, K, N, groups, slices):
+    import paper_2309_10285_amd as fls
+
+    out = (ctypes.c_uint32 * 2)()
+    fls.lib().fls_internal_dense_plan(M, K, N, 256, out)
+    assert tuple(out) == (groups, slices)
 
 
 def _shapes(count):
