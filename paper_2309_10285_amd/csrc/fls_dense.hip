@@ -312,7 +312,7 @@ hipError_t launch_dense(const DenseLaunch& a, hipStream_t stream) {
   p.out.M = a.M;
   p.out.N = a.N;
   p.out.raised = 1u;
-  const Shares shares = pick_shares(a.M / kTileM, a.K / kTileK, a.num_cus, 0.27f, a.N > 16u);
+  const Shares shares = pick_shares(a.M / kTileM, a.K / kTileK, a.num_cus, kDenseTileUs, a.N > 16u);
   p.out.P = shares.P;
   p.out.unit = shares.unit;
   p.out.units = shares.unit ? shares.P / shares.unit : 0u;

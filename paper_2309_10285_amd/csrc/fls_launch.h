@@ -224,7 +224,8 @@ struct Shares {
   uint32_t unit;  // shares that stay together on an XCD; 0: a share is whole bands, no partial sum crosses between workgroups
   uint32_t grid;  // workgroups, the idle ones that fill up the XCDs' parts among them (see share_of_block)
 };
-// What a tile costs a workgroup, in us, by the rounds that its variant stages (tiles of W that was left dense: 0.27).
+// What a tile costs a workgroup, in us, by the rounds that its variant stages, and a tile of W that was left dense.
+constexpr float kDenseTileUs = 0.27f;
 inline float tile_us(uint32_t rounds, bool wide) { return 0.035f + 0.0175f * (float)rounds + (wide ? 0.02f : 0.f); }
 // ... and a hand-over, of a band cut into k shares on one XCD.
 inline float hand_over_us(uint32_t k, bool wide) { return wide ? 1.9f + 0.52f * (float)(k / 2u) : 1.6f + 0.6f * (float)((k + 2u) / 4u); }
@@ -268,7 +269,14 @@ inline Shares pick_shares(uint32_t bands, uint32_t KT, int cus, float tile_us, b
         best = k;
       }
     }
-    return best > 1u ? cut_shares(bands * best, bands, cus) : shares_of(bands, 0u);
+    if (best > 1u) return cut_shares(bands * best, bands, cus);
+    // Bands for more than half the CUs leave no two shares to a band: whole bands, or all tiles cut evenly over all CUs where that is estimated to be less, for sparse
+    // tiles 2.5 us less.  (Dense, whole / cut: 138 bands of 92 steps of 32, N = 9 36.9 / 26.7, 149 of 62, N = 21 29.1 / 25.1, 175 of 49, N = 22 24.7 / 24.1; all 117 drawn products that
+    // it cuts gain, up to 1.46 times.  Of 34 sparse ones that took another time without the 2.5 us 27 were slower, by up to a tenth: 150 of 61, N = 24 14.6 / 16.1.)
+    const float cut = tile_us * (float)((T + (uint64_t)cus - 1u) / (uint64_t)cus) + hand_over_us(2u, wide) + 1.5f + (tile_us < kDenseTileUs ? 2.5f : 0.f);
+    if (T >= 8u * (uint64_t)cus && cut < us)
+      return cut_shares((uint32_t)cus, bands, cus);
+    return shares_of(bands, 0u);
   }
   // Larger problems are paced by HBM, not by the CUs: a count of the form bands * k, where every band has its own k workgroups, is
   // worth leaving up to a fifth of the CUs without one.
