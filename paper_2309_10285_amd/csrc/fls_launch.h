@@ -269,14 +269,14 @@ inline Shares pick_shares(uint32_t bands, uint32_t KT, int cus, float tile_us, b
         best = k;
       }
     }
-    if (best > 1u) return cut_shares(bands * best, bands, cus);
-    // Bands for more than half the CUs leave no two shares to a band: whole bands, or all tiles cut evenly over all CUs where that is estimated to be less, for sparse
-    // tiles 2.5 us less.  (Dense, whole / cut: 138 bands of 92 steps of 32, N = 9 36.9 / 26.7, 149 of 62, N = 21 29.1 / 25.1, 175 of 49, N = 22 24.7 / 24.1; all 117 drawn products that
-    // it cuts gain, up to 1.46 times.  Of 34 sparse ones that took another time without the 2.5 us 27 were slower, by up to a tenth: 150 of 61, N = 24 14.6 / 16.1.)
-    const float cut = tile_us * (float)((T + (uint64_t)cus - 1u) / (uint64_t)cus) + hand_over_us(2u, wide) + 1.5f + (tile_us < kDenseTileUs ? 2.5f : 0.f);
+    // k shares to a band leave up to half the CUs without one: all tiles cut evenly over all CUs instead where that is estimated to be 0.3 us less, for sparse
+    // tiles 2.5.  (Dense, k shares / cut: 138 bands of 92 steps of 32, N = 9 36.9 / 26.7, 149 of 62, N = 21 29.1 / 25.1, 175 of 49, N = 22 24.7 / 24.1, 92 of 154, N = 6 34.2 / 29.3, 70 of
+    // 123, N = 16 27.2 / 25.2; all 139 drawn products whose time it changed gain, up to 1.46 times.  Of 34 sparse ones that took another time without the 2.5 us
+    // 27 were slower, by up to a tenth: 150 of 61, N = 24 14.6 / 16.1.)
+    const float cut = tile_us * (float)((T + (uint64_t)cus - 1u) / (uint64_t)cus) + hand_over_us((uint32_t)cus / bands + 1u, wide) + 1.5f + (tile_us < kDenseTileUs ? 2.5f : 0.3f);
     if (T >= 8u * (uint64_t)cus && cut < us)
       return cut_shares((uint32_t)cus, bands, cus);
-    return shares_of(bands, 0u);
+    return best > 1u ? cut_shares(bands * best, bands, cus) : shares_of(bands, 0u);
   }
   // Larger problems are paced by HBM, not by the CUs: a count of the form bands * k, where every band has its own k workgroups, is
   // worth leaving up to a fifth of the CUs without one.

@@ -85,6 +85,8 @@ def test_shares_begin_where_the_kernels_division_says(shares, cus):
     (8, 64, 0.125, True, [40]),     # whole 12.8, in 4 / 5 / 8 9.6 / 9.3 / 9.6
     (138, 92, 0.27, False, [256]),  # dense: whole 36.9, cut evenly 26.7
     (191, 63, 0.27, False, [256]),  # 35.6 / 32.4
+    (92, 154, 0.27, False, [256]),  # in 2 shares 34.2, cut evenly 29.3
+    (25, 474, 0.27, True, [250]),   # in 10 shares 33.7, cut evenly 34.6
     (150, 61, 0.125, True, [150]),  # 90 %: 14.6 / 16.1
     (130, 110, 0.16, True, [256]),  # 21.2 / 18.9
     (384, 8, 0.105, False, [192]),  # two bands to a workgroup 7.3, cut over 256 9.7
