@@ -163,11 +163,13 @@ int fls_check_workspace(fls_stream_t stream);
 
 /*
  * C = W . X with W given as a Tiled-CSL blob (the SpMM of Alg. 1): streams the blob from HBM
- * (once per 64 columns for N > 32, per 128 or 256 in the block pass that many calls of more than 64 take, else once), rebuilds each tile densely in LDS, multiplies
+ * (once up to 32 columns; beyond, once per 32 columns in narrow passes, per 64 in the 64-column pass, per 128 or 256 in the block pass), rebuilds each tile densely in LDS, multiplies
  * with MFMA, fp32 accumulation.  Partial sums of different workgroups are added in a fixed order;
  * inside a workgroup the waves' sums are added in the order they finish unless the workgroup's
  * tiles lie in one row band (then in wave order), so two runs may differ in the last bit of an
- * fp32 sum, never by more.  2*K*N and 2*M*N must stay below 2^31 (32-bit byte offsets into X and C).
+ * fp32 sum, never by more; this holds for calls of up to 64 columns - those
+ * of 33 - 64 run as passes of up to 32 where that is the faster way - and wider ones on blobs with tiles less than about 40 % sparse.
+ * The 64-column and block passes give the same bits every time and wait for no other workgroup.  2*K*N and 2*M*N must stay below 2^31 (32-bit byte offsets into X and C).
  *   Wc_dev in : blob made by fls_compress (or byte-identical); its header must match M, K
  *   X_dev  in : fp16 column-major K x N;  C_dev out: fp16 column-major M x N (fully overwritten)
  * The first call on a given blob address reads its 64-byte header back (a copy on `stream`, waited for) to
