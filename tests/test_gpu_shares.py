@@ -37,6 +37,7 @@ def _operands(bands, kt, N, sparsity, seed):
     (8, 9), (3, 31), (8, 32), (7, 63),       # whole bands, or cut into shares of at least eight tiles
     (9, 144), (1, 512), (3, 700), (42, 51),  # many shares to a band; bands that lie on two XCDs
     (257, 4), (300, 9), (270, 40),           # more bands than CUs: whole bands, or all tiles cut evenly
+    (130, 36), (130, 88),                    # more than half as many: whole bands, or all tiles cut evenly (dense; and 24 columns)
 ])
 def test_products_of_every_cut(fls, oracle_mod, bands, kt, N, version):
     import torch
