@@ -105,7 +105,9 @@ inline uint32_t wide_slices(uint32_t bands, uint32_t col_groups, uint32_t KT, in
     const uint32_t by_length = KT / shortest > 0 ? KT / shortest : 1u;
     return fill < by_length ? fill : by_length;
   };
-  const uint32_t S16 = slices(16u), S2 = slices(2u);
+  // (at most 128 of two steps: the second kernel adds them one after the other.  One unit, 256 / 128 slices: 128 x 30848, N = 52 27.9 / 20.5, 256 x 32640, N = 57 34.9 / 25.7, 128 x
+  // 18368, N = 52 19.3 / 18.4; 64 are faster still there, and up to 1.29 times slower on two units.)
+  const uint32_t S16 = slices(16u), S2 = slices(2u) < 128u ? slices(2u) : 128u;
   if (S2 <= S16) return S16;
   const float saved = 2.4f * (float)((KT + S16 - 1u) / S16 - (KT + S2 - 1u) / S2);
   const float sums = 2.f * 32768.f / 4.2e6f * (float)bands * (float)col_groups * (float)(S2 - (S16 > 1u ? S16 : 0u));

@@ -121,6 +121,7 @@ def test_slices_of_one_body_where_they_measured_faster(plan, rounds, version, M,
     (1408, 1120, 182, 3, 9),    # 37.9 / 18.0
     (5120, 1120, 51, 1, 9),     # 71.2 / 22.8
     (1280, 1888, 97, 2, 15),    # 90.0 / 18.3
+    (128, 30848, 52, 1, 128),   # 27.9 with 256
     (30848, 5248, 143, 2, 2),   # with a pass of its own for the rest 217, without 246
 ])
 def test_dense_slices_where_they_measured_faster(plan, M, K, N, groups, slices):
